@@ -2,14 +2,21 @@
 // (the quantities of interest of Sec. 4: averages over realizations, the
 // asymptotic velocity of Sec. 5, the Kuramoto order parameter).
 //
-// One workgroup per group.  Thread t takes elements t, t + 256, ... in FP64;
-// partial sums are combined by a wavefront butterfly and then by wave index
-// through LDS, always in the same order, so results are bitwise
-// reproducible.  The spread is taken about the mean in a second pass over
-// the group (no cancellation from sum of squares minus squared sum).
+// A group is reduced in slices of at most kObsThreads * kObsItems elements,
+// one workgroup each, that are read once: the workgroup holds its slice in
+// registers (FP64), sums it, and takes the spread about the slice's own mean
+// from the registers (no cancellation from sum of squares minus squared
+// sum).  A second kernel combines a group's slices in a fixed order: the
+// mean from the sums, and about it
+//   sum (x - mean)^2 = sum_s [ M2_s + n_s (mean_s - mean)^2 ].
+// Groups that fit one slice are finished by the first kernel.  All sums run
+// in a fixed order (elements by thread, wavefront butterfly, waves, slices),
+// so results are bitwise reproducible.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "device_common.h"
 #include "sde_internal.h"
@@ -31,54 +38,130 @@ __device__ double block_sum(double x, double* lds)
     return t;
 }
 
-template <typename T>
-__device__ __forceinline__ double load_value(const void* in, uint64_t i, int square)
+// Elements per lane of a slice.  One workgroup per group and two passes over
+// it (the earlier kernel) read a single group of 2^19 values with one CU:
+// 580-930 us; in slices of 1024-4096 the same call takes 24 us, its launches
+// and the final synchronization.
+constexpr int kObsItems = 16;
+
+struct ObsArgs {
+    const void* in;
+    const uint64_t* first;         // [n_groups] first element of the group
+    const uint32_t* counts;        // [n_groups]
+    const uint32_t* slice_begin;   // [n_groups + 1] slices before the group
+    double* part;                  // [slices][2]: (sum, M2 about the slice's mean), or (sum cos, sum sin)
+    double* out;                   // [n_groups][2], pinned host memory
+    uint32_t n_groups, slice;      // slice: elements per slice, at most kObsThreads * kObsItems
+};
+
+// A slice's two sums (every thread has them): (sum, M2 about its mean) or,
+// for the order parameter, (sum cos, sum sin) in FP64.
+template <int KIND, int ITEMS>
+__device__ __forceinline__ void obs_slice(const void* in, uint64_t base, uint32_t n, double* lds, double& a, double& b)
 {
-    const double x = (double)static_cast<const T*>(in)[i];
-    return square ? x * x : x;
+    using T = typename std::conditional<KIND == SDE_OBS_MEAN_F64, double, float>::type;
+    const T* p = static_cast<const T*>(in) + base;
+    T raw[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const uint32_t i = k * kObsThreads + threadIdx.x;
+        raw[k] = i < n ? p[i] : T(0);
+    }
+    a = 0.0;
+    b = 0.0;
+    if constexpr (KIND == SDE_OBS_ORDER) {
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            if ((uint32_t)(k * kObsThreads) + threadIdx.x >= n) break;
+            double sn, cs;
+            sincospi(2.0 * (double)raw[k], &sn, &cs);
+            a += cs;
+            b += sn;
+        }
+        a = block_sum(a, lds);
+        b = block_sum(b, lds);
+    } else {
+        double x[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            x[k] = (double)raw[k];
+            if (KIND == SDE_OBS_MEANSQ_F32) x[k] *= x[k];
+            a += x[k];  // lanes past the end hold zero
+        }
+        a = block_sum(a, lds);
+        const double mean = a / (double)n;
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) {
+            const double d = (uint32_t)(k * kObsThreads) + threadIdx.x < n ? x[k] - mean : 0.0;
+            b += d * d;
+        }
+        b = block_sum(b, lds);
+    }
 }
 
-__global__ __launch_bounds__(kObsThreads) void obs_kernel(int kind, const void* in, const uint64_t* first,
-                                                          const uint32_t* counts, double* out)
+__device__ __forceinline__ void obs_finish(int kind, uint32_t n, double a, double b, double* out)
+{
+    if (kind == SDE_OBS_ORDER) {
+        const double inv = n ? 1.0 / (double)n : 0.0;
+        out[0] = std::sqrt(a * a + b * b) * inv;
+        out[1] = n ? atan2(b, a) / (2.0 * M_PI) : 0.0;
+    } else {
+        out[0] = n ? a / (double)n : 0.0;
+        out[1] = n > 1 ? std::sqrt(b / (double)(n - 1) / (double)n) : 0.0;
+    }
+}
+
+// One workgroup per slice; a group of one slice (or none) is finished here.
+template <int KIND, int ITEMS>
+__global__ __launch_bounds__(kObsThreads) void obs_slice_kernel(ObsArgs A)
 {
     __shared__ double lds[kObsThreads / kWave];
-    const uint32_t g = blockIdx.x;
-    const uint64_t base = first[g];
-    const uint32_t n = counts[g];
-    if (kind == SDE_OBS_ORDER) {
-        double c = 0.0, s = 0.0;
-        for (uint32_t i = threadIdx.x; i < n; i += kObsThreads) {
-            double sn, cs;
-            sincospi(2.0 * (double)static_cast<const float*>(in)[base + i], &sn, &cs);
-            c += cs;
-            s += sn;
+    // the group of this slice: the last one whose slices begin at or before it
+    uint32_t lo = 0, hi = A.n_groups;
+    while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (A.slice_begin[mid] <= blockIdx.x)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    const uint32_t sl = blockIdx.x - A.slice_begin[lo], n = A.counts[lo];
+    const uint64_t off = (uint64_t)sl * A.slice;
+    const uint32_t cnt = (uint32_t)min((uint64_t)A.slice, (uint64_t)n - off);
+    double a, b;
+    obs_slice<KIND, ITEMS>(A.in, A.first[lo] + off, cnt, lds, a, b);
+    if (threadIdx.x) return;
+    if (n <= A.slice)
+        obs_finish(KIND, n, a, b, A.out + 2 * (uint64_t)lo);
+    else {
+        A.part[2 * (uint64_t)blockIdx.x] = a;
+        A.part[2 * (uint64_t)blockIdx.x + 1] = b;
+    }
+}
+
+// One workgroup per group of more than one slice: its slices, in order.
+__global__ __launch_bounds__(kObsThreads) void obs_combine_kernel(ObsArgs A, int kind)
+{
+    __shared__ double lds[kObsThreads / kWave];
+    const uint32_t g = blockIdx.x, n = A.counts[g];
+    if (n <= A.slice) return;
+    const uint32_t s0 = A.slice_begin[g], ns = A.slice_begin[g + 1] - s0;
+    const double* p = A.part + 2 * (uint64_t)s0;
+    double a = 0.0, b = 0.0;
+    for (uint32_t i = threadIdx.x; i < ns; i += kObsThreads) a += p[2 * (uint64_t)i];
+    a = block_sum(a, lds);
+    const double mean = a / (double)n;
+    for (uint32_t i = threadIdx.x; i < ns; i += kObsThreads) {
+        b += p[2 * (uint64_t)i + 1];
+        if (kind != SDE_OBS_ORDER) {
+            const double cnt = (double)min((uint64_t)A.slice, (uint64_t)n - (uint64_t)i * A.slice);
+            const double m = p[2 * (uint64_t)i] / cnt;
+            const double d = m == mean ? 0.0 : m - mean;  // equal infinities: the slice's own spread stands
+            b += cnt * (d * d);
         }
-        c = block_sum(c, lds);
-        s = block_sum(s, lds);
-        if (threadIdx.x == 0) {
-            const double inv = n ? 1.0 / (double)n : 0.0;
-            out[2 * g] = std::sqrt(c * c + s * s) * inv;
-            out[2 * g + 1] = n ? atan2(s, c) / (2.0 * M_PI) : 0.0;
-        }
-        return;
     }
-    const int square = kind == SDE_OBS_MEANSQ_F32;
-    double sum = 0.0;
-    for (uint32_t i = threadIdx.x; i < n; i += kObsThreads)
-        sum += kind == SDE_OBS_MEAN_F64 ? load_value<double>(in, base + i, 0) : load_value<float>(in, base + i, square);
-    sum = block_sum(sum, lds);
-    const double mean = n ? sum / (double)n : 0.0;
-    double ss = 0.0;
-    for (uint32_t i = threadIdx.x; i < n; i += kObsThreads) {
-        const double x = kind == SDE_OBS_MEAN_F64 ? load_value<double>(in, base + i, 0)
-                                                  : load_value<float>(in, base + i, square);
-        ss += (x - mean) * (x - mean);
-    }
-    ss = block_sum(ss, lds);
-    if (threadIdx.x == 0) {
-        out[2 * g] = mean;
-        out[2 * g + 1] = n > 1 ? std::sqrt(ss / (double)(n - 1) / (double)n) : 0.0;
-    }
+    b = block_sum(b, lds);
+    if (threadIdx.x == 0) obs_finish(kind, n, a, b, A.out + 2 * (uint64_t)g);
 }
 
 // ---- coarse-grained position histogram (one bin per potential period) ----
@@ -210,33 +293,91 @@ int phase_histogram_impl(sde_ctx* ctx, const float* theta, uint64_t n, uint64_t 
     return SDE_OK;
 }
 
+template <int ITEMS>
+static void launch_obs(int kind, const ObsArgs& A, uint32_t slices, hipStream_t stream)
+{
+    const dim3 grid(slices), block(kObsThreads);
+    switch (kind) {
+    case SDE_OBS_MEAN_F32: hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_MEAN_F32, ITEMS>), grid, block, 0, stream, A); break;
+    case SDE_OBS_MEAN_F64: hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_MEAN_F64, ITEMS>), grid, block, 0, stream, A); break;
+    case SDE_OBS_MEANSQ_F32:
+        hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_MEANSQ_F32, ITEMS>), grid, block, 0, stream, A);
+        break;
+    default: hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_ORDER, ITEMS>), grid, block, 0, stream, A); break;
+    }
+}
+
 int observables_impl(sde_ctx* ctx, int kind, const void* in, const uint32_t* counts, uint32_t n_groups,
                      double* host_out, hipStream_t stream)
 {
     if (kind < SDE_OBS_MEAN_F32 || kind > SDE_OBS_ORDER) return fail(ctx, SDE_ERR_INVALID, "unknown kind %d", kind);
     if (!in || !counts || !host_out || n_groups == 0) return fail(ctx, SDE_ERR_INVALID, "null argument or no groups");
     if (!aligned(in, kind == SDE_OBS_MEAN_F64 ? 8 : 4)) return fail(ctx, SDE_ERR_INVALID, "misaligned input");
-    // layout of the workspace: first[n_groups] (u64) | counts[n_groups] (u32) | out[n_groups][2]
-    std::vector<unsigned char> meta((size_t)n_groups * 12);
-    uint64_t off = 0;
+    uint64_t total = 0;
+    for (uint32_t g = 0; g < n_groups; ++g) total += counts[g];
+    // Slices of 4 elements per lane until there are 4 workgroups per CU, then
+    // of up to 16 (fewer partials for the same bandwidth).
+    int items = 4;
+    while (items < kObsItems && total / ((uint64_t)items * kObsThreads) >= 4ull * ctx->n_cu) items *= 2;
+    ObsArgs A;
+    A.slice = (uint32_t)items * kObsThreads;
+    // layout of the workspace: first[n_groups] (u64) | counts[n_groups] (u32) | slice_begin[n_groups + 1] (u32)
+    std::vector<unsigned char> meta((size_t)n_groups * 16 + 4);
+    uint64_t off = 0, slices = 0;
+    bool split = false;
     for (uint32_t g = 0; g < n_groups; ++g) {
+        const uint32_t s32 = (uint32_t)slices;
         std::memcpy(meta.data() + 8 * (size_t)g, &off, 8);
+        std::memcpy(meta.data() + 12 * (size_t)n_groups + 4 * (size_t)g, &s32, 4);
         off += counts[g];
+        slices += counts[g] ? ((uint64_t)counts[g] + A.slice - 1) / A.slice : 1;  // an empty group still has a result
+        split |= counts[g] > A.slice;
+        if (slices > 0x7fffffffull) return fail(ctx, SDE_ERR_INVALID, "observables: too many elements in one call");
     }
+    const uint32_t all = (uint32_t)slices;
+    std::memcpy(meta.data() + 16 * (size_t)n_groups, &all, 4);
     std::memcpy(meta.data() + 8 * (size_t)n_groups, counts, 4 * (size_t)n_groups);
     int st = upload(ctx, kSlotMisc, 3, meta.data(), meta.size(), stream);
     if (st) return st;
-    void* outbuf = nullptr;
-    if ((st = ensure_ws(ctx, kSlotObs, (size_t)n_groups * 2 * sizeof(double), &outbuf))) return st;
+    // The results (16 B a group) go straight to pinned host memory, which the
+    // final synchronization makes visible: no copy after the kernels (a call
+    // on one group of 2^19 values 33 -> 24 us).
+    const size_t out_bytes = (size_t)n_groups * 2 * sizeof(double);
+    DevBuf& host = ctx->obs_host;
+    if (host.bytes < out_bytes) {
+        if (host.ptr) SDE_HIP(ctx, hipHostFree(host.ptr));  // every earlier call has synchronized
+        host.ptr = nullptr;
+        host.bytes = 0;
+        const size_t cap = std::max<size_t>(4096, out_bytes + out_bytes / 4);
+        if (hipHostMalloc(&host.ptr, cap, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            host.ptr = nullptr;
+            return fail(ctx, SDE_ERR_NOMEM, "observables: cannot allocate %zu bytes of pinned memory", cap);
+        }
+        host.bytes = cap;
+    }
+    void* part = nullptr;
+    if (split && (st = ensure_ws(ctx, kSlotObs, (size_t)slices * 2 * sizeof(double), &part))) return st;
     const unsigned char* dmeta = static_cast<const unsigned char*>(ctx->ws[kSlotMisc].ptr);
-    hipLaunchKernelGGL(obs_kernel, dim3(n_groups), dim3(kObsThreads), 0, stream, kind, in,
-                       reinterpret_cast<const uint64_t*>(dmeta),
-                       reinterpret_cast<const uint32_t*>(dmeta + 8 * (size_t)n_groups),
-                       static_cast<double*>(outbuf));
+    A.in = in;
+    A.first = reinterpret_cast<const uint64_t*>(dmeta);
+    A.counts = reinterpret_cast<const uint32_t*>(dmeta + 8 * (size_t)n_groups);
+    A.slice_begin = A.counts + n_groups;
+    A.out = static_cast<double*>(host.ptr);
+    A.part = static_cast<double*>(part);
+    A.n_groups = n_groups;
+    switch (items) {
+    case 4: launch_obs<4>(kind, A, all, stream); break;
+    case 8: launch_obs<8>(kind, A, all, stream); break;
+    default: launch_obs<16>(kind, A, all, stream); break;
+    }
     SDE_HIP(ctx, hipGetLastError());
-    SDE_HIP(ctx, hipMemcpyAsync(host_out, outbuf, (size_t)n_groups * 2 * sizeof(double), hipMemcpyDeviceToHost,
-                                stream));
+    if (split) {
+        hipLaunchKernelGGL(obs_combine_kernel, dim3(n_groups), dim3(kObsThreads), 0, stream, A, kind);
+        SDE_HIP(ctx, hipGetLastError());
+    }
     SDE_HIP(ctx, hipStreamSynchronize(stream));
+    std::memcpy(host_out, host.ptr, out_bytes);
     return SDE_OK;
 }
 

@@ -288,6 +288,7 @@ void sde_destroy(sde_ctx* ctx)
     }
     for (auto& g : ctx->graphs) drop_graph(g);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
+    if (ctx->obs_host.ptr) (void)hipHostFree(ctx->obs_host.ptr);
     if (ctx->noalloc_staging) (void)hipHostFree(ctx->noalloc_staging);
     if (ctx->noalloc_done) (void)hipEventDestroy(ctx->noalloc_done);
     if (ctx->flag) (void)hipFree(ctx->flag);

@@ -74,6 +74,7 @@ struct sde_ctx {
                                   // 7, 8: row-half waves with two register sets, bands / plain order;
                                   // 9, 10: 4 waves with K double-buffered in LDS, bands / plain order;
                                   // 11, 12: wave pairs sharing K through LDS, bands / plain order
+    sde::DevBuf obs_host;         // pinned host memory the observables kernels write their results to
     std::map<std::string, int> tune;
     std::string tune_path;
     sde_stats last{};
