@@ -348,20 +348,34 @@ __global__ __launch_bounds__(256) void jj_persistent_kernel(JJArgs A)
     }
 }
 
-// Stage 2: per point, the chunk partials in chunk order.
+// Stage 2: per point, its chunk partials -- one wavefront a point, lane l
+// adding chunks l, l + 64, ..., then the fixed butterfly.  (One thread a point
+// walked its chunks one load latency at a time: 195 us for the 2048 chunks of
+// a single point of 2^18 paths, a quarter of that call; 17 us for a ragged
+// batch.)
+constexpr uint32_t kPointSumWaves = 4;  // points per workgroup
+
 template <typename R>
-__global__ void jj_point_sums_kernel(const JJPointT<R>* pts, uint32_t n_pts, const double* partials, double* out)
+__global__ __launch_bounds__(kPointSumWaves* kWave) void jj_point_sums_kernel(const JJPointT<R>* pts, uint32_t n_pts,
+                                                                              const double* partials, double* out)
 {
-    const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t q = blockIdx.x * kPointSumWaves + threadIdx.x / kWave;
     if (q >= n_pts) return;
-    const uint32_t first = pts[q].chunk_first, nc = pts[q].n_chunks;
+    const uint32_t first = pts[q].chunk_first, nc = pts[q].n_chunks, lane = threadIdx.x & (kWave - 1);
+    const double2* p = reinterpret_cast<const double2*>(partials) + first;
     double s1 = 0.0, s2 = 0.0;
-    for (uint32_t c = 0; c < nc; ++c) {
-        s1 += partials[2 * (first + c)];
-        s2 += partials[2 * (first + c) + 1];
+#pragma unroll 4
+    for (uint32_t c = lane; c < nc; c += kWave) {
+        const double2 x = p[c];
+        s1 += x.x;
+        s2 += x.y;
     }
-    out[2 * q] = s1;
-    out[2 * q + 1] = s2;
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if (lane == 0) {
+        out[2 * (uint64_t)q] = s1;
+        out[2 * (uint64_t)q + 1] = s2;
+    }
 }
 
 // Test hooks: raw Philox words and the integrators' Gaussians.
@@ -517,8 +531,9 @@ static int jj_record(sde_ctx* ctx, const JJLaunch& L, hipStream_t s)
         SDE_HIP(ctx, hipGetLastError());
     }
     if (L.point_sums) {
-        hipLaunchKernelGGL(jj_point_sums_kernel<R>, dim3((L.n_pts + 255) / 256), dim3(256), 0, s,
-                           static_cast<const JJPointT<R>*>(L.A.pts), L.n_pts, L.A.partials, L.point_sums);
+        hipLaunchKernelGGL(jj_point_sums_kernel<R>, dim3((L.n_pts + kPointSumWaves - 1) / kPointSumWaves),
+                           dim3(kPointSumWaves * kWave), 0, s, static_cast<const JJPointT<R>*>(L.A.pts), L.n_pts,
+                           static_cast<const double*>(L.A.partials), L.point_sums);
         SDE_HIP(ctx, hipGetLastError());
     }
     return SDE_OK;
