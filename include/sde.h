@@ -174,9 +174,10 @@ int sde_jj_integrate(sde_ctx* ctx, const sde_jj_point* pts /* [host] */, uint32_
  * ends), whose address sde_create looks up once per device; the host image
  * of the tables goes through a pinned buffer that sde_create reserves
  * (8 MiB per context).  No graphs are recorded and nothing is tuned: the
- * paths per lane are the forced option, else a choice the autotuner of
- * sde_jj_integrate cached for this shape class, else 2 (the result does not
- * depend on it).  Host-side planning uses ordinary heap memory.
+ * launch is the forced option, else a choice the autotuner of
+ * sde_jj_integrate cached for this shape class, else the untuned default (2
+ * paths per lane; 1 for calls too small to fill the chip); the paths do not
+ * depend on it.  Host-side planning uses ordinary heap memory.
  * Every call on one GPU shares that GPU's array, which keeps the last
  * call's contents (the queue words are cleared by each call): calls that
  * overlap on one GPU -- from several contexts, or on streams not ordered
@@ -417,8 +418,10 @@ enum {
     SDE_OPT_GRAPHS = 2,   /* 1 (default): record each call's launch sequence once in */
                           /* a HIP graph keyed by its arguments and replay it; 0:    */
                           /* launch kernels directly                                 */
-    SDE_OPT_JJ_PPT = 3,   /* Josephson-junction paths per lane: 0 (default) = tuned, */
-                          /* or 1, 2, 4 to force                                     */
+    SDE_OPT_JJ_PPT = 3,   /* Josephson-junction paths per lane: 0 (default) = tuned  */
+                          /* (calls too small to fill the chip may run 1 path per    */
+                          /* lane with the noise drawn by other waves), or 1, 2, 4   */
+                          /* to force that many in the persistent kernel             */
     SDE_OPT_KURA_MF = 4,  /* mean-field variant: 0 (default) = registers when the    */
                           /* realization fits (N <= 2^19 on 256 CUs), else streamed  */
                           /* through HBM; 1 = always streamed; 2 = always registers  */

@@ -183,10 +183,81 @@ __device__ __forceinline__ void jj_step(const JJPointT<R>& P, R e0, R e1, const 
     }
 }
 
-template <typename R, int PPT, int SCHEME, bool INERTIAL, bool COSF>
-__device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t chunk)
+// Where an item's noise and drive come from: blocks in ascending order, each
+// taken once, avail() of them (at least one after ensure()) without another
+// ensure().  take() gives the four Gaussians of block b of each path and, for
+// a whole block that begins at drive phase kk, the drive terms e of its steps.
+//
+// Drawn by the wave itself, right where it is used.
+template <typename R, int PPT>
+struct OwnNoise {
+    uint32_t key0, key1, q;
+    const uint32_t (&pid)[PPT];
+    R c2, a_im, f_im;
+    const R* lut;
+    static constexpr uint32_t kUnroll = 1;
+
+    __device__ __forceinline__ void ensure() {}
+    __device__ __forceinline__ uint32_t avail() const { return 1u << 28; }
+    template <int N>
+    __device__ __forceinline__ void take(uint32_t b, uint32_t kk, R (&g)[N][PPT][4], R (&e)[N][5])
+    {
+        static_assert(N == 1, "one block at a time");
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) jj_gauss4(U4{b, pid[k], q, (uint32_t)SDE_TAG_NOISE}, key0, key1, c2, g[0][k]);
+#pragma unroll
+        for (int j = 0; j < 5; ++j) e[0][j] = fm(a_im, load_uniform(lut + kk + j), f_im);
+    }
+};
+
+// Drawn ahead by other waves of the workgroup into a double-buffered LDS ring
+// (kBlocks blocks per buffer, one barrier per buffer): see jj_split_kernel.
+template <typename R>
+struct JJRing {
+    static constexpr uint32_t kBlocks = 64 / sizeof(R);  // 16 KB per buffer
+    R g[2 * kBlocks][kWave][4];
+    R e[2 * kBlocks][8];  // the drive terms, the same for every lane
+};
+
+template <typename R>
+struct RingNoise {
+    // Blocks taken per loop iteration: a wave alone on its SIMD issues an
+    // instruction every ~6 cycles whatever it is, so the loop's scalar work
+    // and register copies count like the steps.
+    static constexpr uint32_t kUnroll = 4;
+    static constexpr uint32_t kBlocks = JJRing<R>::kBlocks;
+    const JJRing<R>& ring;
+    uint32_t left = 0, at = 0;  // blocks left in the current buffer; its next slot
+
+    __device__ __forceinline__ void ensure()
+    {
+        if (left) return;
+        __syncthreads();  // the other buffer is full, and its writers go on to the one just used up
+        at = at == 2 * kBlocks ? 0u : at;
+        left = kBlocks;
+    }
+    __device__ __forceinline__ uint32_t avail() const { return left; }
+    template <int N>
+    __device__ __forceinline__ void take(uint32_t, uint32_t, R (&g)[N][1][4], R (&e)[N][5])
+    {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) e[i][j] = ring.e[at + i][j];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) g[i][0][j] = ring.g[at + i][threadIdx.x & (kWave - 1)][j];
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) e[i][4] = i + 1 < N ? e[i + 1][0] : ring.e[at + i][4];
+        left -= N;
+        at += N;
+    }
+};
+
+template <typename R, int PPT, int SCHEME, bool INERTIAL, bool COSF, typename Noise>
+__device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, uint32_t q, uint32_t chunk,
+                                        const uint32_t (&pid)[PPT], Noise& src)
 {
-    const JJPointT<R> P = load_uniform(static_cast<const JJPointT<R>*>(A.pts) + q);
     const uint32_t lane = threadIdx.x & (kWave - 1);
     R* theta = static_cast<R*>(A.theta);
     R* vel = static_cast<R*>(A.v);
@@ -194,11 +265,9 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
     R th[PPT], vv[PPT], af[PPT];
     int32_t wd[PPT];
     double ad[PPT];
-    uint32_t pid[PPT];
     bool live[PPT];
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
-        pid[k] = chunk * (kWave * PPT) + k * kWave + lane;
         live[k] = pid[k] < P.n_paths;
         const uint64_t gi = P.path_first + pid[k];
         if (A.init_from_state) {
@@ -220,7 +289,15 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
     const uint64_t n_end = A.step0 + P.n_steps;
     uint64_t n = A.step0;
     uint32_t kk = (uint32_t)(n % P.S);               // drive phase index of step n
-    uint32_t to_fold = A.M - (uint32_t)(n % A.M);    // steps until the next multiple of M
+    // steps until the next multiple of M, kept from the window's start on (no
+    // sum is open before it, so folds there would add nothing)
+    uint32_t to_fold = 0;
+    bool opened = false;
+    auto open_window = [&]() {
+        if (opened) return;
+        opened = true;
+        to_fold = A.M - (uint32_t)(n % A.M);
+    };
     // recording: rc = n mod rec_every; row r holds the state after the
     // (r + 1)-th multiple of rec_every past step0
     uint32_t rc = A.rec ? (uint32_t)(n % A.rec_every) : 0u;
@@ -233,12 +310,6 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
             af[k] = R(0);
         }
         to_fold = A.M;
-    };
-    // sigma * Gaussians of steps 4b .. 4b + 3 of each path
-    auto noise = [&](uint32_t b, R (&g)[PPT][4]) {
-#pragma unroll
-        for (int k = 0; k < PPT; ++k)
-            jj_gauss4(U4{b, pid[k], q, (uint32_t)SDE_TAG_NOISE}, A.key0, A.key1, P.c2, g[k]);
     };
     // keep theta in [0, 1): move whole revolutions into the winding count
     auto wrap = [&]() {
@@ -257,30 +328,46 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
             if (live[k]) out[pid[k]] = wd[k];
         ++row;
     };
-    // `count` whole 4-step blocks with nothing but steps in them
-    auto run_blocks = [&](auto in_window, uint32_t count) {
-        uint32_t blk = (uint32_t)(n >> 2);
-        for (uint32_t i = 0; i < count; ++i, ++blk) {
-            R g[PPT][4], e[5];
-            noise(blk, g);
-#pragma unroll
-            for (int j = 0; j < 5; ++j) e[j] = fm(P.a_im, load_uniform(lut + kk + j), P.f_im);
-            kk += 4;
-            kk -= kk >= P.S ? P.S : 0u;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                R ns[PPT];
-#pragma unroll
-                for (int k = 0; k < PPT; ++k) ns[k] = g[k][j];
-                jj_step<R, PPT, SCHEME, INERTIAL, COSF, decltype(in_window)::value>(P, e[j], e[j + 1], ns, th, vv, af);
+    // `count` whole 4-step blocks with nothing but steps in them, U at a time
+    auto run_some = [&](auto in_window, auto unroll, uint32_t iterations, uint32_t blk) {
+        constexpr uint32_t U = decltype(unroll)::value;
+        for (uint32_t i = 0; i < iterations; ++i, blk += U) {
+            R g[U][PPT][4], e[U][5];
+            src.take(blk, kk, g, e);
+            if constexpr (Noise::kUnroll == 1) {
+                kk += 4;
+                kk -= kk >= P.S ? P.S : 0u;
             }
-            wrap();
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    R ns[PPT];
+#pragma unroll
+                    for (int k = 0; k < PPT; ++k) ns[k] = g[u][k][j];
+                    jj_step<R, PPT, SCHEME, INERTIAL, COSF, decltype(in_window)::value>(P, e[u][j], e[u][j + 1], ns,
+                                                                                       th, vv, af);
+                }
+                wrap();
+            }
+        }
+    };
+    auto run_blocks = [&](auto in_window, uint32_t count) {
+        constexpr uint32_t U = Noise::kUnroll;
+        const uint32_t blk = (uint32_t)(n >> 2);
+        run_some(in_window, std::integral_constant<uint32_t, U>{}, count / U, blk);
+        if constexpr (U > 1) {
+            run_some(in_window, std::integral_constant<uint32_t, 1>{}, count % U, blk + count / U * U);
+            kk += 4 * count;  // the source holds the drive: the phase only matters afterwards
+            kk -= kk >= P.S ? P.S : 0u;
+            if (kk >= P.S) kk %= P.S;
         }
     };
 
     while (n < n_end) {
         const uint32_t j0 = (uint32_t)n & 3u;
         const uint64_t left = n_end - n;
+        src.ensure();
         if (j0 == 0 && left >= 4 && P.S >= 4) {
             // The whole blocks up to the next event: the end of the call, the
             // start of the window, the block that a fold falls into (or ends
@@ -292,12 +379,13 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
             // 18.4 -> 17.7 ms; a ragged batch 4.41 -> 3.72 ms).
             const bool window = n >= P.n_transient;
             uint64_t blocks = left >> 2;
-            if (window)
+            if (window) {
+                open_window();
                 blocks = min(blocks, (uint64_t)(to_fold >> 2));
-            else
+            } else
                 blocks = min(blocks, (P.n_transient - n) >> 2);
             if (A.rec) blocks = min(blocks, (uint64_t)((A.rec_every - rc) >> 2));
-            const uint32_t count = (uint32_t)min(blocks, (uint64_t)1 << 28);
+            const uint32_t count = (uint32_t)min(blocks, (uint64_t)src.avail());
             if (count) {
                 if (window) {
                     run_blocks(std::true_type{}, count);
@@ -307,8 +395,6 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
                     run_blocks(std::false_type{}, count);
                 }
                 n += 4 * (uint64_t)count;
-                // no sum is open before the window, so folds there add nothing
-                if (!window) to_fold = A.M - (uint32_t)(n % A.M);
                 if (A.rec) {
                     rc += 4 * count;
                     if (rc == A.rec_every) record();
@@ -319,16 +405,18 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
         // one block step by step: a first or last partial one, one the window
         // begins in, or one with a fold between its steps
         const uint32_t jn = left >= (uint64_t)(4u - j0) ? 4u : j0 + (uint32_t)left;
-        R g[PPT][4];
-        noise((uint32_t)(n >> 2), g);
+        R g[1][PPT][4], unused[1][5];  // the drive terms are taken step by step
+        src.take((uint32_t)(n >> 2), 0u, g, unused);
         auto step = [&](const R (&ns)[PPT]) {
             const R ea = fm(P.a_im, load_uniform(lut + kk), P.f_im);
             const R eb = fm(P.a_im, load_uniform(lut + kk + 1), P.f_im);
-            if (n >= P.n_transient)
+            if (n >= P.n_transient) {
+                open_window();
                 jj_step<R, PPT, SCHEME, INERTIAL, COSF, true>(P, ea, eb, ns, th, vv, af);
-            else
+                if (--to_fold == 0) fold();
+            } else {
                 jj_step<R, PPT, SCHEME, INERTIAL, COSF, false>(P, ea, eb, ns, th, vv, af);
-            if (--to_fold == 0) fold();
+            }
             ++n;
             kk = (kk + 1 == P.S) ? 0u : kk + 1;
         };
@@ -337,7 +425,7 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
             for (int j = 0; j < 4; ++j) {
                 R ns[PPT];
 #pragma unroll
-                for (int k = 0; k < PPT; ++k) ns[k] = g[k][j];
+                for (int k = 0; k < PPT; ++k) ns[k] = g[0][k][j];
                 step(ns);
             }
         } else {
@@ -345,7 +433,7 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, uint32_t q, uint32_t ch
                 R ns[PPT];
 #pragma unroll
                 for (int k = 0; k < PPT; ++k)
-                    ns[k] = j == 0 ? g[k][0] : j == 1 ? g[k][1] : j == 2 ? g[k][2] : g[k][3];
+                    ns[k] = j == 0 ? g[0][k][0] : j == 1 ? g[0][k][1] : j == 2 ? g[0][k][2] : g[0][k][3];
                 step(ns);
             }
         }
@@ -393,7 +481,57 @@ __global__ __launch_bounds__(256) void jj_persistent_kernel(JJArgs A)
         item = uniform_u32(__shfl(item, 0, kWave));
         if (item >= A.n_items) break;
         const JJItem it = load_uniform(A.items + item);
-        jj_item<R, PPT, SCHEME, INERTIAL, COSF>(A, it.point, it.chunk);
+        const JJPointT<R> P = load_uniform(static_cast<const JJPointT<R>*>(A.pts) + it.point);
+        uint32_t pid[PPT];
+#pragma unroll
+        for (int k = 0; k < PPT; ++k) pid[k] = it.chunk * (kWave * PPT) + k * kWave + lane;
+        OwnNoise<R, PPT> src{A.key0, A.key1, it.point, pid, P.c2, P.a_im, P.f_im, static_cast<const R*>(A.lut) + P.lut_off};
+        jj_item<R, PPT, SCHEME, INERTIAL, COSF>(A, P, it.point, it.chunk, pid, src);
+    }
+}
+
+// The same integration for calls with too few paths to fill the chip, where
+// a wave is alone on its SIMD and waits out the latency of every dependent
+// instruction.  The noise does not depend on the path, so it leaves the
+// chain: one workgroup per item of 64 paths, wave 0 runs the steps, the other
+// waves (on SIMDs that would idle) draw the Gaussians of the blocks ahead
+// into LDS.  With kB the blocks of a ring buffer, block b of the call goes
+// through slot b mod 2 kB; the waves meet at one barrier per buffer: past
+// barrier c, buffer c mod 2 is full and its predecessor used up.  Every wave
+// of a workgroup passes exactly ceil(blocks / kB) barriers.
+constexpr int kSplitDrawers = 3;
+constexpr int kSplitThreads = (1 + kSplitDrawers) * kWave;
+
+template <typename R, int SCHEME, bool INERTIAL, bool COSF>
+__global__ __launch_bounds__(kSplitThreads) void jj_split_kernel(JJArgs A)
+{
+    __shared__ __attribute__((aligned(16))) JJRing<R> ring;
+    constexpr uint32_t kB = JJRing<R>::kBlocks;
+    const JJItem it = load_uniform(A.items + blockIdx.x);
+    const JJPointT<R> P = load_uniform(static_cast<const JJPointT<R>*>(A.pts) + it.point);
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = uniform_u32(threadIdx.x / kWave);
+    const uint32_t pid[1] = {it.chunk * kWave + lane};
+    if (wave == 0) {
+        RingNoise<R> src{ring};
+        jj_item<R, 1, SCHEME, INERTIAL, COSF>(A, P, it.point, it.chunk, pid, src);
+        return;
+    }
+    if (P.n_steps == 0) return;
+    const uint64_t b0 = A.step0 >> 2, blocks = ((A.step0 + P.n_steps - 1) >> 2) - b0 + 1;
+    const R* lut = static_cast<const R*>(A.lut) + P.lut_off;
+    uint32_t phase = (uint32_t)((4 * b0) % P.S);  // drive phase of the buffer's first block
+    for (uint64_t c = 0; c < blocks; c += kB) {
+        const uint32_t cnt = (uint32_t)min(blocks - c, (uint64_t)kB);
+        const uint32_t base = (c / kB) & 1u ? kB : 0u;
+        for (uint32_t i = wave - 1; i < cnt; i += kSplitDrawers) {
+            R g[4];
+            jj_gauss4(U4{(uint32_t)(b0 + c) + i, pid[0], it.point, (uint32_t)SDE_TAG_NOISE}, A.key0, A.key1, P.c2, g);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ring.g[base + i][lane][j] = g[j];
+            if (lane < 5) ring.e[base + i][lane] = fm(P.a_im, lut[(phase + 4 * i) % P.S + lane], P.f_im);
+        }
+        phase = (phase + 4 * kB) % P.S;
+        __syncthreads();
     }
 }
 
@@ -472,6 +610,18 @@ static JJKernel pick_kernel_t(int ppt, int scheme)
     return jj_persistent_kernel<R, 2, SDE_EULER, INERTIAL, COSF>;
 }
 
+template <typename R>
+static JJKernel pick_split(int kind, int scheme)
+{
+    const bool heun = scheme == SDE_HEUN;
+    switch (kind) {
+    case 0: return heun ? jj_split_kernel<R, SDE_HEUN, true, false> : jj_split_kernel<R, SDE_EULER, true, false>;
+    case 1: return heun ? jj_split_kernel<R, SDE_HEUN, false, false> : jj_split_kernel<R, SDE_EULER, false, false>;
+    case 2: return heun ? jj_split_kernel<R, SDE_HEUN, true, true> : jj_split_kernel<R, SDE_EULER, true, true>;
+    default: return heun ? jj_split_kernel<R, SDE_HEUN, false, true> : jj_split_kernel<R, SDE_EULER, false, true>;
+    }
+}
+
 // Point kinds, one persistent launch each: bit 0 = overdamped, bit 1 = the
 // sin(2 pi x) potential.
 constexpr int kJJKinds = 4;
@@ -528,10 +678,24 @@ static void plan_items(std::vector<JJPointT<R>>& P, const std::vector<int>& kind
     out.n_chunks = chunk_first;
 }
 
+// How the items run: 1, 2 or 4 paths per lane of the persistent kernel, or
+// kSplitChoice for jj_split_kernel (1 path per lane).  These are the values
+// the tune cache holds.
+constexpr int kSplitChoice = 17;
+
+// Most items (of 64 paths) per CU the split kernel is tried for, FP32 and
+// FP64.  With more, every SIMD has waves enough to switch between, and the
+// waves that draw ahead only take issue slots.  One point, 10^4 FP32 steps
+// (2000 FP64 steps), best persistent against split, us: 4096 paths 898 : 478
+// (782 : 417), 32768 (2 per CU) 907 : 615 (807 : 620), 65536 923 : 869
+// (840 : 1097), 98304 (6 per CU) 1492 : 1245, 131072 (8 per CU) 1503 : 1561.
+constexpr uint32_t kSplitItemsPerCU32 = 6, kSplitItemsPerCU64 = 2;
+
 struct JJLaunch {
     JJArgs A;
     uint32_t* queues;  // kJJKinds work-queue words, zeroed by each launch sequence
     int ppt;
+    bool split;  // jj_split_kernel (ppt = 1)
     int scheme;
     uint32_t kind_begin[kJJKinds + 1];
     uint32_t n_items, n_pts;
@@ -546,6 +710,10 @@ static int jj_grids(sde_ctx* ctx, JJLaunch& L)
         const uint32_t count = L.kind_begin[kind + 1] - L.kind_begin[kind];
         L.grid[kind] = 0;
         if (!count) continue;
+        if (L.split) {  // one workgroup per item
+            L.grid[kind] = count;
+            continue;
+        }
         JJKernel kern = pick_kernel<R>(kind, L.ppt, L.scheme);
         int per_cu = 0;
         SDE_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), 256, 0));
@@ -575,8 +743,8 @@ static int jj_record(sde_ctx* ctx, const JJLaunch& L, hipStream_t s)
         A.items = all + L.kind_begin[kind];
         A.n_items = L.kind_begin[kind + 1] - L.kind_begin[kind];
         A.queue = L.queues + kind;
-        JJKernel kern = pick_kernel<R>(kind, L.ppt, L.scheme);
-        hipLaunchKernelGGL(kern, dim3(L.grid[kind]), dim3(256), 0, s, A);
+        JJKernel kern = L.split ? pick_split<R>(kind, L.scheme) : pick_kernel<R>(kind, L.ppt, L.scheme);
+        hipLaunchKernelGGL(kern, dim3(L.grid[kind]), dim3(L.split ? kSplitThreads : 256), 0, s, A);
         SDE_HIP(ctx, hipGetLastError());
     }
     if (L.point_sums) {
@@ -599,10 +767,10 @@ static std::string jj_graph_key(const char* prec, const JJLaunch& L)
     char buf[640];
     snprintf(buf, sizeof buf,
              "jj|%s|pts%p|it%p|lut%p|q%p|fl%p|th%p|wd%p|v%p|acc%p|pa%p|rec%p/%llu/%u|n0%llu|k%u.%u|ni%u|M%u|ini%d|"
-             "ppt%d|sch%d|np%u|ps%p",
+             "ppt%d/%d|sch%d|np%u|ps%p",
              prec, A.pts, (const void*)A.items, A.lut, (void*)L.queues, (void*)A.flag, A.theta, (void*)A.winding, A.v,
              (void*)A.acc, (void*)A.partials, (void*)A.rec, (unsigned long long)A.rec_pitch, A.rec_every,
-             (unsigned long long)A.step0, A.key0, A.key1, L.n_items, A.M, A.init_from_state, L.ppt, L.scheme,
+             (unsigned long long)A.step0, A.key0, A.key1, L.n_items, A.M, A.init_from_state, L.ppt, (int)L.split, L.scheme,
              L.n_pts, (void*)L.point_sums);
     std::string k = buf;
     for (int kind = 0; kind < kJJKinds; ++kind)
@@ -641,12 +809,27 @@ static int ilog2u64(uint64_t x)
     return r;
 }
 
-// Times the candidate paths-per-lane choices on a short slice of the call
+static void set_choice(JJLaunch& L, int choice)
+{
+    L.split = choice == kSplitChoice;
+    L.ppt = L.split ? 1 : choice;
+}
+
+// Whether a call is small enough for the split kernel.
+template <typename R>
+static bool split_fits(const sde_ctx* ctx, const std::vector<JJPointT<R>>& P)
+{
+    uint64_t items = 0;
+    for (const auto& d : P) items += (d.n_paths + kWave - 1) / kWave;
+    return items <= (uint64_t)(sizeof(R) == 4 ? kSplitItemsPerCU32 : kSplitItemsPerCU64) * ctx->n_cu;
+}
+
+// Times the candidate choices on a short slice of the call
 // (same points, at most 2048 steps, no per-path outputs) and returns the
 // fastest.  Nothing the caller passed is written.
 template <typename R>
 static int jj_tune(sde_ctx* ctx, const std::vector<JJPointT<R>>& P0, const std::vector<int>& kinds,
-                   const JJLaunch& base, hipStream_t stream, int* best_ppt)
+                   const JJLaunch& base, hipStream_t stream, int* best_choice)
 {
     std::vector<JJPointT<R>> P = P0;
     uint64_t work = 0;
@@ -655,7 +838,7 @@ static int jj_tune(sde_ctx* ctx, const std::vector<JJPointT<R>>& P0, const std::
         work += (uint64_t)d.n_paths * d.n_steps;
     }
     if (work == 0) {
-        *best_ppt = 2;
+        *best_choice = 2;
         return SDE_OK;
     }
     hipEvent_t e0, e1;
@@ -663,12 +846,13 @@ static int jj_tune(sde_ctx* ctx, const std::vector<JJPointT<R>>& P0, const std::
     SDE_HIP(ctx, hipEventCreate(&e1));
     double best = 1e300;
     int st = SDE_OK;
-    const std::vector<int> cands = sizeof(R) == 4 ? std::vector<int>{1, 2, 4} : std::vector<int>{1, 2};
-    for (int ppt : cands) {
-        JJPlan<R> plan;
-        plan_items(P, kinds, ppt, plan);
+    std::vector<int> cands = sizeof(R) == 4 ? std::vector<int>{1, 2, 4} : std::vector<int>{1, 2};
+    if (split_fits(ctx, P)) cands.push_back(kSplitChoice);
+    for (int choice : cands) {
         JJLaunch L = base;
-        L.ppt = ppt;
+        set_choice(L, choice);
+        JJPlan<R> plan;
+        plan_items(P, kinds, L.ppt, plan);
         L.point_sums = nullptr;
         L.A.theta = nullptr;
         L.A.winding = nullptr;
@@ -691,7 +875,7 @@ static int jj_tune(sde_ctx* ctx, const std::vector<JJPointT<R>>& P0, const std::
         if (st) break;
         if (ms < best) {
             best = ms;
-            *best_ppt = ppt;
+            *best_choice = choice;
         }
     }
     (void)hipEventDestroy(e0);
@@ -831,6 +1015,13 @@ static void jj_fill_args(sde_ctx* ctx, const sde_run* run, const JJSetup<R>& S, 
     L.A.init_from_state = run->init == SDE_INIT_FROM_STATE;
 }
 
+// The choice of a call that is neither forced nor tuned.
+template <typename R>
+static int default_choice(const sde_ctx* ctx, const JJSetup<R>& S)
+{
+    return split_fits(ctx, S.P) ? kSplitChoice : 2;
+}
+
 // Tune-cache key of a call's shape class (paths per lane).
 template <typename R>
 static std::string jj_tune_key(sde_ctx* ctx, const sde_run* run, const JJSetup<R>& S)
@@ -870,27 +1061,30 @@ static int jj_integrate_t(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_pts,
     L.A.rec_every = rec ? rec_every : 0u;
     const char* prec = sizeof(R) == 4 ? "f32" : "f64";
 
-    // paths per lane: forced, cached, or tuned on this call's shape class
-    int ppt = ctx->jj_ppt;
-    if (sizeof(R) == 8 && ppt == 4) ppt = 2;
-    if (!ppt) {
+    // the launch choice: paths per lane as forced, cached, or tuned on this
+    // call's shape class
+    int choice = ctx->jj_ppt;
+    if (sizeof(R) == 8 && choice == 4) choice = 2;
+    if (!choice) {
         const std::string key = jj_tune_key<R>(ctx, run, S);
-        if (!tune_lookup(ctx, key, &ppt)) {
-            ppt = 2;
+        if (!tune_lookup(ctx, key, &choice)) {
+            choice = default_choice(ctx, S);
             if (ctx->autotune) {
                 const auto t0 = std::chrono::steady_clock::now();
-                if ((st = jj_tune<R>(ctx, S.P, S.kinds, L, stream, &ppt))) return st;
+                if ((st = jj_tune<R>(ctx, S.P, S.kinds, L, stream, &choice))) return st;
                 ctx->last.tuned = 1;
                 ctx->last.tune_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-                tune_store(ctx, key, ppt);
+                tune_store(ctx, key, choice);
             }
         }
     }
-    L.ppt = ppt;
+    // a choice cached for a smaller call of the class
+    if (choice == kSplitChoice && !split_fits(ctx, S.P)) choice = 1;
+    set_choice(L, choice);
     JJPlan<R> plan;
-    plan_items(S.P, S.kinds, ppt, plan);
+    plan_items(S.P, S.kinds, L.ppt, plan);
     if ((st = jj_upload_plan(ctx, plan, stream, L))) return st;
-    ctx->last.jj_paths_per_lane = ppt;
+    ctx->last.jj_paths_per_lane = L.ppt;
     ctx->last.work_items = plan.items.size();
 
     if ((st = run_recorded(ctx, jj_graph_key(prec, L), stream, [&](hipStream_t s) { return jj_record<R>(ctx, L, s); })))
@@ -969,24 +1163,29 @@ int jj_integrate_noalloc_impl(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_
     JJSetup<float> S;
     int st = jj_setup<float>(ctx, pts, n_pts, run, theta, winding, v, acc, point_sums, S);
     if (st) return st;
-    // paths per lane: forced, else a choice the tuner cached, else 2; never
-    // tuned here (tuning allocates)
-    int ppt = ctx->jj_ppt;
-    if (!ppt && !tune_lookup(ctx, jj_tune_key<float>(ctx, run, S), &ppt)) ppt = 2;
-    JJPlan<float> plan;
-    plan_items(S.P, S.kinds, ppt, plan);
+    // paths per lane: forced, else a choice the tuner cached, else the
+    // default; never tuned here (tuning allocates)
+    int choice = ctx->jj_ppt;
+    if (!choice && !tune_lookup(ctx, jj_tune_key<float>(ctx, run, S), &choice)) choice = default_choice(ctx, S);
+    if (choice == kSplitChoice && !split_fits(ctx, S.P)) choice = 1;
 
     // layout of the scratch; the tables [o_pts, o_part) are one host image
-    const size_t pts_bytes = plan.pts.size() * sizeof(JJPointDev);
-    const size_t items_bytes = plan.items.size() * sizeof(JJItem);
-    const size_t lut_bytes = S.lut.size() * sizeof(float);
-    const size_t part_bytes = (size_t)std::max(plan.n_chunks, 1u) * 2 * sizeof(double);
-    const size_t o_queue = 0;
-    const size_t o_pts = align256(o_queue + kJJKinds * sizeof(uint32_t));
+    JJLaunch L;
+    JJPlan<float> plan;
+    const size_t pts_bytes = S.P.size() * sizeof(JJPointDev), lut_bytes = S.lut.size() * sizeof(float);
+    const size_t o_queue = 0, o_pts = align256(o_queue + kJJKinds * sizeof(uint32_t));
     const size_t o_items = align256(o_pts + pts_bytes);
-    const size_t o_lut = align256(o_items + items_bytes);
-    const size_t o_part = align256(o_lut + lut_bytes);
-    const size_t need = o_part + part_bytes;
+    size_t items_bytes, o_lut, o_part, need;
+    for (;;) {
+        set_choice(L, choice);
+        plan_items(S.P, S.kinds, L.ppt, plan);
+        items_bytes = plan.items.size() * sizeof(JJItem);
+        o_lut = align256(o_items + items_bytes);
+        o_part = align256(o_lut + lut_bytes);
+        need = o_part + (size_t)std::max(plan.n_chunks, 1u) * 2 * sizeof(double);
+        if (need <= kNoAllocScratchBytes || ctx->jj_ppt || choice == 2) break;
+        choice = 2;  // not forced: half the chunks may fit
+    }
     if (need > kNoAllocScratchBytes)
         return fail(ctx, SDE_ERR_INVALID,
                     "sde_jj_integrate_noalloc: %u points in %u path chunks need %zu bytes of scratch, the maximum "
@@ -1007,9 +1206,7 @@ int jj_integrate_noalloc_impl(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_
     SDE_HIP(ctx, hipEventRecord(ctx->noalloc_done, stream));
     ctx->noalloc_pending = true;
 
-    JJLaunch L;
     jj_fill_args<float>(ctx, run, S, theta, winding, v, acc, point_sums, L);
-    L.ppt = ppt;
     L.queues = reinterpret_cast<uint32_t*>(base + o_queue);
     L.A.pts = base + o_pts;
     L.A.items = reinterpret_cast<const JJItem*>(base + o_items);
@@ -1019,7 +1216,7 @@ int jj_integrate_noalloc_impl(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_
     L.n_items = (uint32_t)plan.items.size();
     L.n_pts = (uint32_t)plan.pts.size();
     if ((st = jj_grids<float>(ctx, L))) return st;
-    ctx->last.jj_paths_per_lane = ppt;
+    ctx->last.jj_paths_per_lane = L.ppt;
     ctx->last.work_items = plan.items.size();
     if ((st = jj_record<float>(ctx, L, stream))) return st;
     if (run->sync) return sync_and_check(ctx, stream);
