@@ -36,7 +36,7 @@ def _run(gpu, pts, step0, M, ppt, scheme=0):
 
 
 @pytest.mark.parametrize("ppt", [0, 1, 2, 4])
-@pytest.mark.parametrize("period", [1, 3, 4, 7, 200])
+@pytest.mark.parametrize("period", [1, 3, 4, 7, 200, 1016, 1017])
 @pytest.mark.parametrize("step0, n_steps", [(0, 120), (8, 3), (5, 1), (6, 117), (3, 64)])
 def test_events_do_not_touch_the_paths(gpu, ppt, period, step0, n_steps):
     def pts(tr):
@@ -65,7 +65,7 @@ def _state(n, dev, t):
 
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("scheme", [0, 1])
-@pytest.mark.parametrize("period", [2, 5, 100])
+@pytest.mark.parametrize("period", [2, 5, 100, 1016, 1017])
 @pytest.mark.parametrize("step0, n_steps", [(0, 1), (0, 64), (3, 2), (0, 257), (62, 131), (5, 1000)])
 def test_noise_drawn_by_other_waves_is_the_same(gpu, f64, scheme, period, step0, n_steps):
     """The launch for small calls (64 paths a workgroup, the noise drawn ahead
