@@ -75,6 +75,7 @@ struct JJArgs {
     const void* pts;      // JJPointT<R>[]
     const JJItem* items;
     const void* lut;      // R[]
+    const void* tables;   // F64Tables (FP64 only)
     uint32_t* queue;
     int* flag;
     void* theta;          // R[]
@@ -96,16 +97,103 @@ struct JJArgs {
 // drift evaluation of Alg. 2 is taken at t + dt), ns the noise increments.
 // The potential's shape at theta (in periods): sin(2 pi theta) for the
 // -sin phi force, cos(2 pi theta) for -V'(x) = -2 pi cos(2 pi x).  FP32: the
-// hardware v_sin/v_cos, which take revolutions; FP64: sinpi/cospi.
+// hardware v_sin/v_cos, which take revolutions; FP64: the table functions.
+
+// ---- FP64 functions of the path integrator ----
+// The arguments are special enough that table lookups beat general library
+// functions: the uniforms are 24-bit fractions, phases are in revolutions.
+// A workgroup keeps in LDS sin and cos of i/256 revolution (in two parts) and,
+// for the logarithm of a mantissa near 1 + i/256, a 24-bit reciprocal v with
+// -log2 v (in two parts, the first short enough to add an exponent exactly).
+// The remainders are exact and small, so 3 polynomial terms (log: 6) reach
+// FP64, and each result is rounded once: errors stay near half an ulp
+// (sines and cosines keep it at their zeros, which are table points).
+// Coefficients: Chebyshev fits, relative errors below 2.2e-17 of the small
+// correction they give.  262144 paths x 400 Heun steps: 582 us with the
+// library's sinpi, log2, sqrt and sincospi, 313 us with these.
+struct F64Tables {
+    double2 sc[256];     // sin, cos of 2 pi i / 256
+    double2 sc_lo[256];  // what their rounding left
+    struct Log {
+        double hi;       // -log2 v (of 2 v from kLogFold on), a multiple of 2^-40
+        float lo, v;     // its rest; v = 256 / (256 + i)
+    } lg[257];
+};
+// Mantissas from 1 + kLogFold / 256 (about sqrt 2) on count to the next power
+// of two, so that the logarithm of a uniform just below 1 has no cancellation.
+constexpr uint32_t kLogFold = 106;
+
+template <typename R>
+struct JJTables {};  // FP32 has hardware functions
+template <>
+struct JJTables<double> : F64Tables {};
+static_assert(sizeof(F64Tables) % 16 == 0, "copied in 16-byte pieces");
+
+__device__ __forceinline__ void fill_tables(JJTables<float>&, const void*) {}
+__device__ __forceinline__ void fill_tables(JJTables<double>& T, const void* src)
+{
+    for (uint32_t i = threadIdx.x; i < sizeof(F64Tables) / 16; i += blockDim.x)
+        reinterpret_cast<double2*>(&T)[i] = static_cast<const double2*>(src)[i];
+    __syncthreads();
+}
+
+// The tables, from long double functions.
+static const F64Tables& host_tables()
+{
+    static const F64Tables tables = [] {
+        F64Tables t{};
+        const long double pi = 3.14159265358979323846264338327950288L;
+        for (int i = 0; i < 256; ++i) {
+            long double sn = std::sin(2 * pi * i / 256), cs = std::cos(2 * pi * i / 256);
+            if (i % 64 == 0) {  // exact at the quarters
+                sn = i == 64 ? 1 : i == 192 ? -1 : 0;
+                cs = i == 0 ? 1 : i == 128 ? -1 : 0;
+            }
+            t.sc[i] = make_double2((double)sn, (double)cs);
+            t.sc_lo[i] = make_double2((double)(sn - t.sc[i].x), (double)(cs - t.sc[i].y));
+        }
+        for (int i = 0; i <= 256; ++i) {
+            const float v = (float)(256.0L / (256 + i));
+            const long double l = -std::log2((long double)v * (i < (int)kLogFold ? 1 : 2));
+            t.lg[i].v = v;
+            t.lg[i].hi = (double)(std::nearbyint(l * 0x1p40L) * 0x1p-40L);
+            t.lg[i].lo = (float)(l - t.lg[i].hi);
+        }
+        return t;
+    }();
+    return tables;
+}
+
+// sin and cos of 2 pi (entry i + r) revolutions, |r| <= 1/512 exact: the
+// entry's pair rotated by the small angle.
+template <bool SIN, bool COS>
+__device__ __forceinline__ void rotate_entry(const F64Tables& T, uint32_t i, double r, double& sn, double& cs)
+{
+    const double2 e = T.sc[i];
+    const double z = r * r;
+    const double sd = fma(fma(0x1.466b53685f962p+6, z, -0x1.4abbce6246526p+5), z, 0x1.921fb54442d18p+2) * r;
+    const double cm = fma(fma(-0x1.55d36d85e5ebfp+6, z, 0x1.03c1f081ad337p+6), z, -0x1.3bd3cc9be45dep+4) * z;
+    if (SIN) sn = e.x + fma(e.x, cm, fma(e.y, sd, T.sc_lo[i].x));
+    if (COS) cs = e.y + fma(e.y, cm, fma(-e.x, sd, T.sc_lo[i].y));
+}
+
+// The force's shape at theta.
 template <bool COSF>
-__device__ __forceinline__ float jj_shape(float theta)
+__device__ __forceinline__ float jj_shape(float theta, const JJTables<float>&)
 {
     return COSF ? cos_rev(theta) : sin_rev(theta);
 }
 template <bool COSF>
-__device__ __forceinline__ double jj_shape(double theta)
+__device__ __forceinline__ double jj_shape(double theta, const JJTables<double>& T)
 {
-    return COSF ? cospi(2.0 * theta) : sinpi(2.0 * theta);
+#pragma clang fp contract(off)
+    // n = 256 theta to the nearest integer, in the low bits of t (|theta| < 2^42)
+    constexpr double kMagic = 0x1.8p52;
+    const double t = fma(256.0, theta, kMagic);
+    const double r = fma(-0x1p-8, t - kMagic, theta);
+    double sn, cs;
+    rotate_entry<!COSF, COSF>(T, (uint32_t)__double_as_longlong(t) & 255u, r, sn, cs);
+    return COSF ? cs : sn;
 }
 
 __device__ __forceinline__ float fm(float a, float b, float c) { return fmaf(a, b, c); }
@@ -115,7 +203,7 @@ __device__ __forceinline__ double fm(double a, double b, double c) { return fma(
 // is rounded to R before a step adds it, whether or not the compiler sees
 // both in one basic block (no contraction of the radius' product into the
 // step's additions): a path's numbers do not depend on which loop runs it.
-__device__ __forceinline__ void jj_gauss4(U4 c, uint32_t k0, uint32_t k1, float c2, float g[4])
+__device__ __forceinline__ void jj_gauss4(U4 c, uint32_t k0, uint32_t k1, float c2, const JJTables<float>&, float g[4])
 {
 #pragma clang fp contract(off)
     const U4 x = philox4x32_10(c, k0, k1);
@@ -129,36 +217,58 @@ __device__ __forceinline__ void jj_gauss4(U4 c, uint32_t k0, uint32_t k1, float 
         g[2 * p + 1] = rho * __builtin_amdgcn_sinf(u2);
     }
 }
-__device__ __forceinline__ void jj_gauss4(U4 c, uint32_t k0, uint32_t k1, double c2, double g[4])
+__device__ __forceinline__ void jj_gauss4(U4 c, uint32_t k0, uint32_t k1, double c2, const JJTables<double>& T,
+                                          double g[4])
 {
 #pragma clang fp contract(off)
     const U4 x = philox4x32_10(c, k0, k1);
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
-        const double u1 = (double)((w[2 * p] >> 8) + 1u) * 0x1p-24;
-        const double u2 = (double)(w[2 * p + 1] >> 8) * 0x1p-24;
-        const double rho = sqrt(c2 * log2(u1));
+        // u1 = k 2^-24, k = 2^E m exact in FP32; the mantissa m to the nearest
+        // 1/256 selects v: log2 u1 = (E - 24) - log2 v + log2(m v)
+        const uint32_t b = __float_as_uint((float)((w[2 * p] >> 8) + 1u));
+        constexpr uint32_t kFold = 0x800000u - ((kLogFold << 15) - (1u << 14));
+        const F64Tables::Log lg = T.lg[((b & 0x7fffffu) + 0x4000u) >> 15];
+        const double r = fma((double)__uint_as_float((b & 0x7fffffu) | 0x3f800000u), (double)lg.v, -1.0);
+        double q = fma(-0x1.ec71295a0d4acp-3, r, 0x1.277714d2a5458p-2);
+        q = fma(q, r, -0x1.71547652b197bp-2);
+        q = fma(q, r, 0x1.ec709dc398b67p-2);
+        q = fma(q, r, -0x1.71547652b82fep-1);
+        q = fma(q, r, 0x1.71547652b82fep+0);
+        const double l = ((double)((int)((b + kFold) >> 23) - 151) + lg.hi) + fma(r, q, (double)lg.lo);
+        // rho sigma = sqrt(c2 l): hardware estimate, one Goldschmidt step, one
+        // correction (zero for u1 = 1 or no noise)
+        const double x2 = c2 * l;
+        const double y = __builtin_amdgcn_rsq(fmax(x2, 0x1p-1000));
+        double rho = x2 * y, h = 0.5 * y;
+        const double d = fma(-h, rho, 0.5);
+        rho = fma(rho, d, rho);
+        h = fma(h, d, h);
+        rho = fma(fma(-rho, rho, x2), h, rho);
+        // u2 to the nearest 1/256 revolution (the top byte, rounded) and the
+        // signed rest of its 24 bits
+        const uint32_t v = w[2 * p + 1];
         double sn, cs;
-        sincospi(2.0 * u2, &sn, &cs);
+        rotate_entry<true, true>(T, (v + 0x800000u) >> 24, (double)((int32_t)(v << 8) >> 16) * 0x1p-24, sn, cs);
         g[2 * p] = rho * cs;
         g[2 * p + 1] = rho * sn;
     }
 }
 
 template <typename R, int PPT, int SCHEME, bool INERTIAL, bool COSF, bool ACC>
-__device__ __forceinline__ void jj_step(const JJPointT<R>& P, R e0, R e1, const R (&ns)[PPT], R (&th)[PPT],
-                                        R (&vv)[PPT], R (&af)[PPT])
+__device__ __forceinline__ void jj_step(const JJPointT<R>& P, const JJTables<R>& T, R e0, R e1,
+                                        const R (&ns)[PPT], R (&th)[PPT], R (&vv)[PPT], R (&af)[PPT])
 {
 #pragma unroll
     for (int k = 0; k < PPT; ++k) {
         if (INERTIAL) {
             // X = (coordinate, v), F = (v, (force - gamma v + a cos wt + f)/m), noise on v
-            const R F1 = fm(-P.kv, jj_shape<COSF>(th[k]), fm(-P.gim, vv[k], e0));
+            const R F1 = fm(-P.kv, jj_shape<COSF>(th[k], T), fm(-P.gim, vv[k], e0));
             if (SCHEME == SDE_HEUN) {
                 const R vt = fm(P.dt, F1, vv[k]) + ns[k];
                 const R tt = fm(P.dtp, vv[k], th[k]);
-                const R F2 = fm(-P.kv, jj_shape<COSF>(tt), fm(-P.gim, vt, e1));
+                const R F2 = fm(-P.kv, jj_shape<COSF>(tt, T), fm(-P.gim, vt, e1));
                 th[k] = fm(P.hdtp, vv[k] + vt, th[k]);
                 vv[k] = fm(P.hdt, F1 + F2, vv[k]) + ns[k];
             } else {
@@ -168,10 +278,10 @@ __device__ __forceinline__ void jj_step(const JJPointT<R>& P, R e0, R e1, const 
         } else {
             // overdamped: coordinate' = (force + a cos wt + f)/gamma + noise on
             // the coordinate; v reports the step's mean velocity (change / dt)
-            const R F1 = fm(-P.kv, jj_shape<COSF>(th[k]), e0);
+            const R F1 = fm(-P.kv, jj_shape<COSF>(th[k], T), e0);
             if (SCHEME == SDE_HEUN) {
                 const R tt = fm(P.dtp, F1, th[k]) + ns[k];
-                const R F2 = fm(-P.kv, jj_shape<COSF>(tt), e1);
+                const R F2 = fm(-P.kv, jj_shape<COSF>(tt, T), e1);
                 th[k] = fm(P.hdtp, F1 + F2, th[k]) + ns[k];
                 vv[k] = fm(R(0.5), F1 + F2, P.sig_v * ns[k]);
             } else {
@@ -201,6 +311,7 @@ template <typename R, int PPT, bool TAB>
 struct OwnNoise {
     uint32_t key0, key1, q;
     const uint32_t (&pid)[PPT];
+    const JJTables<R>& T;
     R c2, a_im, f_im;
     const R* lut;  // cos(2 pi k / S), or with TAB the drive terms
     static constexpr uint32_t kUnroll = 1;
@@ -212,7 +323,8 @@ struct OwnNoise {
     {
         static_assert(N == 1, "one block at a time");
 #pragma unroll
-        for (int k = 0; k < PPT; ++k) jj_gauss4(U4{b, pid[k], q, (uint32_t)SDE_TAG_NOISE}, key0, key1, c2, g[0][k]);
+        for (int k = 0; k < PPT; ++k) 
+            jj_gauss4(U4{b, pid[k], q, (uint32_t)SDE_TAG_NOISE}, key0, key1, c2, T, g[0][k]);
 #pragma unroll
         for (int j = 0; j < 5; ++j) e[0][j] = TAB ? lut[kk + j] : fm(a_im, load_uniform(lut + kk + j), f_im);
     }
@@ -263,8 +375,8 @@ struct RingNoise {
 };
 
 template <typename R, int PPT, int SCHEME, bool INERTIAL, bool COSF, typename Noise>
-__device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, uint32_t q, uint32_t chunk,
-                                        const uint32_t (&pid)[PPT], Noise& src)
+__device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, const JJTables<R>& T, uint32_t q,
+                                        uint32_t chunk, const uint32_t (&pid)[PPT], Noise& src)
 {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     R* theta = static_cast<R*>(A.theta);
@@ -353,8 +465,8 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, u
                     R ns[PPT];
 #pragma unroll
                     for (int k = 0; k < PPT; ++k) ns[k] = g[u][k][j];
-                    jj_step<R, PPT, SCHEME, INERTIAL, COSF, decltype(in_window)::value>(P, e[u][j], e[u][j + 1], ns,
-                                                                                       th, vv, af);
+                    jj_step<R, PPT, SCHEME, INERTIAL, COSF, decltype(in_window)::value>(
+                        P, T, e[u][j], e[u][j + 1], ns, th, vv, af);
                 }
                 wrap();
             }
@@ -420,10 +532,10 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, u
             const R eb = fm(P.a_im, load_uniform(lut + kk + 1), P.f_im);
             if (n >= P.n_transient) {
                 open_window();
-                jj_step<R, PPT, SCHEME, INERTIAL, COSF, true>(P, ea, eb, ns, th, vv, af);
+                jj_step<R, PPT, SCHEME, INERTIAL, COSF, true>(P, T, ea, eb, ns, th, vv, af);
                 if (--to_fold == 0) fold();
             } else {
-                jj_step<R, PPT, SCHEME, INERTIAL, COSF, false>(P, ea, eb, ns, th, vv, af);
+                jj_step<R, PPT, SCHEME, INERTIAL, COSF, false>(P, T, ea, eb, ns, th, vv, af);
             }
             ++n;
             kk = (kk + 1 == P.S) ? 0u : kk + 1;
@@ -484,6 +596,8 @@ __global__ __launch_bounds__(256) void jj_persistent_kernel(JJArgs A)
 {
     __shared__ __attribute__((aligned(16))) R drive[4][TAB ? kDriveTable : 1];
     R* mine = drive[threadIdx.x / kWave];  // this wave's own: no barrier
+    __shared__ JJTables<R> T;
+    fill_tables(T, A.tables);
     const uint32_t lane = threadIdx.x & (kWave - 1);
     for (;;) {
         uint32_t item = 0;
@@ -503,8 +617,8 @@ __global__ __launch_bounds__(256) void jj_persistent_kernel(JJArgs A)
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
-        OwnNoise<R, PPT, TAB> src{A.key0, A.key1, it.point, pid, P.c2, P.a_im, P.f_im, TAB ? mine : lut};
-        jj_item<R, PPT, SCHEME, INERTIAL, COSF>(A, P, it.point, it.chunk, pid, src);
+        OwnNoise<R, PPT, TAB> src{A.key0, A.key1, it.point, pid, T, P.c2, P.a_im, P.f_im, TAB ? mine : lut};
+        jj_item<R, PPT, SCHEME, INERTIAL, COSF>(A, P, T, it.point, it.chunk, pid, src);
     }
 }
 
@@ -524,6 +638,8 @@ template <typename R, int SCHEME, bool INERTIAL, bool COSF>
 __global__ __launch_bounds__(kSplitThreads) void jj_split_kernel(JJArgs A)
 {
     __shared__ __attribute__((aligned(16))) JJRing<R> ring;
+    __shared__ JJTables<R> T;
+    fill_tables(T, A.tables);
     constexpr uint32_t kB = JJRing<R>::kBlocks;
     const JJItem it = load_uniform(A.items + blockIdx.x);
     const JJPointT<R> P = load_uniform(static_cast<const JJPointT<R>*>(A.pts) + it.point);
@@ -531,7 +647,7 @@ __global__ __launch_bounds__(kSplitThreads) void jj_split_kernel(JJArgs A)
     const uint32_t pid[1] = {it.chunk * kWave + lane};
     if (wave == 0) {
         RingNoise<R> src{ring};
-        jj_item<R, 1, SCHEME, INERTIAL, COSF>(A, P, it.point, it.chunk, pid, src);
+        jj_item<R, 1, SCHEME, INERTIAL, COSF>(A, P, T, it.point, it.chunk, pid, src);
         return;
     }
     if (P.n_steps == 0) return;
@@ -543,7 +659,7 @@ __global__ __launch_bounds__(kSplitThreads) void jj_split_kernel(JJArgs A)
         const uint32_t base = (c / kB) & 1u ? kB : 0u;
         for (uint32_t i = wave - 1; i < cnt; i += kSplitDrawers) {
             R g[4];
-            jj_gauss4(U4{(uint32_t)(b0 + c) + i, pid[0], it.point, (uint32_t)SDE_TAG_NOISE}, A.key0, A.key1, P.c2, g);
+            jj_gauss4(U4{(uint32_t)(b0 + c) + i, pid[0], it.point, (uint32_t)SDE_TAG_NOISE}, A.key0, A.key1, P.c2, T, g);
 #pragma unroll
             for (int j = 0; j < 4; ++j) ring.g[base + i][lane][j] = g[j];
             if (lane < 5) ring.e[base + i][lane] = fm(P.a_im, lut[(phase + 4 * i) % P.S + lane], P.f_im);
@@ -712,11 +828,11 @@ constexpr int kSplitChoice = 17;
 
 // Most items (of 64 paths) per CU the split kernel is tried for, FP32 and
 // FP64.  With more, every SIMD has waves enough to switch between, and the
-// waves that draw ahead only take issue slots.  One point, 10^4 FP32 steps
-// (2000 FP64 steps), best persistent against split, us: 4096 paths 898 : 478
-// (782 : 417), 32768 (2 per CU) 907 : 615 (807 : 620), 65536 923 : 869
-// (840 : 1097), 98304 (6 per CU) 1492 : 1245, 131072 (8 per CU) 1503 : 1561.
-constexpr uint32_t kSplitItemsPerCU32 = 6, kSplitItemsPerCU64 = 2;
+// waves that draw ahead only take issue slots.  One point, best persistent
+// against split, us: 10^4 FP32 steps of 4096 paths 831 : 486, 32768 (2 per
+// CU) 852 : 620, 98304 (6) 1327 : 1248, 131072 (8) 1329 : 1566; 2000 FP64
+// steps of 4096 paths 598 : 360, 49152 (3) 637 : 490, 65536 (4) 643 : 755.
+constexpr uint32_t kSplitItemsPerCU32 = 6, kSplitItemsPerCU64 = 3;
 
 struct JJLaunch {
     JJArgs A;
@@ -794,9 +910,9 @@ static std::string jj_graph_key(const char* prec, const JJLaunch& L)
     const JJArgs& A = L.A;
     char buf[640];
     snprintf(buf, sizeof buf,
-             "jj|%s|pts%p|it%p|lut%p|q%p|fl%p|th%p|wd%p|v%p|acc%p|pa%p|rec%p/%llu/%u|n0%llu|k%u.%u|ni%u|M%u|ini%d|"
+             "jj|%s|pts%p|it%p|lut%p|tab%p|q%p|fl%p|th%p|wd%p|v%p|acc%p|pa%p|rec%p/%llu/%u|n0%llu|k%u.%u|ni%u|M%u|ini%d|"
              "ppt%d/%d/%d|sch%d|np%u|ps%p",
-             prec, A.pts, (const void*)A.items, A.lut, (void*)L.queues, (void*)A.flag, A.theta, (void*)A.winding, A.v,
+             prec, A.pts, (const void*)A.items, A.lut, A.tables, (void*)L.queues, (void*)A.flag, A.theta, (void*)A.winding, A.v,
              (void*)A.acc, (void*)A.partials, (void*)A.rec, (unsigned long long)A.rec_pitch, A.rec_every,
              (unsigned long long)A.step0, A.key0, A.key1, L.n_items, A.M, A.init_from_state, L.ppt, (int)L.split, (int)L.tab, L.scheme,
              L.n_pts, (void*)L.point_sums);
@@ -1036,6 +1152,7 @@ static void jj_fill_args(sde_ctx* ctx, const sde_run* run, const JJSetup<R>& S, 
     L.A.v = v;
     L.A.acc = acc;
     L.A.step0 = run->step0;
+    L.A.tables = nullptr;
     L.A.rec = nullptr;
     L.A.rec_pitch = S.path_first;
     L.A.rec_every = 0u;
@@ -1087,6 +1204,10 @@ static int jj_integrate_t(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_pts,
     JJLaunch L;
     jj_fill_args<R>(ctx, run, S, theta, winding, v, acc, point_sums, L);
     L.A.lut = ctx->ws[kSlotJJLut].ptr;
+    if (sizeof(R) == 8) {
+        if ((st = upload(ctx, kSlotJJTables, 3, &host_tables(), sizeof(F64Tables), stream))) return st;
+        L.A.tables = ctx->ws[kSlotJJTables].ptr;
+    }
     L.A.rec = rec;
     L.A.rec_every = rec ? rec_every : 0u;
     const char* prec = sizeof(R) == 4 ? "f32" : "f64";

@@ -107,6 +107,7 @@ enum Slot {
     kSlotMisc = 10,
     kSlotStep = 11,
     kSlotTune = 12,
+    kSlotJJTables = 13,
 };
 
 // A roctx range around one C-ABI call (shown by rocprofv3 --marker-trace;
