@@ -3,14 +3,12 @@
 // inference with hand-written FP32 kernels, and the scan that falls back to
 // the integrator where the ensemble disagrees.
 //
-// Training works on minibatches of B samples for all members at once
-// (grid.z = member).  One tiled kernel serves the three products of a layer
-// -- forward Z = A W^T + b, weight gradient dW = dZ^T A, input gradient
-// dA = dZ W -- on the FP32 matrix cores (v_mfma_f32_16x16x4_f32; 64 x 64
-// tiles staged through LDS in 16-k slices, a 32 x 32 quarter per wave), with
-// the bias/GELU (forward) and GELU' (backward) applied in its epilogue.  A
-// whole epoch of steps is recorded once as a HIP graph; the Adam step count
-// is read from a device counter so the same graph replays every epoch.
+// Training works on minibatches of B samples for all members at once, three
+// launches a step, all products on the FP32 matrix cores
+// (v_mfma_f32_16x16x4_f32): the rows of the batch forward and back through
+// every layer, the weight gradients, the update.  A whole epoch of steps is
+// recorded once as a HIP graph; the Adam step count is a device counter, so
+// the same graph replays every epoch.
 //
 // Inference is one fused kernel for all members (mlp_infer_mfma_kernel):
 // the hidden weights are packed once per call into the fragment layout of
@@ -115,34 +113,298 @@ __global__ void mlp_normalize_kernel(NormArgs A)
     }
 }
 
-// --------------------------------------------------------------- GEMMs ----
-// C[M][N] = sum_k opA(m, k) opB(k, n) over the members in grid.z.
-//  FWD: opA = X[rows ? rows[m] : m][k] (ld = K), opB = W[n][k]; epilogue
-//       Z = acc + b[n], A_out = GELU(Z) (or Z for the output layer)
-//  DW:  opA = dZ[k][m] (ld = M), opB = A[k][n] (ld = N); C = dW
-//  DX:  opA = dZ[m][k] (ld = K), opB = W[k][n] (ld = N); epilogue
-//       dZ_prev = acc * GELU'(Z_prev)
-enum { kFwd = 0, kDW = 1, kDX = 2 };
+// ------------------------------------------------------------- training ---
+// A step is three launches.
+//  1. mlp_rows_kernel: forward and the chain of input gradients.  Both are
+//     local to a sample, so a workgroup takes 16 or 32 of them through every
+//     layer and back, activations and gradients in LDS in the operand layout
+//     of the next product, the weights streamed from L2 in the layout the
+//     matrix cores read (kept up to date by launch 3).  What the weight
+//     gradients need (activations, dZ) goes to memory once.
+//  2. mlp_grads_kernel: every layer's weight gradient dW = dZ^T A in k slices,
+//     the bias gradients in slices of rows, the loss.
+//  3. mlp_update_kernel: the slices added in order, Adam, the packed weights.
+// The sums keep a fixed order that does not depend on this split (every
+// product adds its k in ascending order on v_mfma_f32_16x16x4_f32, which
+// rounds each multiply-add of its four k in turn as an FMA chain does), so a
+// seed gives the same weights bit for bit as one launch per product did.
+// What bounded that: 31 launches a step, and 64 x 64 tiles staged through LDS
+// in 16-k slices with nothing in flight over a slice (15 TFLOP/s).  Five
+// members of 5-256-256-256-1, 1024 samples: 413 us a step then, 104 now (rows
+// 65, of which the products' MFMAs are 34; gradients 24; update 10).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kGT = 64;   // tile
-constexpr int kGK = 16;   // k step
+// Operands of a 16 x 16 block (16 rows or output columns by 16 k) of the FP32
+// products are one 1 KB run: lane l = i % 16 + 16 * (k % 4) holds the float4 of
+// k = k % 4 + {0, 4, 8, 12}, the operands of four consecutive MFMAs.
+__device__ __forceinline__ uint32_t frag32_index(uint32_t i, uint32_t k, uint32_t kb16)
+{
+    return (((i >> 4) * kb16 + (k >> 4)) * 64 + ((i & 15u) + 16u * (k & 3u))) * 4 + ((k & 15u) >> 2);
+}
 
-struct GemmArgs {
-    const float* A;  uint64_t a_mstride;   // member strides in elements
-    const float* B;  uint64_t b_mstride;
-    float* C;        uint64_t c_mstride;
-    float* C2;       uint64_t c2_mstride;  // FWD: activation output
-    const float* bias; uint64_t bias_mstride;
-    const float* Zp;   uint64_t zp_mstride;  // DX: pre-activation of the previous layer
-    const uint32_t* rows; uint64_t rows_mstride;  // FWD first layer: gathered sample rows
-    uint32_t rows_offset;                   // first row of this minibatch in rows
-    uint32_t M, N, K;
-    int32_t last;                           // FWD: output layer (no GELU)
-    uint32_t kslices;                       // DW: the k range is split over grid.z = member *
-                                            // kslices + slice; slice s writes the M x N partial
-                                            // C + member * c_mstride + s * M * N (summed later)
+constexpr int kGK = 16;   // granularity of the k slices
+constexpr int kGT = 64;   // tile of the weight gradients
+constexpr uint32_t kColSlice = 64;  // rows per bias-gradient slice
+
+// Shapes and buffers of one step; layer l < hidden is hidden, layer `hidden`
+// is the output.  Sample rows have a pitch of Hp = H rounded up to 16, the
+// columns past H are zero.
+struct TrainArgs {
+    const float* Xn;          // [n][w0] normalized inputs
+    const float* yn;          // [n] normalized targets
+    const uint32_t* rows;     // sample order of each member, or null
+    uint64_t rows_mstride;
+    uint32_t rows_offset;     // first row of this minibatch
+    uint32_t B, w0, H, Hp, hidden, members;
+    float* params;            // [members][P]
+    uint64_t P;
+    uint64_t w_off[kMaxLayers], b_off[kMaxLayers];
+    float* wf;                // [members][hidden - 1][Hp * Hp] operands of the forward products
+    float* wb;                // the same of the input gradients
+    float* act;               // [hidden][members][B][Hp] activations
+    float* slope;             // GELU' at the pre-activations
+    float* dz;                // gradients of the pre-activations
+    float* y;                 // [members][B] outputs
+    float* dy;                // their gradients
+    float* part_h;            // [hidden - 1][members][ks_h][Hp * Hp] dW slices
+    float* part_in;           // [members][ks_in][H * w0] of the first layer
+    float* part_out;          // [members][ks_out][H] of the output layer
+    float* part_b;            // [hidden][members][col_slices][Hp] dB slices
+    float* part_bo;           // [members][col_slices] of the output bias
+    uint32_t ks_h, ks_in, ks_out, col_slices;
+    float* loss;              // [members][loss_stride]
+    uint32_t loss_slot, loss_stride;
+    // update
+    float* grads;             // [members][P], or null (Adam steps do not keep them)
+    float* m;
+    float* v;                 // Adam state, null: gradients only
+    uint64_t* t;              // [members] Adam step counts
+    float* bc;                // [members][2] the step's bias corrections
+    float lr, b1, b2, eps;
+
+    __host__ __device__ uint64_t layer_stride() const { return (uint64_t)members * B * Hp; }
 };
+
+__device__ __forceinline__ uint64_t train_row(const TrainArgs& A, uint32_t mem, uint32_t b)
+{
+    return A.rows ? A.rows[mem * A.rows_mstride + A.rows_offset + b] : b;
+}
+
+constexpr int kRowsThreads = 512;
+constexpr int kRowsWaves = kRowsThreads / 64;  // wave w has columns 32 w .. 32 w + 31
+
+// The products of a workgroup's rows with packed weights: start() sends for
+// the first two k blocks of a wave's 32 columns, run() multiplies (in: LDS,
+// operand layout), always two blocks of weights ahead.
+template <int RB>
+struct RowsProduct {
+    uint32_t KB, wave, lane;
+    const float* wp[2];
+    f32x4_t w0[2], w1[2];
+
+    __device__ __forceinline__ void load(uint32_t kb, f32x4_t (&w)[2])
+    {
+        const uint32_t k = min(kb, KB - 1);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) w[n] = *reinterpret_cast<const f32x4_t*>(wp[n] + k * 256);
+    }
+    __device__ __forceinline__ void start(const float* W)
+    {
+#pragma unroll
+        for (int n = 0; n < 2; ++n)  // a wave past the last column block repeats it (and drops the result)
+            wp[n] = W + (min(2 * wave + n, KB - 1) * KB * 64 + lane) * 4;
+        load(0, w0);
+        load(1, w1);
+    }
+    __device__ __forceinline__ void block(const float* in, uint32_t kb, const f32x4_t (&w)[2], f32x4_t (&acc)[RB][2])
+    {
+        f32x4_t a[RB];
+#pragma unroll
+        for (int m = 0; m < RB; ++m) a[m] = *reinterpret_cast<const f32x4_t*>(in + ((m * KB + kb) * 64 + lane) * 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int m = 0; m < RB; ++m)
+#pragma unroll
+                for (int n = 0; n < 2; ++n)
+                    acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][j], w[n][j], acc[m][n], 0, 0, 0);
+    }
+    __device__ __forceinline__ void run(const float* in, f32x4_t (&acc)[RB][2])
+    {
+#pragma unroll
+        for (int m = 0; m < RB; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) acc[m][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (uint32_t kb = 0; kb + 1 < KB; kb += 2) {  // no branch: loads in flight are counted, not drained
+            const f32x4_t c[2] = {w0[0], w0[1]};
+            load(kb + 2, w0);
+            __builtin_amdgcn_sched_barrier(0);  // the loads go out first, two blocks ahead of their use
+            block(in, kb, c, acc);
+            __builtin_amdgcn_sched_barrier(0);
+            const f32x4_t d[2] = {w1[0], w1[1]};
+            load(kb + 3, w1);
+            __builtin_amdgcn_sched_barrier(0);
+            block(in, kb + 1, d, acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (KB & 1u) block(in, KB - 1, w0, acc);
+    }
+};
+
+// Forward and input gradients of samples blockIdx.x * 16 RB .. of member
+// blockIdx.y.
+template <int RB>
+__global__ __launch_bounds__(kRowsThreads) void mlp_rows_kernel(TrainArgs A)
+{
+    constexpr uint32_t kRows = 16 * RB;
+    __shared__ __attribute__((aligned(16))) float buf[2][kRows * 256];
+    __shared__ float xs[kRows][8], ts[kRows], dys[kRows];
+    const uint32_t mem = blockIdx.y, r0 = blockIdx.x * kRows;
+    const uint32_t wave = uniform_u32(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    const uint32_t H = A.H, Hp = A.Hp, KB = Hp / 16, hidden = A.hidden, B = A.B;
+    const float* prm = A.params + mem * A.P;
+    const uint64_t ls = A.layer_stride();
+    for (uint32_t e = threadIdx.x; e < kRows * 8; e += kRowsThreads) {
+        const uint32_t row = e / 8, j = e % 8;
+        const bool ok = r0 + row < B;
+        const uint64_t sample = ok ? train_row(A, mem, r0 + row) : 0u;
+        xs[row][j] = ok && j < A.w0 ? A.Xn[sample * A.w0 + j] : 0.f;
+        if (j == 7) ts[row] = ok ? A.yn[sample] : 0.f;
+    }
+    // Lane l of a 16 x 16 block holds rows 4 (l / 16) + q, column l % 16: this
+    // lane's first element in a [row][Hp] array and in the operand layout.
+    const uint32_t lrow = 4 * (lane >> 4), lcol = wave * 32 + (lane & 15u);
+    const uint64_t at = ((uint64_t)mem * B + r0 + lrow) * Hp + lcol;
+    const uint32_t frag = frag32_index(lrow, lcol, KB);
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const uint32_t col = lcol + 16 * n;
+            if (wave * 32 + 16 * n >= Hp) continue;
+#pragma unroll
+            for (int m = 0; m < RB; ++m)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    f(m, n, q, (uint32_t)(m * 16 + q) + lrow, col, (m * 16 + q) * Hp + 16 * n,
+                      frag + (m * KB + n) * 256 + 4 * q);
+        }
+    };
+    const bool whole = r0 + kRows <= B;  // every row is a sample
+    RowsProduct<RB> prod{KB, wave, lane};
+    const uint64_t hh = (uint64_t)Hp * Hp;
+    const float* wf = A.wf + (uint64_t)mem * (hidden - 1) * hh;  // forward operands of layer 1
+    const float* wb = A.wb + (uint64_t)mem * (hidden - 1) * hh;
+    if (hidden > 1) prod.start(wf);
+    __syncthreads();
+    // pre-activation z of layer l -> its activation and slope
+    auto activate = [&](float* act, float* slope, uint32_t row, uint32_t col, uint32_t off, float z, float* out) {
+        float a = 0.f, d = 0.f;
+        if (col < H) {
+            a = gelu(z);
+            d = gelu_grad(z);
+        }
+        *out = a;
+        if (whole || r0 + row < B) {
+            act[off] = a;
+            slope[off] = d;
+        }
+    };
+    uint32_t cur = 0;
+    f32x4_t acc[RB][2];
+    if (hidden) {
+        const float* W = prm + A.w_off[0];
+        const float* b = prm + A.b_off[0];
+        float wx[2][8], bias[2];
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const uint32_t col = min(lcol + 16 * n, H - 1);
+            bias[n] = b[col];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) wx[n][j] = (uint32_t)j < A.w0 ? W[col * A.w0 + j] : 0.f;
+        }
+        each([&](int, int n, int, uint32_t row, uint32_t col, uint32_t off, uint32_t fi) {
+            float z = 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) z = fmaf(xs[row][j], wx[n][j], z);  // zeros past the inputs
+            activate(A.act + at, A.slope + at, row, col, off, z + bias[n], buf[0] + fi);
+        });
+    }
+    __syncthreads();
+    for (uint32_t l = 1; l < hidden; ++l) {
+        const float* b = prm + A.b_off[l];
+        const float bias[2] = {b[min(lcol, H - 1)], b[min(lcol + 16, H - 1)]};
+        prod.run(buf[cur], acc);
+        prod.start(l + 1 < hidden ? wf + l * hh : wb + (hidden - 2) * hh);  // the next product's first weights
+        each([&](int m, int n, int q, uint32_t row, uint32_t col, uint32_t off, uint32_t fi) {
+            activate(A.act + l * ls + at, A.slope + l * ls + at, row, col, off, acc[m][n][q] + bias[n],
+                     buf[cur ^ 1] + fi);
+        });
+        cur ^= 1;
+        __syncthreads();
+    }
+    // output layer, the loss' gradient
+    if (threadIdx.x < kRows) {
+        const uint32_t row = threadIdx.x;
+        const float* W = prm + A.w_off[hidden];
+        float z = 0.f;
+        if (hidden) {
+            // k in ascending order; a float4 of the operand layout holds every fourth
+            const float* a = buf[cur] + frag32_index(row, 0, KB);
+            for (uint32_t kb = 0; kb < KB; ++kb) {
+                f32x4_t x[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[r] = *reinterpret_cast<const f32x4_t*>(a + kb * 256 + r * 64);
+#pragma unroll
+                for (int k = 0; k < 16; ++k) z = fmaf(x[k & 3][k >> 2], W[min(kb * 16 + k, H - 1)], z);  // zeros past H
+            }
+        } else {
+            for (uint32_t j = 0; j < A.w0; ++j) z = fmaf(xs[row][j], W[j], z);
+        }
+        z += prm[A.b_off[hidden]];
+        float g = 0.f;
+        if (r0 + row < B) {
+            g = 2.f * (z - ts[row]) / (float)B;
+            A.y[(uint64_t)mem * B + r0 + row] = z;
+            A.dy[(uint64_t)mem * B + r0 + row] = g;
+        }
+        dys[row] = g;
+    }
+    if (!hidden) return;
+    // dZ of layer l from the gradient of its activation; slopes were sent for
+    // before the product
+    float slope[RB][2][4];
+    auto load_slopes = [&](uint32_t l) {
+        const float* p = A.slope + l * ls + at;
+        each([&](int m, int n, int q, uint32_t row, uint32_t, uint32_t off, uint32_t) {
+            slope[m][n][q] = whole || r0 + row < B ? p[off] : 0.f;
+        });
+    };
+    auto store_dz = [&](float* dz, uint32_t row, uint32_t off, float g, float* out) {
+        *out = g;
+        if (whole || r0 + row < B) dz[off] = g;
+    };
+    load_slopes(hidden - 1);
+    {
+        const float* W = prm + A.w_off[hidden];
+        const float w[2] = {W[min(lcol, H - 1)], W[min(lcol + 16, H - 1)]};
+        __syncthreads();
+        each([&](int m, int n, int q, uint32_t row, uint32_t, uint32_t off, uint32_t fi) {
+            store_dz(A.dz + (hidden - 1) * ls + at, row, off, dys[row] * w[n] * slope[m][n][q], buf[cur ^ 1] + fi);
+        });
+        cur ^= 1;
+        __syncthreads();
+    }
+    for (uint32_t l = hidden - 1; l > 0; --l) {
+        load_slopes(l - 1);
+        prod.run(buf[cur], acc);
+        if (l > 1) prod.start(wb + (l - 2) * hh);
+        each([&](int m, int n, int q, uint32_t row, uint32_t, uint32_t off, uint32_t fi) {
+            store_dz(A.dz + (l - 1) * ls + at, row, off, acc[m][n][q] * slope[m][n][q], buf[cur ^ 1] + fi);
+        });
+        cur ^= 1;
+        __syncthreads();
+    }
+}
 
 // The k range of slice ks of kslices, in whole k steps.
 __device__ __forceinline__ void k_range(uint32_t K, uint32_t kslices, uint32_t ks, uint32_t& k_begin, uint32_t& k_end)
@@ -152,250 +414,270 @@ __device__ __forceinline__ void k_range(uint32_t K, uint32_t kslices, uint32_t k
     k_end = min(K, k_begin + per);
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void mlp_gemm_kernel(GemmArgs g)
-{
-    __shared__ float As[kGK][kGT + 1];
-    __shared__ float Bs[kGK][kGT + 1];
-    const uint32_t ksl = MODE == kDW ? g.kslices : 1u;
-    const uint32_t mem = blockIdx.z / ksl, ks = blockIdx.z % ksl;
-    const float* A = g.A + mem * g.a_mstride;
-    const float* B = g.B + mem * g.b_mstride;
-    const uint32_t m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT;
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, wm = wave >> 1, wn = wave & 1u;
-    uint32_t kb = 0, ke = g.K;
-    if (MODE == kDW) k_range(g.K, ksl, ks, kb, ke);
-    f32x4_t acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    for (uint32_t k0 = kb; k0 < ke; k0 += kGK) {
-        // 64 x 16 elements of each operand, 4 per lane
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t idx = threadIdx.x + 256 * e;  // 0..1023
-            const uint32_t kk = idx & 15u, mm = idx >> 4; // for k-contiguous loads
-            const uint32_t mm2 = idx & 63u, kk2 = idx >> 6; // for m-contiguous loads
-            float va = 0.f, vb = 0.f;
-            if (MODE == kFwd || MODE == kDX) {
-                const uint32_t m = m0 + mm, k = k0 + kk;
-                if (m < g.M && k < g.K) {
-                    uint64_t row = m;
-                    if (MODE == kFwd && g.rows) row = g.rows[mem * g.rows_mstride + g.rows_offset + m];
-                    va = A[row * g.K + k];
-                }
-                As[kk][mm] = va;
-            } else {
-                const uint32_t m = m0 + mm2, k = k0 + kk2;
-                if (m < g.M && k < ke) va = A[(uint64_t)k * g.M + m];
-                As[kk2][mm2] = va;
-            }
-            if (MODE == kFwd) {
-                const uint32_t n = n0 + mm, k = k0 + kk;
-                if (n < g.N && k < g.K) vb = B[(uint64_t)n * g.K + k];
-                Bs[kk][mm] = vb;
-            } else {
-                const uint32_t n = n0 + mm2, k = k0 + kk2;
-                if (n < g.N && k < ke) vb = B[(uint64_t)k * g.N + n];
-                Bs[kk2][mm2] = vb;
-            }
-        }
-        __syncthreads();
-        // wave (wm, wn) takes the 32 x 32 quarter of the tile: 2 x 2 blocks of
-        // v_mfma_f32_16x16x4_f32, lane l reading A[m = l % 16][k = l / 16] and
-        // B[k = l / 16][n = l % 16] of each 4-k group from the LDS slices
-#pragma unroll
-        for (int kg = 0; kg < kGK / 4; ++kg) {
-            const uint32_t k = kg * 4 + (lane >> 4);
-            float a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                a[i] = As[k][wm * 32 + i * 16 + (lane & 15u)];
-                b[i] = Bs[k][wn * 32 + i * 16 + (lane & 15u)];
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
+// The work of mlp_grads_kernel's workgroups, in this order: 64-row bands of
+// the hidden layers' dW (a wave per 64 columns), the first layer's dW, the
+// output layer's dW, bias slices of 64 rows per hidden layer, bias slices of
+// the output with them, the loss.
+struct GradsGrid {
+    uint32_t hidden, in, out, bias, loss;
+    __host__ __device__ explicit GradsGrid(const TrainArgs& A)
+    {
+        hidden = A.hidden > 1 ? (A.hidden - 1) * A.members * A.ks_h * ((A.Hp + kGT - 1) / kGT) : 0u;
+        in = A.hidden ? A.members * A.ks_in : 0u;
+        out = A.members * A.ks_out;
+        bias = A.members * A.col_slices * (A.hidden + 1);
+        loss = A.members;
     }
-    // lane l holds rows 4 (l / 16) + q, column l % 16 of each block
+    __host__ __device__ uint32_t total() const { return hidden + in + out + bias + loss; }
+};
+
+// One wave's 64 x 64 tile of dW = dZ^T A over k (samples) in [kb, ke).  Both
+// operands lie with k in rows, so a lane's float4 of 4 neighbouring columns
+// (16 lanes and 4 rows: 4 runs of 256 B) is its operand of 4 MFMAs: operand j
+// of row or column i is row or column 4 i + j of the tile.  Four k steps of 4
+// are in flight ahead of the 64 MFMAs of the current ones.
+__device__ __forceinline__ void grads_tile(const float* dz, const float* act, uint32_t Hp, uint32_t m0, uint32_t n0,
+                                           uint32_t kb, uint32_t ke, uint32_t lane, float* part)
+{
+    const uint32_t i = 4 * (lane & 15u), kq = lane >> 4;
+    const bool n_ok = n0 + i < Hp;
+    // a lane past the last row or column takes the first one's values; what
+    // they give is not stored
+    const float* pa = dz + (uint64_t)kq * Hp + m0 + (m0 + i < Hp ? i : 0u);
+    const float* pb = act + (uint64_t)kq * Hp + n0 + (n_ok ? i : 0u);
+    f32x4_t acc[4][4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int b = 0; b < 4; ++b) acc[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto products = [&](const f32x4_t& x, const f32x4_t& y) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t m = m0 + wm * 32 + i * 16 + 4 * (lane >> 4) + q;
-                const uint32_t n = n0 + wn * 32 + j * 16 + (lane & 15u);
-                if (m >= g.M || n >= g.N) continue;
-                const uint64_t o = (uint64_t)m * g.N + n;
-                const float v = acc[i][j][q];
-                if (MODE == kFwd) {
-                    const float z = v + g.bias[mem * g.bias_mstride + n];
-                    g.C[mem * g.c_mstride + o] = z;
-                    g.C2[mem * g.c2_mstride + o] = g.last ? z : gelu(z);
-                } else if (MODE == kDW) {
-                    g.C[mem * g.c_mstride + (uint64_t)ks * g.M * g.N + o] = v;
-                } else {
-                    g.C[mem * g.c_mstride + o] = v * gelu_grad(g.Zp[mem * g.zp_mstride + o]);
-                }
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[a], y[b], acc[a][b], 0, 0, 0);
+    };
+    // whole blocks of 16 k; the loads have no condition on them (the last
+    // block sends for itself again), so none is waited for early
+    const uint32_t full = kb + (ke - kb) / 16 * 16;
+    f32x4_t fa[4], fb[4];
+    auto load = [&](uint32_t k0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            fa[u] = *reinterpret_cast<const f32x4_t*>(pa + (uint64_t)(k0 + 4 * u) * Hp);
+            fb[u] = *reinterpret_cast<const f32x4_t*>(pb + (uint64_t)(k0 + 4 * u) * Hp);
+        }
+    };
+    if (full > kb) {
+        load(kb);
+        for (uint32_t k0 = kb; k0 < full; k0 += 16) {
+            f32x4_t ca[4], cb[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                ca[u] = fa[u];
+                cb[u] = fb[u];
             }
+            load(min(k0 + 16, full - 16));
+            __builtin_amdgcn_sched_barrier(0);  // the loads go out before the products
+#pragma unroll
+            for (int u = 0; u < 4; ++u) products(ca[u], cb[u]);
+        }
+    }
+    for (uint32_t k0 = full; k0 < ke; k0 += 4) {  // the batch's last k, zeros past its end
+        f32x4_t x = {0.f, 0.f, 0.f, 0.f}, y = x;
+        if (k0 + kq < ke) {
+            x = *reinterpret_cast<const f32x4_t*>(pa + (uint64_t)k0 * Hp);
+            y = *reinterpret_cast<const f32x4_t*>(pb + (uint64_t)k0 * Hp);
+        }
+        products(x, y);
+    }
+    if (!n_ok) return;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t m = m0 + 4 * (4 * kq + q) + a;
+            if (m >= Hp) continue;
+            *reinterpret_cast<f32x4_t*>(part + (uint64_t)m * Hp + n0 + i) =
+                f32x4_t{acc[a][0][q], acc[a][1][q], acc[a][2][q], acc[a][3][q]};
+        }
 }
 
-// dW of the first layer: dW[o][j] = sum_b dZ[b][o] Xn[rows[b]][j] (gathered input rows).
-__global__ __launch_bounds__(256) void mlp_gemm_dw_gather_kernel(GemmArgs g)
+__global__ __launch_bounds__(256) void mlp_grads_kernel(TrainArgs A)
 {
-    __shared__ float As[kGK][kGT + 1];
-    __shared__ float Bs[kGK][kGT + 1];
-    const uint32_t mem = blockIdx.z / g.kslices, ks = blockIdx.z % g.kslices;
-    const float* A = g.A + mem * g.a_mstride;
-    const uint32_t m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT;
-    const uint32_t tx = threadIdx.x & 15u, ty = threadIdx.x >> 4;
-    uint32_t kb, ke;
-    k_range(g.K, g.kslices, ks, kb, ke);
-    float acc[4][4] = {};
-    for (uint32_t k0 = kb; k0 < ke; k0 += kGK) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t idx = threadIdx.x + 256 * e;
-            const uint32_t mm2 = idx & 63u, kk2 = idx >> 6;
-            const uint32_t k = k0 + kk2;
-            const uint32_t m = m0 + mm2, n = n0 + mm2;
-            As[kk2][mm2] = (m < g.M && k < ke) ? A[(uint64_t)k * g.M + m] : 0.f;
-            float vb = 0.f;
-            if (n < g.N && k < ke) {
-                const uint64_t row = g.rows ? g.rows[mem * g.rows_mstride + g.rows_offset + k] : k;
-                vb = g.B[row * g.N + n];
-            }
-            Bs[kk2][mm2] = vb;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kGK; ++k) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = As[k][ty * 4 + i];
-                b[i] = Bs[k][tx * 4 + i];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
+    const GradsGrid G(A);
+    const uint32_t tid = threadIdx.x, H = A.H, Hp = A.Hp, B = A.B;
+    const uint64_t ls = A.layer_stride();
+    uint32_t w = blockIdx.x, kb, ke;
+    if (w < G.hidden) {
+        const uint32_t bands = (Hp + kGT - 1) / kGT, band = w % bands, ks = w / bands % A.ks_h;
+        const uint32_t mem = w / bands / A.ks_h % A.members, l = 1 + w / bands / A.ks_h / A.members;
+        const uint32_t n0 = (tid >> 6) * kGT;
+        if (n0 >= Hp) return;
+        k_range(B, A.ks_h, ks, kb, ke);
+        const uint64_t o = (uint64_t)mem * B * Hp;
+        grads_tile(A.dz + l * ls + o, A.act + (l - 1) * ls + o, Hp, band * kGT, n0, kb, ke, tid & 63u,
+                   A.part_h + (((uint64_t)(l - 1) * A.members + mem) * A.ks_h + ks) * Hp * Hp);
+        return;
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t m = m0 + ty * 4 + i;
-        if (m >= g.M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t n = n0 + tx * 4 + j;
-            if (n < g.N) g.C[mem * g.c_mstride + (uint64_t)ks * g.M * g.N + (uint64_t)m * g.N + n] = acc[i][j];
-        }
-    }
-}
-
-
-// db[n] = sum_b dZ[b][n] in two passes with a fixed order: slices of
-// kColSlice rows summed in parallel (grid.y = slice), then the slice sums in
-// slice order.  One thread per column walking all B rows alone leaves a few
-// workgroups waiting out one load latency per row.
-constexpr uint32_t kColSlice = 64;
-
-__global__ void mlp_colsum_slices_kernel(const float* dZ, uint64_t dz_mstride, float* part, uint32_t B, uint32_t N)
-{
-    const uint32_t n = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t sl = blockIdx.y, mem = blockIdx.z;
-    if (n >= N) return;
-    const float* p = dZ + mem * dz_mstride;
-    const uint32_t b0 = sl * kColSlice, b1 = min(B, b0 + kColSlice);
-    float s = 0.f;
+    w -= G.hidden;
+    if (w < G.in) {  // dW of the first layer: thread per output, the samples' inputs through LDS
+        const uint32_t ks = w % A.ks_in, mem = w / A.ks_in;
+        __shared__ __attribute__((aligned(16))) float xs[64][8];
+        k_range(B, A.ks_in, ks, kb, ke);
+        float acc[8] = {};
+        const float* dz = A.dz + (uint64_t)mem * B * Hp + min(tid, H - 1);
+        for (uint32_t k0 = kb; k0 < ke; k0 += 64) {
+            __syncthreads();
+            for (uint32_t e = tid; e < 64 * 8; e += 256) {
+                const uint32_t k = k0 + e / 8, j = e % 8;
+                xs[e / 8][j] = k < ke && j < A.w0 ? A.Xn[train_row(A, mem, k) * A.w0 + j] : 0.f;
+            }
+            __syncthreads();
+            const uint32_t n = min(64u, ke - k0);
 #pragma unroll 16
-    for (uint32_t b = b0; b < b1; ++b) s += p[(uint64_t)b * N + n];
-    part[((uint64_t)mem * gridDim.y + sl) * N + n] = s;
-}
-
-// dW = sum of the k-slice partials of a split weight-gradient product, in
-// slice order: part[member][slice][MN] -> out + member * out_mstride.
-__global__ void mlp_ksum_kernel(const float* part, uint32_t kslices, uint64_t MN, float* out, uint64_t out_mstride)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t mem = blockIdx.y;
-    if (i >= MN) return;
-    const float* p = part + (uint64_t)mem * kslices * MN + i;
-    float s = 0.f;
-    for (uint32_t k = 0; k < kslices; ++k) s += p[(uint64_t)k * MN];
-    out[mem * out_mstride + i] = s;
-}
-
-__global__ void mlp_colsum_kernel(const float* part, uint32_t n_slices, float* db, uint64_t db_mstride, uint32_t N)
-{
-    const uint32_t n = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t mem = blockIdx.y;
-    if (n >= N) return;
-    const float* p = part + (uint64_t)mem * n_slices * N + n;
-    float s = 0.f;
-    for (uint32_t sl = 0; sl < n_slices; ++sl) s += p[(uint64_t)sl * N];
-    db[mem * db_mstride + n] = s;
-}
-
-// dZ_L = 2 (y - t) / B for the output layer; loss = mean (y - t)^2 (FP64
-// block sum, one workgroup per member).
-__global__ __launch_bounds__(256) void mlp_loss_kernel(const float* y, uint64_t y_mstride, const float* t,
-                                                       const uint32_t* rows, uint64_t rows_mstride,
-                                                       uint32_t rows_offset, float* dZ, uint64_t dz_mstride,
-                                                       uint32_t B, float* loss, uint32_t loss_slot,
-                                                       uint32_t loss_stride)
-{
+            for (uint32_t k = 0; k < n; ++k) {
+                const float d = dz[(uint64_t)(k0 + k) * Hp];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[j] = fmaf(d, xs[k][j], acc[j]);
+            }
+        }
+        if (tid >= H) return;
+        float* out = A.part_in + ((uint64_t)mem * A.ks_in + ks) * H * A.w0 + (uint64_t)tid * A.w0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if ((uint32_t)j < A.w0) out[j] = acc[j];
+        return;
+    }
+    w -= G.in;
+    if (w < G.out) {  // dW of the output layer: thread per input
+        const uint32_t ks = w % A.ks_out, mem = w / A.ks_out, in = A.hidden ? H : A.w0;
+        if (tid >= in) return;
+        k_range(B, A.ks_out, ks, kb, ke);
+        const float* dy = A.dy + (uint64_t)mem * B;
+        const float* act = A.act + (A.hidden ? (A.hidden - 1) * ls : 0u) + (uint64_t)mem * B * Hp + tid;
+        float acc = 0.f;
+#pragma unroll 16
+        for (uint32_t k = kb; k < ke; ++k)
+            acc = fmaf(dy[k], A.hidden ? act[(uint64_t)k * Hp] : A.Xn[train_row(A, mem, k) * A.w0 + tid], acc);
+        A.part_out[((uint64_t)mem * A.ks_out + ks) * in + tid] = acc;
+        return;
+    }
+    w -= G.out;
+    if (w < G.bias) {  // db[n] = sum_b dZ[b][n], one slice of rows
+        const uint32_t sl = w % A.col_slices, mem = w / A.col_slices % A.members, l = w / A.col_slices / A.members;
+        const uint32_t b0 = sl * kColSlice, b1 = min(B, b0 + kColSlice);
+        const bool last = l == A.hidden;
+        if (tid >= (last ? 1u : H)) return;
+        const float* p = last ? A.dy + (uint64_t)mem * B : A.dz + l * ls + (uint64_t)mem * B * Hp + tid;
+        const uint64_t pitch = last ? 1u : Hp;
+        float s = 0.f;
+#pragma unroll 16
+        for (uint32_t b = b0; b < b1; ++b) s += p[b * pitch];
+        if (last)
+            A.part_bo[(uint64_t)mem * A.col_slices + sl] = s;
+        else
+            A.part_b[(((uint64_t)l * A.members + mem) * A.col_slices + sl) * Hp + tid] = s;
+        return;
+    }
+    // loss = mean (y - t)^2 (FP64 block sum), and the step count
+    const uint32_t mem = w - G.bias;
     __shared__ double lds[4];
-    const uint32_t mem = blockIdx.x;
     double s = 0.0;
-    for (uint32_t b = threadIdx.x; b < B; b += 256) {
-        const uint32_t row = rows ? rows[mem * rows_mstride + rows_offset + b] : b;
-        const float r = y[mem * y_mstride + b] - t[row];
-        dZ[mem * dz_mstride + b] = 2.f * r / (float)B;
+    for (uint32_t b = tid; b < B; b += 256) {
+        const float r = A.y[(uint64_t)mem * B + b] - A.yn[train_row(A, mem, b)];
         s += (double)r * (double)r;
     }
     s = wave_sum(s);
-    if ((threadIdx.x & 63u) == 0) lds[threadIdx.x >> 6] = s;
+    if ((tid & 63u) == 0) lds[tid >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0 && loss) loss[(uint64_t)mem * loss_stride + loss_slot] = (float)((lds[0] + lds[1] + lds[2] + lds[3]) / B);
+    if (tid == 0) {
+        A.loss[(uint64_t)mem * A.loss_stride + A.loss_slot] = (float)((lds[0] + lds[1] + lds[2] + lds[3]) / B);
+        if (A.t) {
+            const uint64_t t = A.t[mem] + 1;
+            A.t[mem] = t;
+            A.bc[2 * mem] = (float)(1.0 - pow((double)A.b1, (double)t));
+            A.bc[2 * mem + 1] = (float)(1.0 - pow((double)A.b2, (double)t));
+        }
+    }
 }
 
-// One Adam step (bias-corrected) of every parameter; the step count of the
-// member is read from (and, by the last lane, advanced in) device memory.
-struct AdamArgs {
-    float* p; float* g; float* m; float* v;
-    uint64_t* t;         // [members], incremented by the advance kernel
-    uint64_t P;
-    uint32_t members;
-    float lr, b1, b2, eps;
-};
-
-__global__ void mlp_adam_kernel(AdamArgs A)
+// A hidden weight W_l[o][k] (l >= 1) into both operand layouts.
+__device__ __forceinline__ void pack_weight(const TrainArgs& A, uint32_t mem, uint32_t l, uint32_t o, uint32_t k, float x)
 {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= A.P * A.members) return;
-    const uint32_t mem = (uint32_t)(i / A.P);
-    const double t = (double)(A.t[mem] + 1);
-    const float bc1 = (float)(1.0 - pow((double)A.b1, t));
-    const float bc2 = (float)(1.0 - pow((double)A.b2, t));
-    const float g = A.g[i];
-    const float m = A.b1 * A.m[i] + (1.f - A.b1) * g;
-    const float v = A.b2 * A.v[i] + (1.f - A.b2) * g * g;
-    A.m[i] = m;
-    A.v[i] = v;
-    A.p[i] -= A.lr * (m / bc1) / (sqrtf(v / bc2) + A.eps);
+    const uint64_t base = ((uint64_t)mem * (A.hidden - 1) + l - 1) * A.Hp * A.Hp;
+    A.wf[base + frag32_index(o, k, A.Hp / 16)] = x;
+    A.wb[base + frag32_index(k, o, A.Hp / 16)] = x;
 }
 
-__global__ void mlp_adam_advance_kernel(uint64_t* t, uint32_t members)
+// The update's workgroups: per layer the blocks of 256 weights, then one
+// block for the biases (at most 256).
+__host__ __device__ inline uint32_t layer_in(const TrainArgs& A, uint32_t l) { return l ? A.H : A.w0; }
+__host__ __device__ inline uint32_t layer_out(const TrainArgs& A, uint32_t l) { return l == A.hidden ? 1u : A.H; }
+__host__ __device__ inline uint32_t update_blocks(const TrainArgs& A, uint32_t l)
 {
-    if (threadIdx.x < members) t[threadIdx.x] += 1;
+    return (layer_in(A, l) * layer_out(A, l) + 255) / 256 + 1;
+}
+
+// Gradients from their slices, one Adam step (bias-corrected), the packed
+// weights.  Thread per parameter of member blockIdx.y; the step count and the
+// corrections that go with it were written by the launch before.
+__global__ __launch_bounds__(256) void mlp_update_kernel(TrainArgs A)
+{
+    const uint32_t mem = blockIdx.y;
+    uint32_t l = 0, blk = blockIdx.x;
+    for (; blk >= update_blocks(A, l); ++l) blk -= update_blocks(A, l);
+    const bool bias = blk + 1 == update_blocks(A, l);
+    const uint32_t e = (bias ? 0u : blk * 256) + threadIdx.x;
+    if (e >= (bias ? layer_out(A, l) : layer_in(A, l) * layer_out(A, l))) return;
+    // slices: part[k * pitch], k < n
+    const float* part;
+    uint64_t pitch;
+    uint32_t n, o = 0, k = 0;
+    if (bias) {
+        n = A.col_slices;
+        part = l == A.hidden ? A.part_bo + (uint64_t)mem * n : A.part_b + ((uint64_t)l * A.members + mem) * n * A.Hp + e;
+        pitch = l == A.hidden ? 1u : A.Hp;
+    } else if (l == A.hidden) {
+        n = A.ks_out;
+        pitch = layer_in(A, l);
+        part = A.part_out + (uint64_t)mem * n * pitch + e;
+    } else if (l == 0) {
+        n = A.ks_in;
+        pitch = (uint64_t)A.H * A.w0;
+        part = A.part_in + (uint64_t)mem * n * pitch + e;
+    } else {
+        n = A.ks_h;
+        pitch = (uint64_t)A.Hp * A.Hp;
+        o = e / A.H;
+        k = e % A.H;
+        part = A.part_h + ((uint64_t)(l - 1) * A.members + mem) * n * pitch + (uint64_t)o * A.Hp + k;
+    }
+    float g = 0.f;
+#pragma unroll 4
+    for (uint32_t s = 0; s < n; ++s) g += part[s * pitch];
+    const uint64_t j = mem * A.P + (bias ? A.b_off[l] : A.w_off[l]) + e;
+    if (A.grads) A.grads[j] = g;
+    if (!A.m) return;
+    // the roundings spelled out, so that no compilation moves them
+    const float m = fmaf(1.f - A.b1, g, A.b1 * A.m[j]);
+    const float v = fmaf(g, (1.f - A.b2) * g, A.b2 * A.v[j]);
+    A.m[j] = m;
+    A.v[j] = v;
+    const float p = A.params[j] - A.lr * (m / A.bc[2 * mem]) / (sqrtf(v / A.bc[2 * mem + 1]) + A.eps);
+    A.params[j] = p;
+    if (!bias && l > 0 && l < A.hidden) pack_weight(A, mem, l, o, k, p);
+}
+
+// Both operand layouts of every hidden weight, zero past H.
+__global__ __launch_bounds__(256) void mlp_pack_train_kernel(TrainArgs A)
+{
+    const uint64_t per = (uint64_t)A.Hp * A.Hp;
+    const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= per * (A.hidden - 1) * A.members) return;
+    const uint32_t mem = (uint32_t)(g / (per * (A.hidden - 1))), l = 1 + (uint32_t)(g / per % (A.hidden - 1));
+    const uint32_t o = (uint32_t)(g % per / A.Hp), k = (uint32_t)(g % A.Hp);
+    pack_weight(A, mem, l, o, k,
+                o < A.H && k < A.H ? A.params[mem * A.P + A.w_off[l] + (uint64_t)o * A.H + k] : 0.f);
 }
 
 // ------------------------------------------------------------ inference ---
@@ -413,17 +695,10 @@ struct InferArgs {
     sde_surrogate_scaling sc;
 };
 
-// FP32 MFMA forward (v_mfma_f32_16x16x4_f32).  Operands of a 16 x 16 block
-// (16 rows or output columns by 16 k) are one 1 KB run: lane l = i % 16 +
-// 16 * (k % 4) holds the float4 of k = k % 4 + {0, 4, 8, 12}, the operands of
-// four consecutive MFMAs.  The hidden weights are packed that way once per
-// call (B(k, c) = W[c][k]); the activations stay in LDS in the same layout, as
-// the A operand of the next layer.
-__device__ __forceinline__ uint32_t frag32_index(uint32_t i, uint32_t k, uint32_t kb16)
-{
-    return (((i >> 4) * kb16 + (k >> 4)) * 64 + ((i & 15u) + 16u * (k & 3u))) * 4 + ((k & 15u) >> 2);
-}
-
+// FP32 MFMA forward (v_mfma_f32_16x16x4_f32) in the operand layout of
+// frag32_index.  The hidden weights are packed that way once per call
+// (B(k, c) = W[c][k]); the activations stay in LDS in the same layout, as the
+// A operand of the next layer.
 struct PackArgs {
     const float* params;
     uint64_t P;
@@ -659,23 +934,6 @@ int ensure_work(sde_surrogate* s, size_t bytes)
     return SDE_OK;
 }
 
-// Training buffers for minibatch B: per layer Z and A (outputs), dZ, plus
-// the normalized inputs/targets [n].
-struct TrainBufs {
-    float* Xn;
-    float* yn;
-    std::vector<float*> Z, Aout, dZ;   // per layer l = 0..L-1, [members][B][w_{l+1}]
-    std::vector<uint64_t> stride;      // member stride of layer l buffers
-    float* colpart;                    // [members][B / kColSlice][max width] bias-gradient slice sums
-    float* dwpart;                     // [members][kMaxKSlices][max width^2] weight-gradient slice sums
-    float* loss;                       // [members][steps_per_epoch]
-};
-
-static uint32_t max_width(const sde_surrogate* s)
-{
-    return *std::max_element(s->widths.begin(), s->widths.end());
-}
-
 // Slices of the batch sum of a weight-gradient product: enough workgroups to
 // cover the CUs (the M x N tiles alone give few), at least 64 rows each.
 constexpr uint32_t kMaxKSlices = 16;
@@ -687,178 +945,97 @@ static uint32_t dw_kslices(uint32_t M, uint32_t N, uint32_t K, uint32_t members)
     return std::max(1u, std::min(k, kMaxKSlices));
 }
 
-size_t train_bytes(const sde_surrogate* s, uint64_t n, uint32_t B, uint32_t steps)
+// Shapes of a step on minibatches of B, and its buffers in the workspace
+// (16-float aligned sections); returns the floats they take.
+size_t carve(sde_surrogate* s, uint64_t n, uint32_t B, uint32_t steps, TrainArgs& A)
 {
-    size_t e = n * (s->widths[0] + 1);
-    for (size_t l = 0; l + 1 < s->widths.size(); ++l) e += 3ull * s->members * B * s->widths[l + 1];
-    e += (size_t)s->members * ((B + kColSlice - 1) / kColSlice) * max_width(s);
-    e += (size_t)s->members * kMaxKSlices * max_width(s) * max_width(s);
-    e += (size_t)s->members * steps;
-    return e * sizeof(float) + 4096;
-}
-
-void carve(sde_surrogate* s, uint64_t n, uint32_t B, TrainBufs& t)
-{
-    float* p = s->work;
-    t.Xn = p;
-    p += n * s->widths[0];
-    t.yn = p;
-    p += n;
-    const size_t L = s->widths.size() - 1;
-    t.Z.resize(L);
-    t.Aout.resize(L);
-    t.dZ.resize(L);
-    t.stride.resize(L);
-    for (size_t l = 0; l < L; ++l) {
-        t.stride[l] = (uint64_t)B * s->widths[l + 1];
-        t.Z[l] = p;
-        p += s->members * t.stride[l];
-        t.Aout[l] = p;
-        p += s->members * t.stride[l];
-        t.dZ[l] = p;
-        p += s->members * t.stride[l];
+    A = TrainArgs{};
+    A.B = B;
+    A.w0 = s->widths[0];
+    A.hidden = (uint32_t)s->widths.size() - 2;
+    A.H = A.hidden ? s->widths[1] : 0u;
+    A.Hp = (A.H + 15u) & ~15u;
+    A.members = s->members;
+    A.params = s->params;
+    A.P = s->P;
+    for (size_t l = 0; l < s->w_off.size(); ++l) {
+        A.w_off[l] = s->w_off[l];
+        A.b_off[l] = s->b_off[l];
     }
-    t.colpart = p;
-    p += (size_t)s->members * ((B + kColSlice - 1) / kColSlice) * max_width(s);
-    t.dwpart = p;
-    p += (size_t)s->members * kMaxKSlices * max_width(s) * max_width(s);
-    t.loss = p;
+    A.ks_h = A.hidden > 1 ? dw_kslices(A.H, A.H, B, A.members) : 0u;
+    A.ks_in = A.hidden ? dw_kslices(A.H, A.w0, B, A.members) : 0u;
+    A.ks_out = dw_kslices(1, A.hidden ? A.H : A.w0, B, A.members);
+    A.col_slices = (B + kColSlice - 1) / kColSlice;
+    A.loss_stride = steps;
+    size_t at = 0;
+    auto take = [&](size_t floats) {
+        float* p = s->work + at;
+        at += (floats + 15) & ~(size_t)15;
+        return p;
+    };
+    const size_t M = A.members, hh = (size_t)A.Hp * A.Hp, pairs = A.hidden > 1 ? A.hidden - 1 : 0;
+    const size_t layers = A.hidden * A.layer_stride();
+    A.Xn = take(n * A.w0);
+    A.yn = take(n);
+    A.act = take(layers);
+    A.slope = take(layers);
+    A.dz = take(layers);
+    A.y = take(M * B);
+    A.dy = take(M * B);
+    A.wf = take(M * pairs * hh);
+    A.wb = take(M * pairs * hh);
+    A.part_h = take(pairs * M * A.ks_h * hh);
+    A.part_in = take(M * A.ks_in * A.H * A.w0);
+    A.part_out = take(M * A.ks_out * (A.hidden ? A.H : A.w0));
+    A.part_b = take((size_t)A.hidden * M * A.col_slices * A.Hp);
+    A.part_bo = take(M * A.col_slices);
+    A.loss = take(M * steps);
+    A.bc = take(2 * M);
+    return at;
 }
 
-template <int MODE>
-int launch_gemm(sde_ctx* ctx, const GemmArgs& g, uint32_t members, hipStream_t st)
+// Sizes the workspace for it first.
+int prepare_steps(sde_surrogate* s, uint64_t n, uint32_t B, uint32_t steps, TrainArgs& A)
 {
-    dim3 grid((g.N + kGT - 1) / kGT, (g.M + kGT - 1) / kGT, members * (MODE == kDW ? g.kslices : 1u));
-    hipLaunchKernelGGL(mlp_gemm_kernel<MODE>, grid, dim3(256), 0, st, g);
+    const size_t floats = carve(s, n, B, steps, A);
+    if (const int e = ensure_work(s, floats * sizeof(float))) return e;
+    carve(s, n, B, steps, A);
+    return SDE_OK;
+}
+
+int pack_weights(sde_surrogate* s, const TrainArgs& A, hipStream_t st)
+{
+    if (A.hidden < 2) return SDE_OK;
+    const uint64_t total = (uint64_t)A.members * (A.hidden - 1) * A.Hp * A.Hp;
+    hipLaunchKernelGGL(mlp_pack_train_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, st, A);
+    SDE_HIP(s->ctx, hipGetLastError());
+    return SDE_OK;
+}
+
+// One step (forward, loss, backward, and Adam where A holds its state).
+int record_step(sde_ctx* ctx, const TrainArgs& A, hipStream_t st)
+{
+    // 16 samples a workgroup until every CU has one, then 32, which halve the
+    // traffic of the weights
+    if ((uint64_t)((A.B + 15) / 16) * A.members <= (uint64_t)ctx->n_cu)
+        hipLaunchKernelGGL(mlp_rows_kernel<1>, dim3((A.B + 15) / 16, A.members), dim3(kRowsThreads), 0, st, A);
+    else
+        hipLaunchKernelGGL(mlp_rows_kernel<2>, dim3((A.B + 31) / 32, A.members), dim3(kRowsThreads), 0, st, A);
+    hipLaunchKernelGGL(mlp_grads_kernel, dim3(GradsGrid(A).total()), dim3(256), 0, st, A);
+    uint32_t blocks = 0;
+    for (uint32_t l = 0; l <= A.hidden; ++l) blocks += update_blocks(A, l);
+    hipLaunchKernelGGL(mlp_update_kernel, dim3(blocks, A.members), dim3(256), 0, st, A);
     SDE_HIP(ctx, hipGetLastError());
     return SDE_OK;
 }
 
-// One training step (forward, loss, backward, Adam) on minibatch rows
-// rows[mem][offset .. offset + B).  If adam is false only the gradient is
-// formed (into s->grads).
-int record_step(sde_surrogate* s, const TrainBufs& t, const uint32_t* rows, uint64_t rows_mstride, uint32_t offset,
-                uint32_t B, const float* targets, uint32_t loss_slot, uint32_t loss_stride, const sde_train_opts* o,
-                bool adam, hipStream_t st)
-{
-    sde_ctx* ctx = s->ctx;
-    const size_t L = s->widths.size() - 1;
-    const uint32_t M = s->members;
-    int e;
-    for (size_t l = 0; l < L; ++l) {
-        GemmArgs g{};
-        g.A = l == 0 ? t.Xn : t.Aout[l - 1];
-        g.a_mstride = l == 0 ? 0 : t.stride[l - 1];
-        g.B = s->params + s->w_off[l];
-        g.b_mstride = s->P;
-        g.C = t.Z[l];
-        g.c_mstride = t.stride[l];
-        g.C2 = t.Aout[l];
-        g.c2_mstride = t.stride[l];
-        g.bias = s->params + s->b_off[l];
-        g.bias_mstride = s->P;
-        g.rows = l == 0 ? rows : nullptr;
-        g.rows_mstride = rows_mstride;
-        g.rows_offset = offset;
-        g.M = B;
-        g.N = s->widths[l + 1];
-        g.K = s->widths[l];
-        g.last = l + 1 == L;
-        if ((e = launch_gemm<kFwd>(ctx, g, M, st))) return e;
-    }
-    hipLaunchKernelGGL(mlp_loss_kernel, dim3(M), dim3(256), 0, st, t.Z[L - 1], t.stride[L - 1], targets, rows,
-                       rows_mstride, offset, t.dZ[L - 1], t.stride[L - 1], B, t.loss, loss_slot, loss_stride);
-    SDE_HIP(ctx, hipGetLastError());
-    for (size_t l = L; l-- > 0;) {
-        const uint32_t out = s->widths[l + 1], in = s->widths[l];
-        GemmArgs g{};
-        g.A = t.dZ[l];
-        g.a_mstride = t.stride[l];
-        g.B = l == 0 ? t.Xn : t.Aout[l - 1];
-        g.b_mstride = l == 0 ? 0 : t.stride[l - 1];
-        g.M = out;
-        g.N = in;
-        g.K = B;
-        g.kslices = dw_kslices(out, in, B, M);
-        g.C = t.dwpart;
-        g.c_mstride = (uint64_t)g.kslices * out * in;
-        if (l > 0) {  // the first layer's inputs are gathered rows: below
-            if ((e = launch_gemm<kDW>(ctx, g, M, st))) return e;
-            hipLaunchKernelGGL(mlp_ksum_kernel, dim3((out * in + 255) / 256, M), dim3(256), 0, st, t.dwpart,
-                               g.kslices, (uint64_t)out * in, s->grads + s->w_off[l], s->P);
-        }
-        const uint32_t n_slices = (B + kColSlice - 1) / kColSlice;
-        hipLaunchKernelGGL(mlp_colsum_slices_kernel, dim3((out + 255) / 256, n_slices, M), dim3(256), 0, st, t.dZ[l],
-                           t.stride[l], t.colpart, B, out);
-        hipLaunchKernelGGL(mlp_colsum_kernel, dim3((out + 255) / 256, M), dim3(256), 0, st, t.colpart, n_slices,
-                           s->grads + s->b_off[l], s->P, out);
-        SDE_HIP(ctx, hipGetLastError());
-        if (l > 0) {
-            GemmArgs d{};
-            d.A = t.dZ[l];
-            d.a_mstride = t.stride[l];
-            d.B = s->params + s->w_off[l];
-            d.b_mstride = s->P;
-            d.C = t.dZ[l - 1];
-            d.c_mstride = t.stride[l - 1];
-            d.Zp = t.Z[l - 1];
-            d.zp_mstride = t.stride[l - 1];
-            d.M = B;
-            d.N = in;
-            d.K = out;
-            if ((e = launch_gemm<kDX>(ctx, d, M, st))) return e;
-        }
-    }
-    // first-layer weight gradient: dW_0[o][j] = sum_b dZ_0[b][o] Xn[rows[b]][j]
-    {
-        GemmArgs g{};
-        g.A = t.dZ[0];
-        g.a_mstride = t.stride[0];
-        g.B = t.Xn;
-        g.b_mstride = 0;
-        g.rows = rows;
-        g.rows_mstride = rows_mstride;
-        g.rows_offset = offset;
-        g.M = s->widths[1];
-        g.N = s->widths[0];
-        g.K = B;
-        g.kslices = dw_kslices(g.M, g.N, B, M);
-        g.C = t.dwpart;
-        g.c_mstride = (uint64_t)g.kslices * g.M * g.N;
-        dim3 grid((g.N + kGT - 1) / kGT, (g.M + kGT - 1) / kGT, M * g.kslices);
-        hipLaunchKernelGGL(mlp_gemm_dw_gather_kernel, grid, dim3(256), 0, st, g);
-        hipLaunchKernelGGL(mlp_ksum_kernel, dim3((g.M * g.N + 255) / 256, M), dim3(256), 0, st, t.dwpart, g.kslices,
-                           (uint64_t)g.M * g.N, s->grads + s->w_off[0], s->P);
-        SDE_HIP(ctx, hipGetLastError());
-    }
-    if (adam) {
-        AdamArgs a;
-        a.p = s->params;
-        a.g = s->grads;
-        a.m = s->adam_m;
-        a.v = s->adam_v;
-        a.t = s->adam_t;
-        a.P = s->P;
-        a.members = M;
-        a.lr = o->lr;
-        a.b1 = o->beta1;
-        a.b2 = o->beta2;
-        a.eps = o->eps;
-        const uint64_t total = s->P * M;
-        hipLaunchKernelGGL(mlp_adam_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, st, a);
-        hipLaunchKernelGGL(mlp_adam_advance_kernel, dim3(1), dim3(64), 0, st, s->adam_t, M);
-        SDE_HIP(ctx, hipGetLastError());
-    }
-    return SDE_OK;
-}
-
-int normalize(sde_surrogate* s, const float* X, const float* y, uint64_t n, const TrainBufs& t, hipStream_t st)
+int normalize(sde_surrogate* s, const float* X, const float* y, uint64_t n, const TrainArgs& t, hipStream_t st)
 {
     NormArgs a;
     a.X = X;
     a.y = y;
-    a.Xn = t.Xn;
-    a.yn = y ? t.yn : nullptr;
+    a.Xn = const_cast<float*>(t.Xn);
+    a.yn = const_cast<float*>(t.yn);
     a.n = n;
     a.w0 = s->widths[0];
     a.sc = s->sc;
@@ -967,12 +1144,10 @@ int sde_surrogate_loss_grad(sde_surrogate* s, uint32_t member, const float* X, c
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const uint32_t B = (uint32_t)n;
     int e;
-    if ((e = ensure_work(s, train_bytes(s, n, B, 1)))) return e;
-    TrainBufs t;
-    carve(s, n, B, t);
-    if ((e = normalize(s, X, y, n, t, st))) return e;
-    sde_train_opts o{};
-    if ((e = record_step(s, t, nullptr, 0, 0, B, t.yn, 0, 1, &o, false, st))) return e;
+    TrainArgs t;
+    if ((e = prepare_steps(s, n, B, 1, t))) return e;
+    t.grads = s->grads;
+    if ((e = normalize(s, X, y, n, t, st)) || (e = pack_weights(s, t, st)) || (e = record_step(ctx, t, st))) return e;
     SDE_HIP(ctx, hipStreamSynchronize(st));
     if (host_grad)
         SDE_HIP(ctx, hipMemcpy(host_grad, s->grads + member * s->P, s->P * sizeof(float), hipMemcpyDeviceToHost));
@@ -1000,10 +1175,9 @@ int sde_surrogate_train(sde_surrogate* s, const float* X, const float* y, uint64
         const uint32_t B = o->batch;
         const uint32_t steps = (uint32_t)(n / B);
         int e;
-        if ((e = ensure_work(s, train_bytes(s, n, B, steps)))) return e;
-        TrainBufs t;
-        carve(s, n, B, t);
-        if ((e = normalize(s, X, y, n, t, st))) return e;
+        TrainArgs t;
+        if ((e = prepare_steps(s, n, B, steps, t))) return e;
+        if ((e = normalize(s, X, y, n, t, st)) || (e = pack_weights(s, t, st))) return e;
         const size_t perm_elems = (size_t)s->members * n;
         if (s->perm_cap < perm_elems) {
             SDE_HIP(ctx, hipDeviceSynchronize());
@@ -1014,6 +1188,15 @@ int sde_surrogate_train(sde_surrogate* s, const float* X, const float* y, uint64
             s->perm_cap = perm_elems;
             ++ctx->ws_generation;
         }
+        t.rows = s->perm;
+        t.rows_mstride = n;
+        t.m = s->adam_m;
+        t.v = s->adam_v;
+        t.t = s->adam_t;
+        t.lr = o->lr;
+        t.b1 = o->beta1;
+        t.b2 = o->beta2;
+        t.eps = o->eps;
         std::vector<uint32_t> perm(perm_elems);
         std::vector<float> losses(steps);
         uint32_t* hperm = nullptr;
@@ -1034,8 +1217,9 @@ int sde_surrogate_train(sde_surrogate* s, const float* X, const float* y, uint64
             SDE_HIP(ctx, hipMemcpyAsync(s->perm, hperm, perm_elems * sizeof(uint32_t), hipMemcpyHostToDevice, st));
             e = run_recorded(ctx, key, st, [&](hipStream_t cs) -> int {
                 for (uint32_t k = 0; k < steps; ++k) {
-                    int r = record_step(s, t, s->perm, n, k * B, B, t.yn, k, steps, o, true, cs);
-                    if (r) return r;
+                    t.rows_offset = k * B;
+                    t.loss_slot = k;
+                    if (const int r = record_step(ctx, t, cs)) return r;
                 }
                 return SDE_OK;
             });

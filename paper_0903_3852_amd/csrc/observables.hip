@@ -174,12 +174,12 @@ __global__ __launch_bounds__(kObsThreads) void obs_combine_kernel(ObsArgs A, int
 // one LDS word are taken one after the other.  So every bin has up to 32
 // copies side by side (lane l adds to copy l mod 32, another bank), as many
 // as 64 KB hold; values come 16 bytes a lane, two loads in flight.  200 rows
-// of 2^19 windings: 227 us (1.85 TB/s) with one copy and 4-byte loads, 70 us
-// (6 TB/s, some of it from the cache) with these.
+// of 2^19 windings: 227 us (1.85 TB/s) with one copy and 4-byte loads, 75-79
+// us (5.3-5.6 TB/s) with these.
 constexpr int kHistThreads = 512;
 constexpr uint32_t kHistWords = 16384;  // LDS words for bins and their copies
 // A share of at least this many values, so that few workgroups add to the
-// same totals (one row of 2^19 phases: 24 us with 1024 of them, 8 with 64).
+// same totals (one row of 2^19 phases: 24 us with 1024 of them, 6 with 64).
 constexpr uint64_t kHistShare = 8192;
 
 __global__ void hist_zero_kernel(uint64_t* counts, uint64_t n)
