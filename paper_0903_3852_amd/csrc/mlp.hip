@@ -10,14 +10,16 @@
 // recorded once as a HIP graph; the Adam step count is a device counter, so
 // the same graph replays every epoch.
 //
-// Inference is one fused kernel for all members (mlp_infer_mfma_kernel):
-// the hidden weights are packed once per call into the fragment layout of
-// the FP32 MFMA (a 16 x 16 block per 1 KB run); a workgroup takes 64 queries
-// whose activations stay in LDS in the operand layout of the next layer,
-// each of its 4 waves computes 16 queries x all 256 outputs of a layer on
-// v_mfma_f32_16x16x4_f32 with the weights streamed from L2, bias and GELU
-// write the next operand, and the output layer, the members' mean and their
-// sample standard deviation follow.
+// Inference is one fused kernel for all members, the hidden weights packed
+// once per call into its operand layout.  Wide networks (mlp_split_infer_kernel):
+// FP16 matrix cores on operands split into two halves, activations in
+// registers from layer to layer, weights streamed through LDS.  Narrow ones
+// and those with one hidden layer (mlp_infer_mfma_kernel): a workgroup takes
+// 64 queries whose activations stay in LDS in the operand layout of the next
+// layer, each of its 4 waves computes 16 queries x all outputs of a layer on
+// v_mfma_f32_16x16x4_f32 with the weights streamed from L2.  In both, bias
+// and GELU write the next operand, and the output layer, the members' mean
+// and their sample standard deviation follow.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -721,17 +723,21 @@ __global__ void mlp_pack_hidden_kernel(PackArgs A)
         (c < A.H && k < A.H) ? W[(uint64_t)c * A.H + k] : 0.f;
 }
 
-constexpr uint32_t kInfBlocks = kInfH / 16;  // column blocks of the widest layer
-// Queries per workgroup: one 16-row block per wave, so that two workgroups
-// (68 KB of LDS each) share a CU and one's GELU epilogue overlaps the
-// other's products.
+// Networks of width 65 and more with two hidden layers or more go to
+// mlp_split_infer_kernel, so a product here has 4 column blocks at the most.
+constexpr uint32_t kSplitMinH = 65;
+constexpr uint32_t kInfBlocks = (kSplitMinH - 1) / 16;
+// Queries per workgroup: one 16-row block per wave.  LDS is sized by the
+// width, so that several workgroups (20 KB each at 64) share a CU and one's
+// GELU epilogue overlaps the other's products: 200000 queries of five
+// 5-64-64-64-1 networks 801 us with room for 256 columns, 420 us so.
 constexpr uint32_t kInfMRows = 64;
 
 __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, const float* packed, uint32_t Hp)
 {
     extern __shared__ float smem[];
     float* act = smem;                      // [kInfMRows x Hp] in the operand layout
-    float* xn = act + kInfMRows * kInfH;    // [kInfMRows][8] normalized features
+    float* xn = act + kInfMRows * Hp;       // [kInfMRows][8] normalized features
     float* outs = xn + kInfMRows * 8;       // [kInfMRows][8] member outputs
     const uint64_t r0 = (uint64_t)blockIdx.x * kInfMRows;
     const uint32_t H = A.H, KB = Hp / 16, NB = KB;
@@ -764,16 +770,12 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
         for (uint32_t l = 0; l < hidden; ++l) {
             const float* Bp = packed + ((uint64_t)mem * hidden + l) * Hp * Hp;
             const float* b = prm + A.b_off[l + 1];
-            f32x4_t acc[1][kInfBlocks];
+            f32x4_t acc[kInfBlocks];
 #pragma unroll
-            for (int m = 0; m < 1; ++m)
-#pragma unroll
-                for (int n = 0; n < (int)kInfBlocks; ++n) acc[m][n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int n = 0; n < (int)kInfBlocks; ++n) acc[n] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             for (uint32_t kb = 0; kb < KB; ++kb) {
-                f32x4_t a[1], w[kInfBlocks];
-#pragma unroll
-                for (int m = 0; m < 1; ++m)
-                    a[m] = *reinterpret_cast<const f32x4_t*>(act + (((wave + m) * KB + kb) * 64 + lane) * 4);
+                const f32x4_t a = *reinterpret_cast<const f32x4_t*>(act + ((wave * KB + kb) * 64 + lane) * 4);
+                f32x4_t w[kInfBlocks];
 #pragma unroll
                 for (int n = 0; n < (int)kInfBlocks; ++n)
                     if ((uint32_t)n < NB)
@@ -781,26 +783,21 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
 #pragma unroll
-                    for (int m = 0; m < 1; ++m)
-#pragma unroll
-                        for (int n = 0; n < (int)kInfBlocks; ++n)
-                            if ((uint32_t)n < NB)
-                                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[m][j], w[n][j], acc[m][n], 0, 0, 0);
+                    for (int n = 0; n < (int)kInfBlocks; ++n)
+                        if ((uint32_t)n < NB) acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], w[n][j], acc[n], 0, 0, 0);
             }
             __syncthreads();  // every wave has read this layer's input
 #pragma unroll
-            for (int m = 0; m < 1; ++m)
+            for (int n = 0; n < (int)kInfBlocks; ++n) {
+                if ((uint32_t)n >= NB) continue;
+                const uint32_t col = n * 16 + (lane & 15u);
+                const float bias = col < H ? b[col] : 0.f;
 #pragma unroll
-                for (int n = 0; n < (int)kInfBlocks; ++n) {
-                    if ((uint32_t)n >= NB) continue;
-                    const uint32_t col = n * 16 + (lane & 15u);
-                    const float bias = col < H ? b[col] : 0.f;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint32_t row = (wave + m) * 16 + 4 * (lane >> 4) + q;
-                        act[frag32_index(row, col, KB)] = col < H ? gelu(acc[m][n][q] + bias) : 0.f;
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t row = wave * 16 + 4 * (lane >> 4) + q;
+                    act[frag32_index(row, col, KB)] = col < H ? gelu(acc[n][q] + bias) : 0.f;
                 }
+            }
             __syncthreads();
         }
         // output layer H -> 1: four lanes per row, each a quarter of the columns
@@ -833,6 +830,390 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
             A.spread[gi] = A.members > 1 ? sqrtf(ss / (float)(A.members - 1)) : 0.f;
         }
     }
+}
+
+// Wide networks (H > 64, two hidden layers or more): the products on the FP16
+// matrix cores, both operands as hi + lo halves (22 bits and the sign between
+// them, what is lost is 2^-24 of a value), hi hi + hi lo + lo hi with FP32
+// accumulators: three products at sixteen times the FP32 matrix rate, and 24
+// roundings per sum where the FP32 chain has 256.  Powers of two keep the halves in range: a
+// weight row is scaled by its largest entry, a query's activations by a bound
+// on them (the layer's largest |b| plus largest row sum of |W| times the
+// query's largest activation of the layer before); both are taken out exactly
+// in the epilogue.
+//
+// A wave owns 16 queries; every wave of the workgroup goes through all output
+// features, 16 at a time, with the weights (A operand, rows = features)
+// streamed through LDS in chunks of 32 features that the eight waves share.
+// The k order of a product is free as long as both operands agree, and it is
+// chosen so that the C values a lane ends with (4 neighbouring features of
+// its query) are the 8 k values its B operand of the next layer needs: the
+// activations never leave the lane's registers.  The output layer is a dot
+// product in the epilogue.
+//
+// Bound by the vector unit's GELU and splitting (33 operations a value, four
+// cycles each: 200000 queries, five 5-256-256-256-1 networks 760 us) next to
+// the products (310 us at the matrix peak) and the LDS reads of the weights
+// (420 us), so the three have to overlap: a step's products are issued between
+// the parts of the step before's GELU, and the weights two blocks ahead.
+// Eight waves of 16 queries fill the registers (256 each); four waves of 32
+// would halve the LDS reads, but a wave alone on its SIMD issues too slowly.
+// 4482 us with FP32 products, 1640 with products and GELU in turn, 1226 us so
+// (214 TFLOP/s of the network's own products); at H = 128 1750 -> 478 us.
+// Error against 64 bits 1.3e-7 of the norm, with FP32 products 2.1e-7.
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+constexpr uint32_t kSplitQueries = 16;  // per wave
+constexpr uint32_t kSplitWaves = 8;
+constexpr uint32_t kSplitThreads = kSplitWaves * kWave;
+
+// GELU(z) = max(z, 0) - t q(t) with t = |z|, q(t) = erfc(t / sqrt 2) / 2 =
+// exp(-t^2 / 2) R(t); R as a polynomial in u = 1 / (1 + 0.3 t) (Chebyshev
+// fit, 1.1e-7 relative).  Against 64 bits over |z| <= 6: 2.4e-7 at the most,
+// 5.0e-8 rms (z (1 + erff) / 2: 4.5e-7, 6.6e-8), and no cancellation for
+// negative z.
+// In four parts, so that a caller can put matrix instructions between them.
+struct Gelu {
+    float z, u, e, r;
+    __device__ __forceinline__ void begin(float x)
+    {
+        z = x;
+        u = __builtin_amdgcn_rcpf(fmaf(fabsf(z), 0.3f, 1.f));
+        e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
+    }
+    __device__ __forceinline__ void first()
+    {
+        r = fmaf(0x1.35f336p-5f, u, -0x1.55841ep-3f);
+        r = fmaf(r, u, 0x1.cb1a38p-3f);
+        r = fmaf(r, u, -0x1.26b58cp-4f);
+        r = fmaf(r, u, 0x1.1e4c54p-3f);
+    }
+    __device__ __forceinline__ void second()
+    {
+        r = fmaf(r, u, 0x1.87e77ap-4f);
+        r = fmaf(r, u, 0x1.f283fcp-4f);
+        r = fmaf(r, u, 0x1.e98550p-4f);
+        r = fmaf(r, u, 0x1.957c6ep-18f);
+    }
+    __device__ __forceinline__ float end() const
+    {
+        return fmaf(-fabsf(z), e * r, __builtin_elementwise_maximum(z, 0.f));  // fmaxf would drop a NaN
+    }
+};
+
+// Largest power of two s = 2^k with s * bound < 2^15 (halves reach 2^16), k
+// limited so that s and 1 / s are normal floats.
+__device__ __forceinline__ float half_scale(float bound)
+{
+    const int e = (int)(__float_as_uint(fminf(bound, 3.4e38f)) >> 23) - 127;  // bound < 2^(e + 1)
+    const int k = min(max(14 - e, -110), 110);
+    return __uint_as_float((uint32_t)(127 + k) << 23);
+}
+
+// A member's table: per layer l < hidden four rows of Hq, bias, 1 / weight
+// scale, weight of the output layer (zero except in the last hidden layer),
+// and per 16 features the largest |bias| (from 0) and sum of |W| (from 16);
+// then the first layer's weights [Hq][wpad] and the output layer's bias.
+constexpr uint32_t kInfoRows = 4;
+__host__ __device__ constexpr uint32_t split_table(uint32_t hidden, uint32_t Hq, uint32_t wpad)
+{
+    return (hidden * kInfoRows + wpad) * Hq + 4;
+}
+
+struct SplitArgs {
+    InferArgs in;
+    uint32_t Hq;      // H rounded up to 128 or 256
+    uint32_t hidden;
+    _Float16* packed; // [members][hidden - 1][Hq / 32 chunks][32 features]...
+    uint32_t wpad;    // inputs the kernel is built for, 5 or 8
+    float* info;      // [members][split_table]
+};
+
+// One workgroup per 16 features of a layer (z = member * hidden + layer): row
+// scales and sums, then (l >= 1) the rows as hi and lo halves in the operand
+// layout: per 32 k two runs of 1 KB (hi, lo), lane i + 16 g holding feature i,
+// k = 32 kb + 16 (s / 4) + 4 g + s % 4 for its halves s = 0 .. 7.
+__global__ __launch_bounds__(256) void mlp_split_pack_kernel(SplitArgs A)
+{
+    __shared__ float scale[16], largest[2][16];
+    const uint32_t mem = blockIdx.y / A.hidden, l = blockIdx.y % A.hidden, ob = blockIdx.x;
+    const uint32_t H = A.in.H, K = l ? H : A.in.w0;
+    const float* prm = A.in.params + mem * A.in.P;
+    const float* W = prm + A.in.w_off[l];
+    float* table = A.info + (uint64_t)mem * split_table(A.hidden, A.Hq, A.wpad);
+    float* rows = table + l * kInfoRows * A.Hq;
+    {   // 16 lanes a feature
+        const uint32_t i = threadIdx.x >> 4, o = ob * 16 + i;
+        float mx = 0.f, sum = 0.f;
+        if (o < H)
+            for (uint32_t k = threadIdx.x & 15u; k < K; k += 16) {
+                const float w = fabsf(W[(uint64_t)o * K + k]);
+                mx = fmaxf(mx, w);
+                sum += w;
+            }
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) {
+            mx = fmaxf(mx, __shfl_xor(mx, off, 16));
+            sum += __shfl_xor(sum, off, 16);
+        }
+        if ((threadIdx.x & 15u) == 0) {
+            const float s = mx > 0.f ? half_scale(mx) : 1.f;
+            scale[i] = s;
+            const float bias = o < H ? prm[A.in.b_off[l] + o] : 0.f;
+            rows[o] = bias;
+            rows[A.Hq + o] = 1.f / s;
+            rows[2 * A.Hq + o] = o < H && l + 1 == A.hidden ? prm[A.in.w_off[A.hidden] + o] : 0.f;
+            largest[0][i] = fabsf(bias);
+            largest[1][i] = sum * 1.0001f;  // its own roundings
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        float m = 0.f;
+        for (int i = 0; i < 16; ++i) m = fmaxf(m, largest[threadIdx.x][i]);
+        rows[3 * A.Hq + 16 * threadIdx.x + ob] = m;
+    }
+    if (l == 0) {
+        float* w_in = table + A.hidden * kInfoRows * A.Hq;
+        for (uint32_t e = threadIdx.x; e < 16 * A.wpad; e += 256) {
+            const uint32_t o = ob * 16 + e / A.wpad, j = e % A.wpad;
+            w_in[ob * 16 * A.wpad + e] = o < H && j < K ? W[(uint64_t)o * K + j] : 0.f;
+        }
+        if (ob == 0 && threadIdx.x == 0) w_in[A.Hq * A.wpad] = prm[A.in.b_off[A.hidden]];
+        return;
+    }
+    const uint32_t KB = A.Hq / 32;
+    _Float16* out = A.packed + ((uint64_t)(mem * (A.hidden - 1) + l - 1) * (A.Hq / 16) + ob) * KB * 1024;
+    for (uint32_t e = threadIdx.x; e < KB * 64; e += 256) {
+        const uint32_t kb = e >> 6, lane = e & 63u, i = lane & 15u, g = lane >> 4, o = ob * 16 + i;
+        half8 hi, lo;
+#pragma unroll
+        for (int sl = 0; sl < 8; ++sl) {
+            const uint32_t k = kb * 32 + 16 * (sl >> 2) + 4 * g + (sl & 3);
+            const float x = o < H && k < H ? W[(uint64_t)o * H + k] * scale[i] : 0.f;
+            hi[sl] = (_Float16)x;
+            lo[sl] = (_Float16)(x - (float)hi[sl]);
+        }
+        reinterpret_cast<half8*>(out)[(2 * kb) * 64 + lane] = hi;
+        reinterpret_cast<half8*>(out)[(2 * kb + 1) * 64 + lane] = lo;
+    }
+}
+
+template <int KB, int W0>
+__global__ __launch_bounds__(kSplitThreads) void mlp_split_infer_kernel(SplitArgs S)
+{
+    constexpr uint32_t HQ = 32 * KB;
+    constexpr uint32_t kChunk = 2 * KB * 2 * 64;        // half8 per chunk of 32 features
+    constexpr uint32_t kPer = kChunk / kSplitThreads;             // of them per thread
+    __shared__ half8 ring[2][kChunk];
+    __shared__ float outs[8][kSplitWaves * kSplitQueries];        // the members' outputs
+    extern __shared__ __attribute__((aligned(16))) float info[];  // the member's table
+    const InferArgs& A = S.in;
+    const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u, g = lane >> 4;
+    const uint32_t hidden = S.hidden;
+    const uint64_t query = ((uint64_t)blockIdx.x * kSplitWaves + wave) * kSplitQueries + (lane & 15u);
+    float x[W0], xmax = 0.f;
+    {
+#pragma unroll
+        for (int j = 0; j < W0; ++j) {
+            const bool ok = query < A.n && (uint32_t)j < A.w0;
+            x[j] = ok ? (A.X[query * A.w0 + j] - A.sc.in_center[j]) / A.sc.in_scale[j] : 0.f;
+            xmax = fmaxf(xmax, fabsf(x[j]));
+        }
+    }
+    // the chunk stream: every layer of every member in turn
+    const half8* src = reinterpret_cast<const half8*>(S.packed) + tid;
+    const half8* last = src + ((uint64_t)A.members * (hidden - 1) * KB - 1) * kChunk;
+    half8 next[kPer];
+    auto fetch = [&]() {
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) next[i] = src[i * kSplitThreads];
+        src = src < last ? src + kChunk : last;
+    };
+    auto put = [&](uint32_t buf) {
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) ring[buf][i * kSplitThreads + tid] = next[i];
+    };
+    const uint32_t table = split_table(hidden, HQ, W0);
+    const float* w_in = info + hidden * kInfoRows * HQ;
+    constexpr uint32_t kCopies = (split_table(kMaxLayers - 1, HQ, W0) / 4 + kSplitThreads - 1) / kSplitThreads;
+    fetch();
+    put(0);
+    fetch();
+    for (uint32_t mem = 0; mem < A.members; ++mem) {
+        {   // sent for at once, and past the table's end its last entry again
+            const f32x4_t* from = reinterpret_cast<const f32x4_t*>(S.info + (uint64_t)mem * table);
+            f32x4_t t[kCopies];
+#pragma unroll
+            for (uint32_t i = 0; i < kCopies; ++i) t[i] = from[min(i * kSplitThreads + tid, table / 4 - 1)];
+            __syncthreads();
+#pragma unroll
+            for (uint32_t i = 0; i < kCopies; ++i)
+                if (i * kSplitThreads + tid < table / 4) reinterpret_cast<f32x4_t*>(info)[i * kSplitThreads + tid] = t[i];
+        }
+        __syncthreads();
+        // the layer's largest |bias| and row sum
+        auto layer_max = [&](uint32_t l, float& bmax, float& wmax) {
+            const f32x4_t* p = reinterpret_cast<const f32x4_t*>(info + (l * kInfoRows + 3) * HQ);
+            bmax = 0.f;
+            wmax = 0.f;
+#pragma unroll
+            for (uint32_t i = 0; i < HQ / 64; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    bmax = fmaxf(bmax, p[i][j]);
+                    wmax = fmaxf(wmax, p[4 + i][j]);
+                }
+        };
+        u32x4_t bh[KB], bl[KB], ch[KB], cl[KB];  // halves in pairs
+        float top = 0.f, scale, y = 0.f;
+        {
+            float bmax, wmax;
+            layer_max(0, bmax, wmax);
+            scale = half_scale(fmaf(wmax, xmax, bmax) * 1.001f);
+        }
+        // activations 2 i and 2 i + 1 of the four of 16 features s
+        auto keep = [&](int s, int i, float a0, float a1, const f32x4_t& wo) {
+            half2_t hi, lo;
+            top = fmaxf(fmaxf(top, fabsf(a0)), fabsf(a1));
+            y = fmaf(a0, wo[2 * i], y);
+            y = fmaf(a1, wo[2 * i + 1], y);
+            hi[0] = (_Float16)(a0 * scale);
+            hi[1] = (_Float16)(a1 * scale);
+            lo[0] = (_Float16)fmaf(a0, scale, -(float)hi[0]);
+            lo[1] = (_Float16)fmaf(a1, scale, -(float)hi[1]);
+            ch[s >> 1][2 * (s & 1) + i] = __builtin_bit_cast(uint32_t, hi);
+            cl[s >> 1][2 * (s & 1) + i] = __builtin_bit_cast(uint32_t, lo);
+            // operands in four neighbouring registers, here and now: the
+            // compiler would carry every half in a register of its own
+            if ((s & 1) && i) asm("" : "+v"(ch[s >> 1]), "+v"(cl[s >> 1]));
+        };
+        auto operand = [](const u32x4_t& x) { return __builtin_bit_cast(half8, x); };
+#pragma unroll
+        for (int o = 0; o < 2 * KB; ++o) {
+            const uint32_t f0 = o * 16 + 4 * g;
+            const f32x4_t bias = *reinterpret_cast<const f32x4_t*>(info + f0);
+            const f32x4_t wo = *reinterpret_cast<const f32x4_t*>(info + 2 * HQ + f0);
+            Gelu a[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float z = bias[q];
+#pragma unroll
+                for (int j = 0; j < W0; ++j) z = fmaf(w_in[(f0 + q) * W0 + j], x[j], z);
+                a[q].begin(z);
+                a[q].first();
+                a[q].second();
+            }
+            keep(o, 0, a[0].end(), a[1].end(), wo);
+            keep(o, 1, a[2].end(), a[3].end(), wo);
+            // without these the compiler sends for several blocks' operands at
+            // once and spills the activations
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        for (uint32_t l = 1; l < hidden; ++l) {
+            const float* inl = info + l * kInfoRows * HQ;
+            float bmax, wmax;
+            layer_max(l, bmax, wmax);
+            float m = fmaxf(top, __shfl_xor(top, 16, 64));
+            m = fmaxf(m, __shfl_xor(m, 32, 64));
+            const float inv = __uint_as_float(0x7f000000u - __float_as_uint(scale));  // 1 / scale, a power of two
+            scale = half_scale(fmaf(wmax, m, bmax) * 1.001f);
+            top = 0.f;
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                bh[k] = ch[k];
+                bl[k] = cl[k];
+            }
+            // 16 features a step, 32 k a block of 3 products; between the
+            // products of a step, a part at a time, the vector unit makes
+            // operands of the results of the step before
+            f32x4_t prev[2], bias, unw, wo;
+            Gelu z[2];
+            auto tables = [&](int s) {
+                const uint32_t f0 = s * 16 + 4 * g;
+                bias = *reinterpret_cast<const f32x4_t*>(inl + f0);
+                unw = *reinterpret_cast<const f32x4_t*>(inl + HQ + f0);
+                wo = *reinterpret_cast<const f32x4_t*>(inl + 2 * HQ + f0);
+            };
+            auto part = [&](int s, int n) {  // of eight
+                const int i = n >> 2;        // which two of the four values
+                if ((n & 3) == 0)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        z[j].begin(fmaf((prev[0][2 * i + j] + prev[1][2 * i + j]) * inv, unw[2 * i + j], bias[2 * i + j]));
+                else if ((n & 3) == 1)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) z[j].first();
+                else if ((n & 3) == 2)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) z[j].second();
+                else
+                    keep(s, i, z[0].end(), z[1].end(), wo);
+            };
+#pragma unroll
+            for (int p = 0; p < KB; ++p) {
+                const half8* w = ring[p & 1] + lane;
+                half8 hi[2], lo[2];  // the next two blocks of weights
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    hi[j] = w[2 * j * 64];
+                    lo[j] = w[(2 * j + 1) * 64];
+                }
+                f32x4_t acc[2];
+#pragma unroll
+                for (int b = 0; b < 2 * KB; ++b) {
+                    const int k = b % KB, s = 2 * p + b / KB;
+                    if (k == 0) {
+                        acc[0] = acc[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                        if (s > 0) tables(s - 1);
+                    }
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[b & 1], operand(bl[k]), acc[1], 0, 0, 0);
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[b & 1], operand(bh[k]), acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo[b & 1], operand(bh[k]), acc[1], 0, 0, 0);
+                    if (b + 2 < 2 * KB) {
+                        hi[b & 1] = w[2 * (b + 2) * 64];
+                        lo[b & 1] = w[(2 * (b + 2) + 1) * 64];
+                    }
+                    if (s > 0)
+#pragma unroll
+                        for (int n = 0; n < 8 / KB; ++n) part(s - 1, k * (8 / KB) + n);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (k == KB - 1) {
+                        prev[0] = acc[0];
+                        prev[1] = acc[1];
+                    }
+                }
+                // the next chunk, at a member's end the next member's first
+                put((p & 1) ^ 1);
+                fetch();
+                __syncthreads();
+            }
+            tables(2 * KB - 1);
+#pragma unroll
+            for (int n = 0; n < 8; ++n) part(2 * KB - 1, n);
+        }
+        float v = y + __shfl_xor(y, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (g == 0) outs[mem][wave * kSplitQueries + lane] = v + info[table - 4];
+    }
+    // members' mean and sample standard deviation, in units of <v>
+    if (g || query >= A.n) return;
+    const float omega = A.sc.target_over_omega ? A.X[query * A.w0 + 1] : 1.f;
+    float v[8], s = 0.f;
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        if ((uint32_t)m < A.members) {
+            v[m] = (A.sc.out_mean + A.sc.out_std * outs[m][wave * kSplitQueries + lane]) * omega;
+            s += v[m];
+        }
+    const float mu = s / (float)A.members;
+    float ss = 0.f;
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        if ((uint32_t)m < A.members) ss += (v[m] - mu) * (v[m] - mu);
+    A.mean[query] = mu;
+    A.spread[query] = A.members > 1 ? sqrtf(ss / (float)(A.members - 1)) : 0.f;
 }
 
 // ------------------------------------------------------------ scan glue ---
@@ -1243,6 +1624,46 @@ int sde_surrogate_train(sde_surrogate* s, const float* X, const float* y, uint64
     }
 }
 
+static int ensure_packed(sde_surrogate* s, size_t need)
+{
+    sde_ctx* ctx = s->ctx;
+    if (s->packed_bytes >= need) return SDE_OK;
+    if (s->packed) SDE_HIP(ctx, hipFree(s->packed));
+    s->packed = nullptr;
+    s->packed_bytes = 0;
+    SDE_HIP(ctx, hipMalloc(&s->packed, need));
+    s->packed_bytes = need;
+    return SDE_OK;
+}
+
+// Widths past 64 with products between hidden layers.  Below the line the
+// operands would be padded to 128 columns: 200000 queries at H = 64 420 us on
+// the FP32 products, 478 us padded; at H = 100 (two hidden layers) 304 against
+// 1060 us.
+static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
+{
+    sde_ctx* ctx = s->ctx;
+    SplitArgs S{};
+    S.in = a;
+    S.hidden = a.n_layers - 1;
+    S.Hq = a.H <= 128 ? 128 : 256;
+    S.wpad = a.w0 <= 5 ? 5 : 8;
+    const size_t halves = (size_t)a.members * (S.hidden - 1) * S.Hq * S.Hq * 2;
+    const uint32_t table = split_table(S.hidden, S.Hq, S.wpad);
+    if (const int e = ensure_packed(s, halves * sizeof(_Float16) + (size_t)a.members * table * sizeof(float))) return e;
+    S.packed = reinterpret_cast<_Float16*>(s->packed);
+    S.info = reinterpret_cast<float*>(S.packed + halves);
+    hipLaunchKernelGGL(mlp_split_pack_kernel, dim3(S.Hq / 16, a.members * S.hidden), dim3(256), 0, st, S);
+    SDE_HIP(ctx, hipGetLastError());
+    void (*kern)(SplitArgs) = S.Hq == 128 ? (S.wpad == 5 ? mlp_split_infer_kernel<4, 5> : mlp_split_infer_kernel<4, 8>)
+                                          : (S.wpad == 5 ? mlp_split_infer_kernel<8, 5> : mlp_split_infer_kernel<8, 8>);
+    const uint32_t per = kSplitQueries * kSplitWaves;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)((a.n + per - 1) / per)), dim3(kSplitThreads),
+                       table * sizeof(float), st, S);
+    SDE_HIP(ctx, hipGetLastError());
+    return SDE_OK;
+}
+
 static int predict_impl(sde_surrogate* s, const float* X, uint64_t n, float* mean, float* spread, hipStream_t st)
 {
     sde_ctx* ctx = s->ctx;
@@ -1263,17 +1684,11 @@ static int predict_impl(sde_surrogate* s, const float* X, uint64_t n, float* mea
         a.b_off[l] = s->b_off[l];
     }
     a.sc = s->sc;
+    if (a.n_layers >= 3 && a.H >= kSplitMinH) return predict_split(s, a, st);
     // hidden weights into the MFMA operand layout (Hp = H rounded up to 16)
     const uint32_t H = a.H, Hp = (H + 15u) & ~15u, hidden = a.n_layers - 2;
     if (hidden > 0) {
-        const size_t need = (size_t)s->members * hidden * Hp * Hp * sizeof(float);
-        if (s->packed_bytes < need) {
-            if (s->packed) SDE_HIP(ctx, hipFree(s->packed));
-            s->packed = nullptr;
-            s->packed_bytes = 0;
-            SDE_HIP(ctx, hipMalloc(&s->packed, need));
-            s->packed_bytes = need;
-        }
+        if (const int e = ensure_packed(s, (size_t)s->members * hidden * Hp * Hp * sizeof(float))) return e;
         PackArgs pk{};
         pk.params = s->params;
         pk.P = s->P;
@@ -1287,11 +1702,12 @@ static int predict_impl(sde_surrogate* s, const float* X, uint64_t n, float* mea
         hipLaunchKernelGGL(mlp_pack_hidden_kernel, dim3((uint32_t)((total + 255) / 256)), dim3(256), 0, st, pk);
         SDE_HIP(ctx, hipGetLastError());
     }
-    const size_t lds = (size_t)(kInfMRows * kInfH + 2 * kInfMRows * 8) * sizeof(float);
+    const size_t lds = (size_t)kInfMRows * (Hp + 16) * sizeof(float);
     static bool attr_set = false;
     if (!attr_set) {
         SDE_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_infer_mfma_kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)(kInfMRows * (kInfH + 16) * sizeof(float))));
         attr_set = true;
     }
     hipLaunchKernelGGL(mlp_infer_mfma_kernel, dim3((uint32_t)((n + kInfMRows - 1) / kInfMRows)), dim3(256), lds, st, a,
