@@ -1211,14 +1211,27 @@ __global__ __launch_bounds__(kDenseThreads, 1) void dense_mfma32_kernel(DenseArg
 }
 
 // ----------------------------------------------------------- preparation --
-// max |K_ij| as the bit pattern of a non-negative float (order-independent max).
-__global__ void dense_maxabs_kernel(const float* K, uint64_t n, uint32_t* out)
+// max |K_ij| as the bit pattern of a non-negative float (order-independent
+// max).  Bound by HBM reads, so eight loads a lane in flight (past the end
+// the last entry again) and one atomic per workgroup: N = 4096 65 -> 21 us
+// (one load in flight, an atomic per wave before).
+__global__ __launch_bounds__(256) void dense_maxabs_kernel(const float* K, uint64_t n, uint32_t* out)
 {
+    __shared__ uint32_t part[256 / kWave];
+    constexpr uint32_t kLoads = 8;
+    const uint64_t stride = (uint64_t)gridDim.x * 256;
     uint32_t m = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-        m = max(m, __float_as_uint(fabsf(K[i])));
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += kLoads * stride) {
+        float x[kLoads];
+#pragma unroll
+        for (uint32_t k = 0; k < kLoads; ++k) x[k] = K[std::min<uint64_t>(i + k * stride, n - 1)];
+#pragma unroll
+        for (uint32_t k = 0; k < kLoads; ++k) m = max(m, __float_as_uint(fabsf(x[k])));
+    }
     for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, kWave));
-    if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(out, m);
+    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(out, max(max(part[0], part[1]), max(part[2], part[3])));
 }
 
 __global__ void dense_zero_kernel(uint32_t* p) { *p = 0u; }
@@ -1234,24 +1247,59 @@ __global__ void dense_scale_kernel(const uint32_t* maxbits, float* scale, int un
 }
 
 // K -> scaled, padded copy over Mp rows x Np columns (zero outside N x N) in
-// the packed layout: FP32, or the 16-bit hi/lo split.
+// the packed layout: FP32, or the 16-bit hi/lo split.  The split's threads
+// take the eight k of a lane's share of a fragment, so that a wave writes two
+// full 1 KB runs (N = 4096: 36 -> 20 us, an entry a thread before).
 template <typename T>
-__global__ void dense_split_kernel(const float* K, uint32_t N, uint32_t Np, uint32_t Mp, const float* scale, void* out)
+__global__ __launch_bounds__(256) void dense_split_kernel(const float* K, uint32_t N, uint32_t Np, uint32_t Mp,
+                                                          const float* scale, void* out)
 {
-    const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (uint64_t)Mp * Np) return;
-    const uint32_t i = (uint32_t)(g / Np), j = (uint32_t)(g % Np);
-    const float x = (i < N && j < N) ? K[(uint64_t)i * N + j] * scale[0] : 0.f;
-    if constexpr (sizeof(T) == 4)
+    const uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    if constexpr (sizeof(T) == 4) {
+        if (g >= (uint64_t)Mp * Np) return;
+        const uint32_t i = (uint32_t)(g / Np), j = (uint32_t)(g % Np);
+        const float x = (i < N && j < N) ? K[(uint64_t)i * N + j] * scale[0] : 0.f;
         static_cast<float*>(out)[frag32_off(i, j, Np / 16)] = x;
-    else
-        store_split<T>(static_cast<T*>(out), frag_off(i, j, Np / kKStep), x);
+    } else {
+        if (g >= (uint64_t)Mp * Np / 8) return;
+        typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+        typedef T T8 __attribute__((ext_vector_type(8)));
+        const uint32_t KB = Np / kKStep, lane = (uint32_t)g & 63u, blk = (uint32_t)(g >> 6);
+        const uint32_t i = blk / KB * 16 + (lane & 15u), j = blk % KB * kKStep + (lane >> 4) * 8;
+        const float* row = K + (uint64_t)std::min(i, N - 1) * N;
+        float x[8];
+        if (j + 8 <= N) {
+            const f32x4_any a = *reinterpret_cast<const f32x4_any*>(row + j);
+            const f32x4_any b = *reinterpret_cast<const f32x4_any*>(row + j + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[e] = a[e];
+                x[4 + e] = b[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = j + e < N ? row[j + e] : 0.f;
+        }
+        const float sc = scale[0];
+        T8 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v = i < N ? x[e] * sc : 0.f;
+            hi[e] = (T)v;
+            lo[e] = (T)(v - (float)hi[e]);
+        }
+        T* to = static_cast<T*>(out) + frag_off(i, j, KB);
+        *reinterpret_cast<T8*>(to) = hi;
+        *reinterpret_cast<T8*>(to + kFragLo) = lo;
+    }
 }
 
 // theta [R][N] -> sin/cos operand over 2 Rp columns x Np rows of k (zero in
 // the padding) in the packed layout: FP32, or the 16-bit hi/lo split.
+// Two copies, `out` and the buffer `pitch` bytes past it.
 template <typename T>
-__global__ void dense_operand_kernel(const float* theta, uint32_t N, uint32_t R, uint32_t Np, uint32_t Rp, void* out)
+__global__ void dense_operand_kernel(const float* theta, uint32_t N, uint32_t R, uint32_t Np, uint32_t Rp, char* out,
+                                     size_t pitch)
 {
     const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= (uint64_t)Rp * Np) return;
@@ -1262,13 +1310,15 @@ __global__ void dense_operand_kernel(const float* theta, uint32_t N, uint32_t R,
         s = sin_rev(t);
         c = cos_rev(t);
     }
-    if constexpr (sizeof(T) == 4) {
-        static_cast<float*>(out)[frag32_off(bcol(r, 0), j, Np / 16)] = s;
-        static_cast<float*>(out)[frag32_off(bcol(r, 1), j, Np / 16)] = c;
-    } else {
-        T* B = static_cast<T*>(out);
-        store_split<T>(B, frag_off(bcol(r, 0), j, Np / kKStep), s);
-        store_split<T>(B, frag_off(bcol(r, 1), j, Np / kKStep), c);
+    for (int b = 0; b < 2; ++b) {
+        T* B = reinterpret_cast<T*>(out + b * pitch);
+        if constexpr (sizeof(T) == 4) {
+            B[frag32_off(bcol(r, 0), j, Np / 16)] = s;
+            B[frag32_off(bcol(r, 1), j, Np / 16)] = c;
+        } else {
+            store_split<T>(B, frag_off(bcol(r, 0), j, Np / kKStep), s);
+            store_split<T>(B, frag_off(bcol(r, 1), j, Np / kKStep), c);
+        }
     }
 }
 
@@ -1314,13 +1364,13 @@ static int dense_run_typed(sde_ctx* ctx, const sde_kuramoto_desc* d, const sde_r
     hipLaunchKernelGGL(dense_zero_kernel, dim3(1), dim3(1), 0, stream, maxbits);
     if (split) hipLaunchKernelGGL(dense_maxabs_kernel, dim3(1024), dim3(256), 0, stream, K, (uint64_t)N * N, maxbits);
     hipLaunchKernelGGL(dense_scale_kernel, dim3(1), dim3(1), 0, stream, maxbits, scale, split ? 0 : 1);
-    hipLaunchKernelGGL(dense_split_kernel<T>, dim3((uint32_t)(((uint64_t)Mp * Np + 255) / 256)), dim3(256), 0, stream,
-                       K, N, Np, Mp, scale, wa);
+    const uint64_t split_threads = (uint64_t)Mp * Np / (split ? 8 : 1);
+    hipLaunchKernelGGL(dense_split_kernel<T>, dim3((uint32_t)((split_threads + 255) / 256)), dim3(256), 0, stream, K, N,
+                       Np, Mp, scale, wa);
     // both operand buffers get their zero padding (rows j >= N, columns of
     // realizations r >= R) here; the epilogues only ever write the live part
-    for (int b = 0; b < 2; ++b)
-        hipLaunchKernelGGL(dense_operand_kernel<T>, dim3((uint32_t)(((uint64_t)Rp * Np + 255) / 256)), dim3(256), 0,
-                           stream, phi, N, R, Np, Rp, Bbuf[b]);
+    hipLaunchKernelGGL(dense_operand_kernel<T>, dim3((uint32_t)(((uint64_t)Rp * Np + 255) / 256)), dim3(256), 0, stream,
+                       phi, N, R, Np, Rp, B0, b_bytes);
     SDE_HIP(ctx, hipGetLastError());
 
     DenseArgs A;
