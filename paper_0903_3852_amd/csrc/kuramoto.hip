@@ -1200,20 +1200,30 @@ __global__ __launch_bounds__(256) void kuramoto_tiled_combine_kernel(TiledArgs A
     const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= NR) return;
     float acc = 0.f;
+#pragma unroll 8
     for (uint32_t z = 0; z < J; ++z) acc += part[(uint64_t)z * NR + g];
     tiled_stage_update(A, (uint32_t)(g / A.N), (uint32_t)(g % A.N), acc, load_uniform(A.nbase) + A.k);
 }
 
-__global__ __launch_bounds__(256) void order_parameter_kernel(const float* theta, uint32_t N, double* out,
-                                                              uint64_t stride, uint64_t col)
+// r of realization blockIdx.x by one workgroup: a chain of loads, so 16 waves
+// with four loads each in flight (N = 16384, four realizations 15 -> 5
+// us; 4 waves of one load before).
+constexpr uint32_t kOrderThreads = 1024;
+__device__ __forceinline__ void order_parameter(const float* theta, uint32_t N, double* out)
 {
-    __shared__ double lds[2 * 256 / kWave];
-    const uint32_t r = blockIdx.x;
+    __shared__ double lds[2 * kOrderThreads / kWave];
+    const float* th = theta + (uint64_t)blockIdx.x * N;
     double s = 0.0, c = 0.0;
-    for (uint32_t i = threadIdx.x; i < N; i += 256) {
-        const float t = theta[(uint64_t)r * N + i];
-        s += (double)sin_rev(t);
-        c += (double)cos_rev(t);
+    for (uint32_t b = 0; b < N; b += 4 * kOrderThreads) {
+        float t[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) t[k] = th[min(b + k * kOrderThreads + threadIdx.x, N - 1)];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const bool in = b + k * kOrderThreads + threadIdx.x < N;
+            s += in ? (double)sin_rev(t[k]) : 0.0;
+            c += in ? (double)cos_rev(t[k]) : 0.0;
+        }
     }
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     s = wave_sum(s);
@@ -1225,46 +1235,29 @@ __global__ __launch_bounds__(256) void order_parameter_kernel(const float* theta
     __syncthreads();
     if (threadIdx.x == 0) {
         double S = 0.0, C = 0.0;
-        for (int w = 0; w < 256 / kWave; ++w) {
+        for (int w = 0; w < (int)(kOrderThreads / kWave); ++w) {
             S += lds[2 * w];
             C += lds[2 * w + 1];
         }
-        out[(uint64_t)r * stride + col] = std::sqrt(S * S + C * C) / (double)N;
+        *out = std::sqrt(S * S + C * C) / (double)N;
     }
+}
+
+__global__ __launch_bounds__(kOrderThreads) void order_parameter_kernel(const float* theta, uint32_t N, double* out,
+                                                                        uint64_t stride, uint64_t col)
+{
+    order_parameter(theta, N, out + (uint64_t)blockIdx.x * stride + col);
 }
 
 // The same, at local step l = *nbase - step0, only when l is a multiple of
 // M (column l / M): lets one recorded chunk of steps sample where due.
-__global__ __launch_bounds__(256) void order_parameter_at_kernel(const float* theta, uint32_t N, double* out,
-                                                                 uint64_t stride, const uint64_t* nbase,
-                                                                 uint64_t step0, uint32_t M)
+__global__ __launch_bounds__(kOrderThreads) void order_parameter_at_kernel(const float* theta, uint32_t N, double* out,
+                                                                           uint64_t stride, const uint64_t* nbase,
+                                                                           uint64_t step0, uint32_t M)
 {
     const uint64_t l = load_uniform(nbase) - step0;
     if (l % M) return;
-    __shared__ double lds[2 * 256 / kWave];
-    const uint32_t r = blockIdx.x;
-    double s = 0.0, c = 0.0;
-    for (uint32_t i = threadIdx.x; i < N; i += 256) {
-        const float t = theta[(uint64_t)r * N + i];
-        s += (double)sin_rev(t);
-        c += (double)cos_rev(t);
-    }
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    s = wave_sum(s);
-    c = wave_sum(c);
-    if (lane == 0) {
-        lds[2 * wid] = s;
-        lds[2 * wid + 1] = c;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double S = 0.0, C = 0.0;
-        for (int w = 0; w < 256 / kWave; ++w) {
-            S += lds[2 * w];
-            C += lds[2 * w + 1];
-        }
-        out[(uint64_t)r * stride + l / M] = std::sqrt(S * S + C * C) / (double)N;
-    }
+    order_parameter(theta, N, out + (uint64_t)blockIdx.x * stride + l / M);
 }
 
 __global__ void step_set_kernel(uint64_t* nbase, uint64_t v) { *nbase = v; }
@@ -1291,13 +1284,13 @@ __global__ void kuramoto_init_kernel(float* theta, uint32_t N, uint32_t R, uint3
 void launch_order_parameter(const float* theta, uint32_t N, uint32_t R, double* out, uint64_t stride,
                             uint64_t col, hipStream_t stream)
 {
-    hipLaunchKernelGGL(order_parameter_kernel, dim3(R), dim3(256), 0, stream, theta, N, out, stride, col);
+    hipLaunchKernelGGL(order_parameter_kernel, dim3(R), dim3(kOrderThreads), 0, stream, theta, N, out, stride, col);
 }
 
 void launch_order_parameter_at(const float* theta, uint32_t N, uint32_t R, double* out, uint64_t stride,
                                const uint64_t* nbase, uint64_t step0, uint32_t M, hipStream_t stream)
 {
-    hipLaunchKernelGGL(order_parameter_at_kernel, dim3(R), dim3(256), 0, stream, theta, N, out, stride, nbase, step0,
+    hipLaunchKernelGGL(order_parameter_at_kernel, dim3(R), dim3(kOrderThreads), 0, stream, theta, N, out, stride, nbase, step0,
                        M);
 }
 
