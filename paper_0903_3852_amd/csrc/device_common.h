@@ -112,14 +112,23 @@ __device__ __forceinline__ void gauss4_scaled(U4 c, uint32_t k0, uint32_t k1, fl
 // sigma * Gaussian j (0..3) of block c alone, by the same operations that
 // gauss4_scaled applies for that output (pair j / 2, cosine for even j).
 // j should be wave-uniform.
-__device__ __forceinline__ float gauss1_scaled(U4 c, uint32_t k0, uint32_t k1, float c2, uint32_t j)
+// It is rho * dir.
+__device__ __forceinline__ void gauss1_polar(U4 c, uint32_t k0, uint32_t k1, float c2, uint32_t j, float& rho,
+                                             float& dir)
 {
     const U4 x = philox4x32_10(c, k0, k1);
     const uint32_t w1 = j < 2 ? x.x : x.z, w2 = j < 2 ? x.y : x.w;
     const float u1 = (float)((w1 >> 8) + 1u) * 0x1p-24f;
     const float u2 = (float)(w2 >> 8) * 0x1p-24f;
-    const float rho = __builtin_amdgcn_sqrtf(c2 * __builtin_amdgcn_logf(u1));
-    return rho * ((j & 1u) ? __builtin_amdgcn_sinf(u2) : __builtin_amdgcn_cosf(u2));
+    rho = __builtin_amdgcn_sqrtf(c2 * __builtin_amdgcn_logf(u1));
+    dir = (j & 1u) ? __builtin_amdgcn_sinf(u2) : __builtin_amdgcn_cosf(u2);
+}
+
+__device__ __forceinline__ float gauss1_scaled(U4 c, uint32_t k0, uint32_t k1, float c2, uint32_t j)
+{
+    float rho, dir;
+    gauss1_polar(c, k0, k1, c2, j, rho, dir);
+    return rho * dir;
 }
 
 // Load of wave-uniform read-only data through the constant address space,

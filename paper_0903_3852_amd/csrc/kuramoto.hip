@@ -926,7 +926,13 @@ __global__ __launch_bounds__(kMFPThreads, 1) void kuramoto_mfp_kernel(MFArgs A)
 //   carry = theta + dt/(4 pi) (F1 + omega) + noise,
 // so that the corrector pass needs only tt and carry:
 //   theta' = carry + dt/(4 pi) (K/N) (cos tt S2 - sin tt C2)
-// (28 bytes per oscillator-step; Euler-Maruyama 12).  The noise is component
+// (28 bytes per oscillator-step; Euler-Maruyama 12).  LDS holds theta, and
+// between the passes tt in its place, for the first 36 rows of 1024
+// oscillators of a workgroup's slice, and with what is left their carry: 16
+// and 8 bytes less per oscillator-step (2^24 oscillators, 64 rows: 19 bytes;
+// 2^21: 4).  A step of 2^24 on one device 91 -> 70 us, of 2^22 28 -> 22 us;
+// bound by the vector unit, mostly Philox and Box-Muller (about 58 us), with
+// the traffic (62 us) beside it.  The noise is component
 // n & 3 of the Gaussians of Philox block n >> 2, regenerated every step: the
 // same stream the register-resident kernel draws once per block.
 struct MFSArgs {
@@ -941,6 +947,7 @@ struct MFSArgs {
     uint32_t N, R, G, M;
     uint32_t r_base;
     uint32_t chunk;          // oscillators per workgroup slice
+    uint32_t lds_theta, lds_carry;  // rows of kMFSThreads held in LDS, whole batches
     uint64_t step0, n_steps, n_samples;
     uint32_t key0, key1;
     float omega_scale, hdt2pi, kn, c2;
@@ -948,9 +955,10 @@ struct MFSArgs {
     uint32_t tree;
 };
 
-// Each pass takes kMFSBatch oscillators per lane per iteration (stride
-// kMFSThreads), all loads first, to keep several memory requests in flight.
+// Each pass takes kMFSBatch rows of a slice per iteration, with the next
+// batch's loads in flight (unconditional, clamped to the slice).
 constexpr int kMFSBatch = 4;
+constexpr uint32_t kMFSLdsRows = 36;  // of 160 KB; the exchange takes 5
 
 template <int SCHEME>
 __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
@@ -958,111 +966,166 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
     __shared__ double lds[2 * kMFSThreads / kWave];
     __shared__ uint32_t words[kMFWordsPerGroup * kMaxMFSGroups];
     __shared__ int lds_ok;
+    extern __shared__ float held[];  // [lds_theta + lds_carry rows][kMFSThreads]
     if (threadIdx.x == 0) lds_ok = 1;  // made visible by the exchange's first barrier
-    const uint32_t r = blockIdx.x / A.G, w = blockIdx.x % A.G;
+    const uint32_t r = blockIdx.x / A.G, w = blockIdx.x % A.G, tid = threadIdx.x;
     const uint64_t N = A.N;
-    const uint64_t i0 = (uint64_t)w * A.chunk, i1 = std::min<uint64_t>(N, i0 + A.chunk);
-    float* th = A.theta + (uint64_t)r * N;
-    float* tl = A.tilde + (uint64_t)r * N;
-    float* cy = A.carry + (uint64_t)r * N;
+    const uint64_t i0 = std::min<uint64_t>(N, (uint64_t)w * A.chunk), i1 = std::min<uint64_t>(N, i0 + A.chunk);
+    float* th = A.theta + (uint64_t)r * N + i0;
+    float* tl = A.tilde + (uint64_t)r * N + i0;
+    float* cy = A.carry + (uint64_t)r * N + i0;
+    const float* omega = A.omega + i0;
     const uint32_t rr = A.r_base + r;
-    constexpr uint64_t kStep = (uint64_t)kMFSBatch * kMFSThreads;
+    // rows of the slice, those with theta and with carry in LDS
+    const uint32_t rows = (uint32_t)((i1 - i0 + kMFSThreads - 1) / kMFSThreads);
+    const uint32_t rows_theta = std::min(rows, A.lds_theta), rows_carry = std::min(rows, A.lds_carry);
+    float* held_cy = held + A.lds_theta * kMFSThreads;
+    // live oscillators from row `row` on, as far as a batch reaches
+    auto left = [&](uint32_t row) {
+        return (uint32_t)std::min<uint64_t>(i1 - i0 - (uint64_t)row * kMFSThreads, kMFSBatch * kMFSThreads);
+    };
+    auto load = [&](const float* from, uint32_t row, float (&x)[kMFSBatch]) {
+        const float* at = from + (uint64_t)row * kMFSThreads;
+        const uint32_t end = left(row) - 1;
+#pragma unroll
+        for (int k = 0; k < kMFSBatch; ++k) x[k] = at[min(k * kMFSThreads + tid, end)];
+    };
     uint32_t epoch = 0;
-    auto exchange = [&](double s, double c, double& S, double& C) -> bool {
+    double s = 0.0, c = 0.0, S, C;
+    auto add = [&](bool in, float u) {
+        s += (double)(in ? sin_rev(u) : 0.f);
+        c += (double)(in ? cos_rev(u) : 0.f);
+    };
+    auto exchange = [&]() -> bool {
         if (!mf_exchange<kMFSThreads>(A, r, w, epoch, s, c, lds, words, &lds_ok, S, C)) return false;
         ++epoch;
+        s = 0.0;
+        c = 0.0;
         return true;
     };
-    double s = 0.0, c = 0.0, S, C;
-    for (uint64_t b = i0 + threadIdx.x; b < i1; b += kStep) {
+    for (uint32_t row = 0; row < rows; row += kMFSBatch) {
         float t[kMFSBatch];
+        load(th, row, t);
+        const uint32_t n_left = left(row);
 #pragma unroll
         for (int k = 0; k < kMFSBatch; ++k) {
-            const uint64_t i = b + (uint64_t)k * kMFSThreads;
-            t[k] = i < i1 ? th[i] : 0.f;
+            if (row < rows_theta) held[(row + k) * kMFSThreads + tid] = t[k];
+            add(k * kMFSThreads + tid < n_left, t[k]);
         }
-#pragma unroll
-        for (int k = 0; k < kMFSBatch; ++k)
-            if (b + (uint64_t)k * kMFSThreads < i1) {
-                s += (double)sin_rev(t[k]);
-                c += (double)cos_rev(t[k]);
-            }
     }
-    if (!exchange(s, c, S, C)) return;
+    if (!exchange()) return;
     const double invN = 1.0 / (double)N;
     uint64_t n = A.step0, local = 0;
     const uint64_t n_end = A.step0 + A.n_steps;
-    for (;;) {
-        if (A.r_samples && local % A.M == 0 && w == 0 && threadIdx.x == 0)
-            A.r_samples[(uint64_t)r * A.n_samples + local / A.M] = std::sqrt(S * S + C * C) * invN;
-        if (n == n_end) break;
+    float Sf, Cf;
+    // predictor (Heun) or the whole step (Euler-Maruyama) of rows [row, end),
+    // theta or the carry in LDS or not
+    auto first = [&](auto theta_held, auto carry_held, uint32_t row, uint32_t end) {
         const uint32_t blk = (uint32_t)(n >> 2), j = (uint32_t)n & 3u;
-        float Sf = (float)S, Cf = (float)C;
-        s = 0.0;
-        c = 0.0;
-        // predictor (Heun) or the whole step (Euler-Maruyama)
-        for (uint64_t b = i0 + threadIdx.x; b < i1; b += kStep) {
-            float t0[kMFSBatch], om[kMFSBatch];
+        float t0[kMFSBatch], om[kMFSBatch], t0n[kMFSBatch], omn[kMFSBatch];
+        if (row >= end) return;
+        load(omega, row, omn);
+        if (!theta_held) load(th, row, t0n);
+        for (; row < end; row += kMFSBatch) {
+            const uint32_t next = min(row + kMFSBatch, end - 1) / kMFSBatch * kMFSBatch, n_left = left(row);
 #pragma unroll
             for (int k = 0; k < kMFSBatch; ++k) {
-                const uint64_t i = b + (uint64_t)k * kMFSThreads;
-                t0[k] = i < i1 ? th[i] : 0.f;
-                om[k] = i < i1 ? A.omega[i] : 0.f;
+                om[k] = omn[k];
+                t0[k] = theta_held ? held[(row + k) * kMFSThreads + tid] : t0n[k];
             }
+            load(omega, next, omn);
+            if (!theta_held) load(th, next, t0n);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint64_t at = (uint64_t)row * kMFSThreads + tid;
 #pragma unroll
             for (int k = 0; k < kMFSBatch; ++k) {
-                const uint64_t i = b + (uint64_t)k * kMFSThreads;
-                if (i >= i1) continue;
+                if ((uint32_t)(k * kMFSThreads) >= n_left) break;  // a row past the slice
+                const bool in = k * kMFSThreads + tid < n_left;
+                const uint64_t e = at + k * kMFSThreads;
                 const float F1 = fmaf(A.kn, fmaf(cos_rev(t0[k]), Sf, -sin_rev(t0[k]) * Cf), om[k]);
-                const float ns =
-                    gauss1_scaled(U4{blk, (uint32_t)i, rr, (uint32_t)SDE_TAG_NOISE}, A.key0, A.key1, A.c2, j);
-                const float tt = fmaf(A.omega_scale, F1, t0[k]) + ns;
-                float u;
+                float rho, dir;  // the noise is their product
+                gauss1_polar(U4{blk, (uint32_t)(i0 + e), rr, (uint32_t)SDE_TAG_NOISE}, A.key0, A.key1, A.c2, j, rho, dir);
+                const float tt = fmaf(rho, dir, fmaf(A.omega_scale, F1, t0[k]));
+                float u = tt;
                 if (SCHEME == SDE_HEUN) {
-                    tl[i] = tt;
-                    cy[i] = fmaf(A.hdt2pi, F1 + om[k], t0[k]) + ns;
-                    u = tt;
+                    const float cv = fmaf(rho, dir, fmaf(A.hdt2pi, F1 + om[k], t0[k]));
+                    if (carry_held)
+                        held_cy[(row + k) * kMFSThreads + tid] = cv;
+                    else if (in)
+                        cy[e] = cv;
                 } else {
                     u = tt - floorf(tt);
-                    th[i] = u;
                 }
-                s += (double)sin_rev(u);
-                c += (double)cos_rev(u);
+                if (theta_held)
+                    held[(row + k) * kMFSThreads + tid] = u;
+                else if (in)
+                    (SCHEME == SDE_HEUN ? tl : th)[e] = u;
+                add(in, u);
             }
         }
-        if (!exchange(s, c, S, C)) return;
+    };
+    // corrector of rows [row, end)
+    auto second = [&](auto theta_held, auto carry_held, uint32_t row, uint32_t end) {
+        float tt[kMFSBatch], cv[kMFSBatch], ttn[kMFSBatch], cvn[kMFSBatch];
+        if (row >= end) return;
+        if (!carry_held) load(cy, row, cvn);
+        if (!theta_held) load(tl, row, ttn);
+        for (; row < end; row += kMFSBatch) {
+            const uint32_t next = min(row + kMFSBatch, end - 1) / kMFSBatch * kMFSBatch, n_left = left(row);
+#pragma unroll
+            for (int k = 0; k < kMFSBatch; ++k) {
+                cv[k] = carry_held ? held_cy[(row + k) * kMFSThreads + tid] : cvn[k];
+                tt[k] = theta_held ? held[(row + k) * kMFSThreads + tid] : ttn[k];
+            }
+            if (!carry_held) load(cy, next, cvn);
+            if (!theta_held) load(tl, next, ttn);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint64_t at = (uint64_t)row * kMFSThreads + tid;
+#pragma unroll
+            for (int k = 0; k < kMFSBatch; ++k) {
+                if ((uint32_t)(k * kMFSThreads) >= n_left) break;  // a row past the slice
+                const bool in = k * kMFSThreads + tid < n_left;
+                const float t = fmaf(A.hdt2pi, A.kn * fmaf(cos_rev(tt[k]), Sf, -sin_rev(tt[k]) * Cf), cv[k]);
+                const float u = t - floorf(t);
+                if (theta_held)
+                    held[(row + k) * kMFSThreads + tid] = u;
+                else if (in)
+                    th[at + k * kMFSThreads] = u;
+                add(in, u);
+            }
+        }
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    for (;;) {
+        if (A.r_samples && local % A.M == 0 && w == 0 && tid == 0)
+            A.r_samples[(uint64_t)r * A.n_samples + local / A.M] = std::sqrt(S * S + C * C) * invN;
+        if (n == n_end) break;
+        Sf = (float)S;
+        Cf = (float)C;
+        if (SCHEME == SDE_HEUN) first(yes, yes, 0, rows_carry);
+        first(yes, no, rows_carry, rows_theta);
+        first(no, no, rows_theta, rows);
+        if (!exchange()) return;
         if (SCHEME == SDE_HEUN) {
             Sf = (float)S;
             Cf = (float)C;
-            s = 0.0;
-            c = 0.0;
-            for (uint64_t b = i0 + threadIdx.x; b < i1; b += kStep) {
-                float tt[kMFSBatch], cv[kMFSBatch];
-#pragma unroll
-                for (int k = 0; k < kMFSBatch; ++k) {
-                    const uint64_t i = b + (uint64_t)k * kMFSThreads;
-                    tt[k] = i < i1 ? tl[i] : 0.f;
-                    cv[k] = i < i1 ? cy[i] : 0.f;
-                }
-#pragma unroll
-                for (int k = 0; k < kMFSBatch; ++k) {
-                    const uint64_t i = b + (uint64_t)k * kMFSThreads;
-                    if (i >= i1) continue;
-                    const float t = fmaf(A.hdt2pi, A.kn * fmaf(cos_rev(tt[k]), Sf, -sin_rev(tt[k]) * Cf), cv[k]);
-                    const float u = t - floorf(t);
-                    th[i] = u;
-                    s += (double)sin_rev(u);
-                    c += (double)cos_rev(u);
-                }
-            }
-            if (!exchange(s, c, S, C)) return;
+            second(yes, yes, 0, rows_carry);
+            second(yes, no, rows_carry, rows_theta);
+            second(no, no, rows_theta, rows);
+            if (!exchange()) return;
         }
         ++n;
         ++local;
     }
     bool bad = false;
-    for (uint64_t i = i0 + threadIdx.x; i < i1; i += kMFSThreads) bad |= !isfinite(th[i]);
-    if (__ballot(bad) != 0 && (threadIdx.x & (kWave - 1)) == 0) atomicOr(A.flag, 1);
+    for (uint32_t row = 0; row < rows; ++row) {
+        const uint64_t e = (uint64_t)row * kMFSThreads + tid;
+        if (e >= i1 - i0) break;
+        if (row < rows_theta) th[e] = held[row * kMFSThreads + tid];
+        bad |= !isfinite(th[e]);
+    }
+    if (__ballot(bad) != 0 && (tid & (kWave - 1)) == 0) atomicOr(A.flag, 1);
 }
 
 __global__ void mf_zero_kernel(uint32_t* p, size_t n)
@@ -1206,8 +1269,8 @@ __global__ __launch_bounds__(256) void kuramoto_tiled_combine_kernel(TiledArgs A
 }
 
 // r of realization blockIdx.x by one workgroup: a chain of loads, so 16 waves
-// with four loads each in flight (N = 16384, four realizations 15 -> 5
-// us; 4 waves of one load before).
+// with four loads each in flight (N = 16384, four realizations 15 -> 5 us; 4
+// waves of one load before).
 constexpr uint32_t kOrderThreads = 1024;
 __device__ __forceinline__ void order_parameter(const float* theta, uint32_t N, double* out)
 {
@@ -1385,7 +1448,9 @@ static int run_meanfield_streamed(sde_ctx* ctx, const sde_kuramoto_desc* d, cons
     void* kern = heun ? reinterpret_cast<void*>(kuramoto_mfs_kernel<SDE_HEUN>)
                       : reinterpret_cast<void*>(kuramoto_mfs_kernel<SDE_EULER>);
     int per_cu = 0;
-    SDE_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kMFSThreads, 0));
+    const size_t most = (size_t)kMFSLdsRows * kMFSThreads * sizeof(float);
+    SDE_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
+    SDE_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kMFSThreads, most));
     const uint64_t capacity = (uint64_t)std::max(per_cu, 0) * ctx->n_cu;
     if (capacity == 0) return fail(ctx, SDE_ERR_UNSUPPORTED, "streamed mean-field kernel does not fit a CU");
     const uint32_t r_per_launch = (uint32_t)std::min<uint64_t>(d->R, capacity);
@@ -1393,6 +1458,11 @@ static int run_meanfield_streamed(sde_ctx* ctx, const sde_kuramoto_desc* d, cons
     const uint32_t G = (uint32_t)std::max<uint64_t>(
         1, std::min<uint64_t>({(uint64_t)kMaxMFSGroups, capacity / r_per_launch, by_lanes}));
     const uint32_t chunk = (uint32_t)(((uint64_t)d->N + G - 1) / G);
+    // theta first, 16 bytes a step less for each row, then the carry, 8
+    const uint32_t rows = ((chunk + kMFSThreads - 1) / kMFSThreads + kMFSBatch - 1) / kMFSBatch * kMFSBatch;
+    const uint32_t lds_theta = std::min(rows, kMFSLdsRows);
+    const uint32_t lds_carry = heun ? std::min(rows, kMFSLdsRows - lds_theta) / kMFSBatch * kMFSBatch : 0;
+    const size_t lds_bytes = (size_t)(lds_theta + lds_carry) * kMFSThreads * sizeof(float);
     const uint64_t NR = (uint64_t)d->N * d->R;
     if (run->init == SDE_INIT_PHILOX) {
         launch_kuramoto_init(phi, d->N, d->R, run->seed, stream);
@@ -1427,6 +1497,8 @@ static int run_meanfield_streamed(sde_ctx* ctx, const sde_kuramoto_desc* d, cons
         A.M = M;
         A.r_base = r0;
         A.chunk = chunk;
+        A.lds_theta = lds_theta;
+        A.lds_carry = lds_carry;
         A.step0 = run->step0;
         A.n_steps = d->n_steps;
         A.n_samples = n_samples;
@@ -1438,7 +1510,7 @@ static int run_meanfield_streamed(sde_ctx* ctx, const sde_kuramoto_desc* d, cons
         A.c2 = kc.c2;
         A.spin_limit = 1u << 26;
         void* args[] = {&A};
-        SDE_HIP(ctx, hipLaunchCooperativeKernel(kern, dim3(nr * G), dim3(kMFSThreads), args, 0, stream));
+        SDE_HIP(ctx, hipLaunchCooperativeKernel(kern, dim3(nr * G), dim3(kMFSThreads), args, lds_bytes, stream));
     }
     ctx->last.mf_streamed = 1;
     return SDE_OK;
