@@ -106,18 +106,24 @@ def mfs_ops_per_osc_step(heun):
     return noise + trans + sums + (12 if heun else 7)
 
 
-def mfs_bytes_per_osc_step(heun):
-    """HBM bytes per oscillator-step of the streamed mean field: Heun reads
-    theta, omega and writes tt, carry; then reads tt, carry and writes theta
-    (7 words); Euler-Maruyama reads theta, omega and writes theta (3)."""
-    return 4 * (7 if heun else 3)
+def mfs_bytes_per_osc_step(heun, N, cu):
+    """HBM bytes per oscillator-step of the streamed mean field, one
+    realization over `cu` workgroups: Heun reads theta, omega and writes tt,
+    carry; then reads tt, carry and writes theta (7 words); Euler-Maruyama
+    reads theta, omega and writes theta (3).  Of a slice's rows of 1024
+    oscillators, LDS holds theta (and tt) of the first 36, 4 (2) words less,
+    and the carry of what still fits, 2 words less."""
+    rows = -(-(-(-N // cu)) // 1024)
+    theta = min(rows, 36)
+    carry = min(rows, (36 - min(-(-rows // 4) * 4, 36)) // 4 * 4) if heun else 0
+    return 4 * ((7 if heun else 3) - ((4 if heun else 2) * theta + 2 * carry) / rows)
 
 
 PEAK_HBM = 8.0e12
 # Measured HBM bytes per oscillator-step of the streamed mean field (Fig. 4),
 # from profiles/kuramoto_fig4_hbm_counters.md; valid for that kernel source.
-FIG4_TRAFFIC_PER_OSC_STEP = 28.05
-FIG4_TRAFFIC_SOURCE_SHA1 = "82fa5aac87989d0a864b0ddad5c1b282e932dd53"
+FIG4_TRAFFIC_PER_OSC_STEP = 19.05
+FIG4_TRAFFIC_SOURCE_SHA1 = "cfd223b66cae4831c8938704a4ba11f6c9f6c3da"
 
 
 def _source_sha1(*files):
@@ -132,10 +138,10 @@ def _source_sha1(*files):
 # (FETCH_SIZE x 2.00 + WRITE_SIZE x 1.00, copy-calibrated), and its VALU
 # counters per path-step, from profiles/jj_scan_valu_counters.md.  Only valid
 # for the kernel source they were measured on.
-JJ_TRAFFIC_BYTES = (2 * 3547.2 + 6612.1) * 1024
-JJ_TRAFFIC_SOURCE_SHA1 = "ca5065025955cec058718be06875fb2e71ce5666"
-JJ_VALU_COUNTERS = {"valu_instructions_per_path_step": 34.28, "transcendental_per_path_step": 4.00,
-                    "salu_instructions_per_path_step": 8.08, "valu_instructions_per_simd_cycle": 0.262,
+JJ_TRAFFIC_BYTES = (2 * 3840.4 + 6591.3) * 1024
+JJ_TRAFFIC_SOURCE_SHA1 = "387ce42d9fc2404733e6858d53a96eb143023c4f"
+JJ_VALU_COUNTERS = {"valu_instructions_per_path_step": 30.75, "transcendental_per_path_step": 4.00,
+                    "salu_instructions_per_path_step": 2.39, "valu_instructions_per_simd_cycle": 0.245,
                     "source": "profiles/jj_scan_valu_counters.md"}
 
 
@@ -145,10 +151,10 @@ KURA_VALU_COUNTERS = {
     "kuramoto_tiled": ({"valu_instructions_per_pair_term": 3.08, "transcendental_per_pair_term": 1.00,
                         "valu_instructions_per_simd_cycle": 0.187,
                         "source": "profiles/kuramoto_tiled_valu_counters.md"},
-                       ("-- TILED ------", "-- host --"), "99154c35b9150737c63b10052e2fb4d746117639"),
+                       ("-- TILED ------", "-- host --"), "5b16bafa171aac2a85542fbd8240562f672cdc2b"),
     "kuramoto_mf": ({"valu_instructions_per_oscillator_stage": 29.1, "transcendental_per_oscillator_stage": 3.07,
                      "valu_instructions_per_simd_cycle": 0.108, "source": "profiles/kuramoto_meanfield_counters.md"},
-                    ("-- MF ------", "-- MF, two realizations per workgroup --"), "fddd8c97c34c8a31a73975c59e0ff3a61eb17c25"),
+                    ("-- MF ------", "-- MF, two realizations per workgroup --"), "80c252a849e8cc6bd1084f04ece2750536475361"),
 }
 
 
@@ -875,7 +881,8 @@ def bench_fig4(args, sde, torch, dev):
     h = dens.cpu().numpy()[:, :nb] * nb / N
     r = rs.cpu().numpy()[0]
     osc_steps = float(N) * n
-    ops, byts = mfs_ops_per_osc_step(True), mfs_bytes_per_osc_step(True)
+    ops, byts = mfs_ops_per_osc_step(True), mfs_bytes_per_osc_step(
+        True, N, torch.cuda.get_device_properties(0).multi_processor_count)
     hbm = byts * osc_steps / t
     alu = ops * osc_steps / t
     traffic = (FIG4_TRAFFIC_PER_OSC_STEP * osc_steps
