@@ -132,8 +132,8 @@ __global__ void mlp_normalize_kernel(NormArgs A)
 // seed gives the same weights bit for bit as one launch per product did.
 // What bounded that: 31 launches a step, and 64 x 64 tiles staged through LDS
 // in 16-k slices with nothing in flight over a slice (15 TFLOP/s).  Five
-// members of 5-256-256-256-1, 1024 samples: 413 us a step then, 104 now (rows
-// 65, of which the products' MFMAs are 34; gradients 24; update 10).
+// members of 5-256-256-256-1, 1024 samples: 413 us a step then, 100 now (rows
+// 61, of which the products' MFMAs are 34; gradients 24; update 10).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // Operands of a 16 x 16 block (16 rows or output columns by 16 k) of the FP32
@@ -1396,9 +1396,12 @@ int pack_weights(sde_surrogate* s, const TrainArgs& A, hipStream_t st)
 // One step (forward, loss, backward, and Adam where A holds its state).
 int record_step(sde_ctx* ctx, const TrainArgs& A, hipStream_t st)
 {
-    // 16 samples a workgroup until every CU has one, then 32, which halve the
-    // traffic of the weights
-    if ((uint64_t)((A.B + 15) / 16) * A.members <= (uint64_t)ctx->n_cu)
+    // 16 samples a workgroup up to three workgroups a CU, then 32, which halve
+    // the traffic of the weights.  An epoch of 16384 samples, 16 against 32:
+    // five members, batch 1024 (320 workgroups) 1679 against 1737 us, 2048
+    // (640) 1277 against 1421; eight members, 1536 (768) 1789 against 1935,
+    // but 2048 (1024) 1852 against 1778 and 4096 1796 against 1736.
+    if ((uint64_t)((A.B + 15) / 16) * A.members <= 3 * (uint64_t)ctx->n_cu)
         hipLaunchKernelGGL(mlp_rows_kernel<1>, dim3((A.B + 15) / 16, A.members), dim3(kRowsThreads), 0, st, A);
     else
         hipLaunchKernelGGL(mlp_rows_kernel<2>, dim3((A.B + 31) / 32, A.members), dim3(kRowsThreads), 0, st, A);

@@ -86,3 +86,11 @@ def test_loss_curve_of_full_batches(gpu, widths, B):
         np.testing.assert_allclose(got, ref, rtol=1e-4)
     finally:
         sde.sde_surrogate_destroy(s)
+
+
+@pytest.mark.parametrize("widths", [[5, 65, 65, 65, 1], [5, 250, 250, 1]])
+@pytest.mark.parametrize("B", [2448, 2449, 2500, 4100])
+def test_gradients_of_large_batches(gpu, widths, B):
+    """On either side of the batch from which five members take 32 samples a
+    workgroup (on 256 CUs), the last workgroup ragged."""
+    test_gradients(gpu, widths, B)
