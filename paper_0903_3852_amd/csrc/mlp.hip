@@ -858,8 +858,8 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
 // the parts of the step before's GELU, and the weights two blocks ahead.
 // Eight waves of 16 queries fill the registers (256 each); four waves of 32
 // would halve the LDS reads, but a wave alone on its SIMD issues too slowly.
-// 4482 us with FP32 products, 1640 with products and GELU in turn, 1226 us so
-// (214 TFLOP/s of the network's own products); at H = 128 1750 -> 478 us.
+// 4482 us with FP32 products, 1640 with products and GELU in turn, 1059 us so
+// (250 TFLOP/s of the network's own products); at H = 128 1750 -> 433 us.
 // Error against 64 bits 1.3e-7 of the norm, with FP32 products 2.1e-7.
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -928,7 +928,36 @@ struct SplitArgs {
     _Float16* packed; // [members][hidden - 1][Hq / 32 chunks][32 features]...
     uint32_t wpad;    // inputs the kernel is built for, 5 or 8
     float* info;      // [members][split_table]
+    uint64_t first;   // of the launch's queries
+    float* raw;       // null, or [members][n - first] outputs where a workgroup takes one member (blockIdx.y)
 };
+
+// Members' mean and sample standard deviation at `query`, in units of <v>.
+template <typename Out>
+__device__ __forceinline__ void store_prediction(const InferArgs& A, uint64_t query, Out out)
+{
+    const float omega = A.sc.target_over_omega ? A.X[query * A.w0 + 1] : 1.f;
+    float v[8], s = 0.f;
+#pragma unroll
+    for (uint32_t m = 0; m < 8; ++m)
+        if (m < A.members) {
+            v[m] = (A.sc.out_mean + A.sc.out_std * out(m)) * omega;
+            s += v[m];
+        }
+    const float mu = s / (float)A.members;
+    float ss = 0.f;
+#pragma unroll
+    for (uint32_t m = 0; m < 8; ++m)
+        if (m < A.members) ss += (v[m] - mu) * (v[m] - mu);
+    A.mean[query] = mu;
+    A.spread[query] = A.members > 1 ? sqrtf(ss / (float)(A.members - 1)) : 0.f;
+}
+
+__global__ __launch_bounds__(256) void mlp_split_combine_kernel(SplitArgs S)
+{
+    const uint64_t q = (uint64_t)blockIdx.x * 256 + threadIdx.x, n = S.in.n - S.first;
+    if (q < n) store_prediction(S.in, S.first + q, [&](uint32_t m) { return S.raw[m * n + q]; });
+}
 
 // One workgroup per 16 features of a layer (z = member * hidden + layer): row
 // scales and sums, then (l >= 1) the rows as hi and lo halves in the operand
@@ -1012,7 +1041,7 @@ __global__ __launch_bounds__(kSplitThreads) void mlp_split_infer_kernel(SplitArg
     const InferArgs& A = S.in;
     const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u, g = lane >> 4;
     const uint32_t hidden = S.hidden;
-    const uint64_t query = ((uint64_t)blockIdx.x * kSplitWaves + wave) * kSplitQueries + (lane & 15u);
+    const uint64_t query = S.first + ((uint64_t)blockIdx.x * kSplitWaves + wave) * kSplitQueries + (lane & 15u);
     float x[W0], xmax = 0.f;
     {
 #pragma unroll
@@ -1022,9 +1051,10 @@ __global__ __launch_bounds__(kSplitThreads) void mlp_split_infer_kernel(SplitArg
             xmax = fmaxf(xmax, fabsf(x[j]));
         }
     }
+    const uint32_t mem0 = S.raw ? blockIdx.y : 0, mem1 = S.raw ? mem0 + 1 : A.members;
     // the chunk stream: every layer of every member in turn
-    const half8* src = reinterpret_cast<const half8*>(S.packed) + tid;
-    const half8* last = src + ((uint64_t)A.members * (hidden - 1) * KB - 1) * kChunk;
+    const half8* src = reinterpret_cast<const half8*>(S.packed) + (uint64_t)mem0 * (hidden - 1) * KB * kChunk + tid;
+    const half8* last = src + ((uint64_t)(mem1 - mem0) * (hidden - 1) * KB - 1) * kChunk;
     half8 next[kPer];
     auto fetch = [&]() {
 #pragma unroll
@@ -1041,7 +1071,7 @@ __global__ __launch_bounds__(kSplitThreads) void mlp_split_infer_kernel(SplitArg
     fetch();
     put(0);
     fetch();
-    for (uint32_t mem = 0; mem < A.members; ++mem) {
+    for (uint32_t mem = mem0; mem < mem1; ++mem) {
         {   // sent for at once, and past the table's end its last entry again
             const f32x4_t* from = reinterpret_cast<const f32x4_t*>(S.info + (uint64_t)mem * table);
             f32x4_t t[kCopies];
@@ -1197,23 +1227,11 @@ __global__ __launch_bounds__(kSplitThreads) void mlp_split_infer_kernel(SplitArg
         v += __shfl_xor(v, 32, 64);
         if (g == 0) outs[mem][wave * kSplitQueries + lane] = v + info[table - 4];
     }
-    // members' mean and sample standard deviation, in units of <v>
     if (g || query >= A.n) return;
-    const float omega = A.sc.target_over_omega ? A.X[query * A.w0 + 1] : 1.f;
-    float v[8], s = 0.f;
-#pragma unroll
-    for (int m = 0; m < 8; ++m)
-        if ((uint32_t)m < A.members) {
-            v[m] = (A.sc.out_mean + A.sc.out_std * outs[m][wave * kSplitQueries + lane]) * omega;
-            s += v[m];
-        }
-    const float mu = s / (float)A.members;
-    float ss = 0.f;
-#pragma unroll
-    for (int m = 0; m < 8; ++m)
-        if ((uint32_t)m < A.members) ss += (v[m] - mu) * (v[m] - mu);
-    A.mean[query] = mu;
-    A.spread[query] = A.members > 1 ? sqrtf(ss / (float)(A.members - 1)) : 0.f;
+    if (S.raw)
+        S.raw[mem0 * (A.n - S.first) + query - S.first] = outs[mem0][wave * kSplitQueries + lane];
+    else
+        store_prediction(A, query, [&](uint32_t m) { return outs[m][wave * kSplitQueries + lane]; });
 }
 
 // ------------------------------------------------------------ scan glue ---
@@ -1640,8 +1658,8 @@ static int ensure_packed(sde_surrogate* s, size_t need)
 }
 
 // Widths past 64 with products between hidden layers.  Below the line the
-// operands would be padded to 128 columns: 200000 queries at H = 64 420 us on
-// the FP32 products, 478 us padded; at H = 100 (two hidden layers) 304 against
+// operands would be padded to 128 columns: 200000 queries at H = 64 412 us on
+// the FP32 products, 433 us padded; at H = 100 (two hidden layers) 274 against
 // 1060 us.
 static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
 {
@@ -1653,17 +1671,36 @@ static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
     S.wpad = a.w0 <= 5 ? 5 : 8;
     const size_t halves = (size_t)a.members * (S.hidden - 1) * S.Hq * S.Hq * 2;
     const uint32_t table = split_table(S.hidden, S.Hq, S.wpad);
-    if (const int e = ensure_packed(s, halves * sizeof(_Float16) + (size_t)a.members * table * sizeof(float))) return e;
+    // Workgroups past the last full round over the CUs: a workgroup per member
+    // where that takes at most half a round's time (a call of one query 176
+    // -> 47 us, of 200000, 6.1 rounds, 1191 -> 1059).
+    const uint32_t per = kSplitQueries * kSplitWaves;
+    const uint64_t blocks = (a.n + per - 1) / per, n_cu = (uint64_t)ctx->n_cu, tail = blocks % n_cu;
+    const bool by_member = tail && 2 * ((tail * a.members + n_cu - 1) / n_cu) <= a.members;
+    const size_t floats = (size_t)a.members * table, raw = (size_t)a.members * n_cu * per;
+    if (const int e = ensure_packed(s, halves * sizeof(_Float16) + (floats + raw) * sizeof(float))) return e;
     S.packed = reinterpret_cast<_Float16*>(s->packed);
     S.info = reinterpret_cast<float*>(S.packed + halves);
     hipLaunchKernelGGL(mlp_split_pack_kernel, dim3(S.Hq / 16, a.members * S.hidden), dim3(256), 0, st, S);
     SDE_HIP(ctx, hipGetLastError());
     void (*kern)(SplitArgs) = S.Hq == 128 ? (S.wpad == 5 ? mlp_split_infer_kernel<4, 5> : mlp_split_infer_kernel<4, 8>)
                                           : (S.wpad == 5 ? mlp_split_infer_kernel<8, 5> : mlp_split_infer_kernel<8, 8>);
-    const uint32_t per = kSplitQueries * kSplitWaves;
-    hipLaunchKernelGGL(kern, dim3((uint32_t)((a.n + per - 1) / per)), dim3(kSplitThreads),
-                       table * sizeof(float), st, S);
-    SDE_HIP(ctx, hipGetLastError());
+    const size_t lds = table * sizeof(float);
+    const uint64_t full = by_member ? blocks - tail : blocks;
+    if (full) {
+        SplitArgs F = S;
+        F.in.n = std::min<uint64_t>(a.n, full * per);
+        hipLaunchKernelGGL(kern, dim3((uint32_t)full), dim3(kSplitThreads), lds, st, F);
+        SDE_HIP(ctx, hipGetLastError());
+    }
+    if (by_member) {
+        S.first = full * per;
+        S.raw = S.info + floats;
+        hipLaunchKernelGGL(kern, dim3((uint32_t)tail, a.members), dim3(kSplitThreads), lds, st, S);
+        SDE_HIP(ctx, hipGetLastError());
+        hipLaunchKernelGGL(mlp_split_combine_kernel, dim3((uint32_t)((a.n - S.first + 255) / 256)), dim3(256), 0, st, S);
+        SDE_HIP(ctx, hipGetLastError());
+    }
     return SDE_OK;
 }
 

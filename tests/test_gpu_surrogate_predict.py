@@ -106,3 +106,28 @@ def test_query_that_is_no_number(gpu, widths, bad):
         keep = np.ones(200, bool)
         keep[[3, 16, 150]] = False
         assert np.array_equal(a[keep], b[keep])
+
+
+@pytest.mark.parametrize("widths, members", [([5, 70, 70, 1], 5), ([5, 256, 256, 1], 3), ([6, 129, 129, 1], 8),
+                                             ([5, 80, 80, 1], 1), ([5, 80, 80, 1], 2)])
+def test_members_in_workgroups_of_their_own(gpu, widths, members):
+    """Few workgroups, alone or past the last full round over the CUs, take a
+    member each: the same bits as where a workgroup takes them all."""
+    sde, ctx, dev = gpu
+    rng = np.random.default_rng(2)
+    params = [_params(rng, widths) for _ in range(members)]
+    per_round = 128 * torch.cuda.get_device_properties(dev).multi_processor_count
+    X = rng.uniform(1.0, 5.0, (per_round + 128 * 60 + 3, widths[0])).astype(np.float32)
+    scaling = ([3.0] * widths[0], [2.0] * widths[0], 0.3, 1.7, 1)
+    whole = _predict(sde, ctx, dev, params, widths, X[:per_round], scaling)
+    _check([w[-2000:] for w in whole], params, X[per_round - 2000:per_round], *[np.array(v) for v in scaling[:2]], 0.3, 1.7,
+           True)
+    for n in (1, 127, 128, 129, 128 * 25 + 1, 128 * 51, 128 * 64 + 5, 128 * 128, 128 * 129, per_round - 128):
+        part = _predict(sde, ctx, dev, params, widths, X[:n], scaling)
+        assert all(np.array_equal(p, w[:n]) for p, w in zip(part, whole)), n
+    last = _predict(sde, ctx, dev, params, widths, X[-per_round:], scaling)
+    for n in (per_round + 1, per_round + 128 * 32, len(X)):
+        more = _predict(sde, ctx, dev, params, widths, X[:n], scaling)
+        assert all(np.array_equal(m[:per_round], w) for m, w in zip(more, whole)), n
+        at = len(X) - per_round
+        assert all(np.array_equal(m[at:], e[:n - at]) for m, e in zip(more, last)), n
