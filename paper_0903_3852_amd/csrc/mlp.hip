@@ -697,6 +697,34 @@ struct InferArgs {
     sde_surrogate_scaling sc;
 };
 
+// Members' mean and sample standard deviation at `query`, in units of <v>.
+template <typename Out>
+__device__ __forceinline__ void store_prediction(const InferArgs& A, uint64_t query, Out out)
+{
+    const float omega = A.sc.target_over_omega ? A.X[query * A.w0 + 1] : 1.f;
+    float v[8], s = 0.f;
+#pragma unroll
+    for (uint32_t m = 0; m < 8; ++m)
+        if (m < A.members) {
+            v[m] = (A.sc.out_mean + A.sc.out_std * out(m)) * omega;
+            s += v[m];
+        }
+    const float mu = s / (float)A.members;
+    float ss = 0.f;
+#pragma unroll
+    for (uint32_t m = 0; m < 8; ++m)
+        if (m < A.members) ss += (v[m] - mu) * (v[m] - mu);
+    A.mean[query] = mu;
+    A.spread[query] = A.members > 1 ? sqrtf(ss / (float)(A.members - 1)) : 0.f;
+}
+
+// The same from the members' outputs of queries first .., raw[members][n - first].
+__global__ __launch_bounds__(256) void mlp_combine_kernel(InferArgs A, uint64_t first, const float* raw)
+{
+    const uint64_t q = (uint64_t)blockIdx.x * 256 + threadIdx.x, n = A.n - first;
+    if (q < n) store_prediction(A, first + q, [&](uint32_t m) { return raw[m * n + q]; });
+}
+
 // FP32 MFMA forward (v_mfma_f32_16x16x4_f32) in the operand layout of
 // frag32_index.  The hidden weights are packed that way once per call
 // (B(k, c) = W[c][k]); the activations stay in LDS in the same layout, as the
@@ -733,7 +761,8 @@ constexpr uint32_t kInfBlocks = (kSplitMinH - 1) / 16;
 // 5-64-64-64-1 networks 801 us with room for 256 columns, 420 us so.
 constexpr uint32_t kInfMRows = 64;
 
-__global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, const float* packed, uint32_t Hp)
+__global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, const float* packed, uint32_t Hp,
+                                                               float* raw)
 {
     extern __shared__ float smem[];
     float* act = smem;                      // [kInfMRows x Hp] in the operand layout
@@ -749,7 +778,8 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
     }
     __syncthreads();
     const uint32_t hidden = A.n_layers - 2;
-    for (uint32_t mem = 0; mem < A.members; ++mem) {
+    const uint32_t mem0 = raw ? blockIdx.y : 0, mem1 = raw ? mem0 + 1 : A.members;
+    for (uint32_t mem = mem0; mem < mem1; ++mem) {
         const float* prm = A.params + (uint64_t)mem * A.P;
         {   // layer 1 from the normalized features
             const float* W = prm + A.w_off[0];
@@ -813,23 +843,13 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
             __syncthreads();
         }
     }
-    // members' mean and sample standard deviation, in units of <v>
-    if (threadIdx.x < kInfMRows) {
-        const uint64_t gi = r0 + threadIdx.x;
-        if (gi < A.n) {
-            const float scale = A.sc.target_over_omega ? A.X[gi * A.w0 + 1] : 1.f;
-            float v[8], s = 0.f;
-            for (uint32_t m = 0; m < A.members; ++m) {
-                v[m] = (A.sc.out_mean + A.sc.out_std * outs[threadIdx.x * 8 + m]) * scale;
-                s += v[m];
-            }
-            const float mu = s / (float)A.members;
-            float ss = 0.f;
-            for (uint32_t m = 0; m < A.members; ++m) ss += (v[m] - mu) * (v[m] - mu);
-            A.mean[gi] = mu;
-            A.spread[gi] = A.members > 1 ? sqrtf(ss / (float)(A.members - 1)) : 0.f;
-        }
-    }
+    const uint64_t gi = r0 + threadIdx.x;
+    if (threadIdx.x >= kInfMRows || gi >= A.n) return;
+    const float* out = outs + threadIdx.x * 8;
+    if (raw)
+        raw[mem0 * A.n + gi] = out[mem0];
+    else
+        store_prediction(A, gi, [&](uint32_t m) { return out[m]; });
 }
 
 // Wide networks (H > 64, two hidden layers or more): the products on the FP16
@@ -931,33 +951,6 @@ struct SplitArgs {
     uint64_t first;   // of the launch's queries
     float* raw;       // null, or [members][n - first] outputs where a workgroup takes one member (blockIdx.y)
 };
-
-// Members' mean and sample standard deviation at `query`, in units of <v>.
-template <typename Out>
-__device__ __forceinline__ void store_prediction(const InferArgs& A, uint64_t query, Out out)
-{
-    const float omega = A.sc.target_over_omega ? A.X[query * A.w0 + 1] : 1.f;
-    float v[8], s = 0.f;
-#pragma unroll
-    for (uint32_t m = 0; m < 8; ++m)
-        if (m < A.members) {
-            v[m] = (A.sc.out_mean + A.sc.out_std * out(m)) * omega;
-            s += v[m];
-        }
-    const float mu = s / (float)A.members;
-    float ss = 0.f;
-#pragma unroll
-    for (uint32_t m = 0; m < 8; ++m)
-        if (m < A.members) ss += (v[m] - mu) * (v[m] - mu);
-    A.mean[query] = mu;
-    A.spread[query] = A.members > 1 ? sqrtf(ss / (float)(A.members - 1)) : 0.f;
-}
-
-__global__ __launch_bounds__(256) void mlp_split_combine_kernel(SplitArgs S)
-{
-    const uint64_t q = (uint64_t)blockIdx.x * 256 + threadIdx.x, n = S.in.n - S.first;
-    if (q < n) store_prediction(S.in, S.first + q, [&](uint32_t m) { return S.raw[m * n + q]; });
-}
 
 // One workgroup per 16 features of a layer (z = member * hidden + layer): row
 // scales and sums, then (l >= 1) the rows as hi and lo halves in the operand
@@ -1698,7 +1691,8 @@ static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
         S.raw = S.info + floats;
         hipLaunchKernelGGL(kern, dim3((uint32_t)tail, a.members), dim3(kSplitThreads), lds, st, S);
         SDE_HIP(ctx, hipGetLastError());
-        hipLaunchKernelGGL(mlp_split_combine_kernel, dim3((uint32_t)((a.n - S.first + 255) / 256)), dim3(256), 0, st, S);
+        hipLaunchKernelGGL(mlp_combine_kernel, dim3((uint32_t)((a.n - S.first + 255) / 256)), dim3(256), 0, st, a,
+                           S.first, static_cast<const float*>(S.raw));
         SDE_HIP(ctx, hipGetLastError());
     }
     return SDE_OK;
@@ -1727,8 +1721,13 @@ static int predict_impl(sde_surrogate* s, const float* X, uint64_t n, float* mea
     if (a.n_layers >= 3 && a.H >= kSplitMinH) return predict_split(s, a, st);
     // hidden weights into the MFMA operand layout (Hp = H rounded up to 16)
     const uint32_t H = a.H, Hp = (H + 15u) & ~15u, hidden = a.n_layers - 2;
+    // Up to one workgroup a CU: a workgroup per member, several of which share
+    // a CU (five 5-64-64-64-1 networks, one query 94 -> 25 us, 16384 96 -> 45).
+    const uint64_t blocks = (n + kInfMRows - 1) / kInfMRows;
+    const bool by_member = a.members > 1 && blocks <= (uint64_t)ctx->n_cu;
+    const size_t weights = (size_t)s->members * hidden * Hp * Hp, raw = (size_t)s->members * ctx->n_cu * kInfMRows;
+    if (const int e = ensure_packed(s, (weights + raw) * sizeof(float))) return e;
     if (hidden > 0) {
-        if (const int e = ensure_packed(s, (size_t)s->members * hidden * Hp * Hp * sizeof(float))) return e;
         PackArgs pk{};
         pk.params = s->params;
         pk.P = s->P;
@@ -1750,9 +1749,15 @@ static int predict_impl(sde_surrogate* s, const float* X, uint64_t n, float* mea
                                          (int)(kInfMRows * (kInfH + 16) * sizeof(float))));
         attr_set = true;
     }
-    hipLaunchKernelGGL(mlp_infer_mfma_kernel, dim3((uint32_t)((n + kInfMRows - 1) / kInfMRows)), dim3(256), lds, st, a,
-                       static_cast<const float*>(s->packed), Hp);
+    float* members_out = by_member ? s->packed + weights : nullptr;
+    hipLaunchKernelGGL(mlp_infer_mfma_kernel, dim3((uint32_t)blocks, by_member ? a.members : 1), dim3(256), lds, st, a,
+                       static_cast<const float*>(s->packed), Hp, members_out);
     SDE_HIP(ctx, hipGetLastError());
+    if (by_member) {
+        hipLaunchKernelGGL(mlp_combine_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, st, a, (uint64_t)0,
+                           static_cast<const float*>(members_out));
+        SDE_HIP(ctx, hipGetLastError());
+    }
     return SDE_OK;
 }
 

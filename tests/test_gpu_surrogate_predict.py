@@ -109,7 +109,8 @@ def test_query_that_is_no_number(gpu, widths, bad):
 
 
 @pytest.mark.parametrize("widths, members", [([5, 70, 70, 1], 5), ([5, 256, 256, 1], 3), ([6, 129, 129, 1], 8),
-                                             ([5, 80, 80, 1], 1), ([5, 80, 80, 1], 2)])
+                                             ([5, 80, 80, 1], 1), ([5, 80, 80, 1], 2),
+                                             ([5, 64, 64, 1], 5), ([5, 17, 17, 1], 8), ([5, 250, 1], 3)])
 def test_members_in_workgroups_of_their_own(gpu, widths, members):
     """Few workgroups, alone or past the last full round over the CUs, take a
     member each: the same bits as where a workgroup takes them all."""
@@ -122,7 +123,8 @@ def test_members_in_workgroups_of_their_own(gpu, widths, members):
     whole = _predict(sde, ctx, dev, params, widths, X[:per_round], scaling)
     _check([w[-2000:] for w in whole], params, X[per_round - 2000:per_round], *[np.array(v) for v in scaling[:2]], 0.3, 1.7,
            True)
-    for n in (1, 127, 128, 129, 128 * 25 + 1, 128 * 51, 128 * 64 + 5, 128 * 128, 128 * 129, per_round - 128):
+    for n in (1, 127, 128, 129, 128 * 25 + 1, 128 * 51, 128 * 64 + 5, 128 * 128, 128 * 128 + 1, 128 * 129,
+              per_round - 128):
         part = _predict(sde, ctx, dev, params, widths, X[:n], scaling)
         assert all(np.array_equal(p, w[:n]) for p, w in zip(part, whole)), n
     last = _predict(sde, ctx, dev, params, widths, X[-per_round:], scaling)
