@@ -956,7 +956,7 @@ struct MFSArgs {
 };
 
 // Each pass takes kMFSBatch rows of a slice per iteration, with the next
-// batch's loads in flight (unconditional, clamped to the slice).
+// batch's loads in flight (clamped to the slice).
 constexpr int kMFSBatch = 4;
 constexpr uint32_t kMFSLdsRows = 36;  // of 160 KB; the exchange takes 5
 
@@ -1027,14 +1027,16 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
         load(omega, row, omn);
         if (!theta_held) load(th, row, t0n);
         for (; row < end; row += kMFSBatch) {
-            const uint32_t next = min(row + kMFSBatch, end - 1) / kMFSBatch * kMFSBatch, n_left = left(row);
+            const uint32_t next = row + kMFSBatch, n_left = left(row);
 #pragma unroll
             for (int k = 0; k < kMFSBatch; ++k) {
                 om[k] = omn[k];
                 t0[k] = theta_held ? held[(row + k) * kMFSThreads + tid] : t0n[k];
             }
-            load(omega, next, omn);
-            if (!theta_held) load(th, next, t0n);
+            if (next < end) {
+                load(omega, next, omn);
+                if (!theta_held) load(th, next, t0n);
+            }
             __builtin_amdgcn_sched_barrier(0);
             const uint64_t at = (uint64_t)row * kMFSThreads + tid;
 #pragma unroll
@@ -1071,14 +1073,16 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
         if (!carry_held) load(cy, row, cvn);
         if (!theta_held) load(tl, row, ttn);
         for (; row < end; row += kMFSBatch) {
-            const uint32_t next = min(row + kMFSBatch, end - 1) / kMFSBatch * kMFSBatch, n_left = left(row);
+            const uint32_t next = row + kMFSBatch, n_left = left(row);
 #pragma unroll
             for (int k = 0; k < kMFSBatch; ++k) {
                 cv[k] = carry_held ? held_cy[(row + k) * kMFSThreads + tid] : cvn[k];
                 tt[k] = theta_held ? held[(row + k) * kMFSThreads + tid] : ttn[k];
             }
-            if (!carry_held) load(cy, next, cvn);
-            if (!theta_held) load(tl, next, ttn);
+            if (next < end) {
+                if (!carry_held) load(cy, next, cvn);
+                if (!theta_held) load(tl, next, ttn);
+            }
             __builtin_amdgcn_sched_barrier(0);
             const uint64_t at = (uint64_t)row * kMFSThreads + tid;
 #pragma unroll
@@ -1122,8 +1126,9 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
     for (uint32_t row = 0; row < rows; ++row) {
         const uint64_t e = (uint64_t)row * kMFSThreads + tid;
         if (e >= i1 - i0) break;
-        if (row < rows_theta) th[e] = held[row * kMFSThreads + tid];
-        bad |= !isfinite(th[e]);
+        const float t = row < rows_theta ? held[row * kMFSThreads + tid] : th[e];
+        if (row < rows_theta) th[e] = t;
+        bad |= !isfinite(t);
     }
     if (__ballot(bad) != 0 && (tid & (kWave - 1)) == 0) atomicOr(A.flag, 1);
 }
@@ -1449,7 +1454,10 @@ static int run_meanfield_streamed(sde_ctx* ctx, const sde_kuramoto_desc* d, cons
                       : reinterpret_cast<void*>(kuramoto_mfs_kernel<SDE_EULER>);
     int per_cu = 0;
     const size_t most = (size_t)kMFSLdsRows * kMFSThreads * sizeof(float);
-    SDE_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
+    if (!ctx->mfs_lds_set[heun]) {
+        SDE_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
+        ctx->mfs_lds_set[heun] = true;
+    }
     SDE_HIP(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kMFSThreads, most));
     const uint64_t capacity = (uint64_t)std::max(per_cu, 0) * ctx->n_cu;
     if (capacity == 0) return fail(ctx, SDE_ERR_UNSUPPORTED, "streamed mean-field kernel does not fit a CU");

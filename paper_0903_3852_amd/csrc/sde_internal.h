@@ -42,6 +42,7 @@ struct GraphEntry {
 }  // namespace sde
 
 struct sde_ctx {
+    bool mfs_lds_set[2] = {};  // the streamed mean field may use its LDS (Euler-Maruyama, Heun)
     int device = 0;
     int n_cu = 0;
     int xcds = 8;
