@@ -123,7 +123,7 @@ PEAK_HBM = 8.0e12
 # Measured HBM bytes per oscillator-step of the streamed mean field (Fig. 4),
 # from profiles/kuramoto_fig4_hbm_counters.md; valid for that kernel source.
 FIG4_TRAFFIC_PER_OSC_STEP = 19.05
-FIG4_TRAFFIC_SOURCE_SHA1 = "cfd223b66cae4831c8938704a4ba11f6c9f6c3da"
+FIG4_TRAFFIC_SOURCE_SHA1 = "9814ff20b268c564384db2e7e7be9354b653f763"
 
 
 def _source_sha1(*files):
