@@ -50,9 +50,11 @@ struct sde_surrogate {
     size_t work_bytes = 0;
     uint32_t* perm = nullptr;            // device [members][n] sample order of the epoch
     size_t perm_cap = 0;
-    // inference: hidden-layer weights in the FP32 MFMA operand layout
+    // inference: hidden-layer weights in the FP32 MFMA operand layout, and the
+    // members' outputs of a call that gives each a workgroup
     float* packed = nullptr;
     size_t packed_bytes = 0;
+    hipEvent_t raw_done = nullptr;       // the last such call has read them
 };
 
 namespace sde {
@@ -1479,6 +1481,7 @@ void sde_surrogate_destroy(sde_surrogate* s)
     for (void* p : {(void*)s->params, (void*)s->grads, (void*)s->adam_m, (void*)s->adam_v, (void*)s->adam_t,
                     (void*)s->work, (void*)s->perm, (void*)s->packed})
         if (p) (void)hipFree(p);
+    if (s->raw_done) (void)hipEventDestroy(s->raw_done);
     delete s;
 }
 
@@ -1650,6 +1653,34 @@ static int ensure_packed(sde_surrogate* s, size_t need)
     return SDE_OK;
 }
 
+// The members' outputs that mlp_combine_kernel reads are the handle's, one
+// region for every stream: a call waits on its stream for the call before to
+// have read them.  A call that is being captured gives no workgroup to one
+// member, since its replays could be ordered with nothing.
+static bool members_apart(hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
+static int raw_begin(sde_surrogate* s, hipStream_t st)
+{
+    if (s->raw_done)
+        SDE_HIP(s->ctx, hipStreamWaitEvent(st, s->raw_done, 0));
+    else
+        SDE_HIP(s->ctx, hipEventCreateWithFlags(&s->raw_done, hipEventDisableTiming));
+    return SDE_OK;
+}
+
+static int raw_end(sde_surrogate* s, hipStream_t st)
+{
+    SDE_HIP(s->ctx, hipGetLastError());
+    SDE_HIP(s->ctx, hipEventRecord(s->raw_done, st));
+    return SDE_OK;
+}
+
 // Widths past 64 with products between hidden layers.  Below the line the
 // operands would be padded to 128 columns: 200000 queries at H = 64 412 us on
 // the FP32 products, 433 us padded; at H = 100 (two hidden layers) 274 against
@@ -1669,7 +1700,7 @@ static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
     // -> 47 us, of 200000, 6.1 rounds, 1191 -> 1059).
     const uint32_t per = kSplitQueries * kSplitWaves;
     const uint64_t blocks = (a.n + per - 1) / per, n_cu = (uint64_t)ctx->n_cu, tail = blocks % n_cu;
-    const bool by_member = tail && 2 * ((tail * a.members + n_cu - 1) / n_cu) <= a.members;
+    const bool by_member = tail && 2 * ((tail * a.members + n_cu - 1) / n_cu) <= a.members && members_apart(st);
     const size_t floats = (size_t)a.members * table, raw = (size_t)a.members * n_cu * per;
     if (const int e = ensure_packed(s, halves * sizeof(_Float16) + (floats + raw) * sizeof(float))) return e;
     S.packed = reinterpret_cast<_Float16*>(s->packed);
@@ -1689,11 +1720,12 @@ static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
     if (by_member) {
         S.first = full * per;
         S.raw = S.info + floats;
+        if (const int e = raw_begin(s, st)) return e;
         hipLaunchKernelGGL(kern, dim3((uint32_t)tail, a.members), dim3(kSplitThreads), lds, st, S);
         SDE_HIP(ctx, hipGetLastError());
         hipLaunchKernelGGL(mlp_combine_kernel, dim3((uint32_t)((a.n - S.first + 255) / 256)), dim3(256), 0, st, a,
                            S.first, static_cast<const float*>(S.raw));
-        SDE_HIP(ctx, hipGetLastError());
+        if (const int e = raw_end(s, st)) return e;
     }
     return SDE_OK;
 }
@@ -1724,7 +1756,7 @@ static int predict_impl(sde_surrogate* s, const float* X, uint64_t n, float* mea
     // Up to one workgroup a CU: a workgroup per member, several of which share
     // a CU (five 5-64-64-64-1 networks, one query 94 -> 25 us, 16384 96 -> 45).
     const uint64_t blocks = (n + kInfMRows - 1) / kInfMRows;
-    const bool by_member = a.members > 1 && blocks <= (uint64_t)ctx->n_cu;
+    const bool by_member = a.members > 1 && blocks <= (uint64_t)ctx->n_cu && members_apart(st);
     const size_t weights = (size_t)s->members * hidden * Hp * Hp, raw = (size_t)s->members * ctx->n_cu * kInfMRows;
     if (const int e = ensure_packed(s, (weights + raw) * sizeof(float))) return e;
     if (hidden > 0) {
@@ -1750,13 +1782,15 @@ static int predict_impl(sde_surrogate* s, const float* X, uint64_t n, float* mea
         attr_set = true;
     }
     float* members_out = by_member ? s->packed + weights : nullptr;
+    if (by_member)
+        if (const int e = raw_begin(s, st)) return e;
     hipLaunchKernelGGL(mlp_infer_mfma_kernel, dim3((uint32_t)blocks, by_member ? a.members : 1), dim3(256), lds, st, a,
                        static_cast<const float*>(s->packed), Hp, members_out);
     SDE_HIP(ctx, hipGetLastError());
     if (by_member) {
         hipLaunchKernelGGL(mlp_combine_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, st, a, (uint64_t)0,
                            static_cast<const float*>(members_out));
-        SDE_HIP(ctx, hipGetLastError());
+        if (const int e = raw_end(s, st)) return e;
     }
     return SDE_OK;
 }
