@@ -12,8 +12,8 @@
 //
 // Inference is one fused kernel for all members, the hidden weights packed
 // once per call into its operand layout.  Wide networks (mlp_split_infer_kernel):
-// FP16 matrix cores on operands split into two halves, activations in
-// registers from layer to layer, weights streamed through LDS.  Narrow ones
+// the FP32 products from BF16 ones of operands in three exact parts,
+// activations in registers from layer to layer, weights streamed through LDS.  Narrow ones
 // and those with one hidden layer (mlp_infer_mfma_kernel): a workgroup takes
 // 64 queries whose activations stay in LDS in the operand layout of the next
 // layer, each of its 4 waves computes 16 queries x all outputs of a layer on
@@ -854,15 +854,12 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
         store_prediction(A, gi, [&](uint32_t m) { return out[m]; });
 }
 
-// Wide networks (H > 64, two hidden layers or more): the products on the FP16
-// matrix cores, both operands as hi + lo halves (22 bits and the sign between
-// them, what is lost is 2^-24 of a value), hi hi + hi lo + lo hi with FP32
-// accumulators: three products at sixteen times the FP32 matrix rate, and 24
-// roundings per sum where the FP32 chain has 256.  Powers of two keep the halves in range: a
-// weight row is scaled by its largest entry, a query's activations by a bound
-// on them (the layer's largest |b| plus largest row sum of |W| times the
-// query's largest activation of the layer before); both are taken out exactly
-// in the epilogue.
+// Wide networks (H > 64, two hidden layers or more): FP32 products on the BF16
+// matrix cores.  An FP32 operand is the sum of three BF16 parts exactly (24
+// bits in three times eight, and FP32's exponents, so nothing is scaled), and
+// of the nine products of parts the six above 2^-24 of the whole are formed:
+// what is left out is below the rounding of an FP32 product, and a sum of 256
+// has 16 roundings of FP32 accumulators where the FP32 chain has 256.
 //
 // A wave owns 16 queries; every wave of the workgroup goes through all output
 // features, 16 at a time, with the weights (A operand, rows = features)
@@ -870,136 +867,122 @@ __global__ __launch_bounds__(256, 2) void mlp_infer_mfma_kernel(InferArgs A, con
 // The k order of a product is free as long as both operands agree, and it is
 // chosen so that the C values a lane ends with (4 neighbouring features of
 // its query) are the 8 k values its B operand of the next layer needs: the
-// activations never leave the lane's registers.  The output layer is a dot
-// product in the epilogue.
+// activations never leave the lane.  They are kept in FP32 (64 registers at
+// 256 columns) and split as the first 16 features of a layer are multiplied
+// (96 for the parts), when no GELU is due.  The weights go to LDS past the
+// registers (global_load_lds), which have no room for a chunk in flight.
 //
-// Bound by the vector unit's GELU and splitting (33 operations a value, four
-// cycles each: 200000 queries, five 5-256-256-256-1 networks 760 us) next to
-// the products (310 us at the matrix peak) and the LDS reads of the weights
-// (420 us), so the three have to overlap: a step's products are issued between
-// the parts of the step before's GELU, and the weights two blocks ahead.
-// Eight waves of 16 queries fill the registers (256 each); four waves of 32
-// would halve the LDS reads, but a wave alone on its SIMD issues too slowly.
-// 4482 us with FP32 products, 1640 with products and GELU in turn, 1059 us so
-// (250 TFLOP/s of the network's own products); at H = 128 1750 -> 433 us.
-// Error against 64 bits 1.3e-7 of the norm, with FP32 products 2.1e-7.
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+// Bound by the vector unit's GELU and splitting next to the products and the
+// LDS reads of the weights (200000 queries, five 5-256-256-256-1 networks: 620
+// us each at their peaks), so the three have to overlap: a step's products are
+// issued between the parts of the step before's GELU, and the weights two
+// blocks ahead.  Eight waves of 16 queries fill the registers (256 each); four
+// waves of 32 would halve the LDS reads, but a wave alone on its SIMD issues
+// too slowly.  That call: 4482 us with FP32 products, 1420 so (185 TFLOP/s of
+// the network's own products); 5-128-128-128-1 1750 -> 500.  Two FP16 parts and
+// three products took 1090 us, but lost the operands' last bit and the products
+// of the lower parts: 1.3e-7 to 2.2e-7 of the norm off in networks of one to
+// four weights a row, where FP32 is 0.8e-7 to 1.5e-7 and this 0.7e-7 to 1.2e-7
+// (dense rows: 2.0e-7, 4.3e-7, 1.7e-7).
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 constexpr uint32_t kSplitQueries = 16;  // per wave
 constexpr uint32_t kSplitWaves = 8;
 constexpr uint32_t kSplitThreads = kSplitWaves * kWave;
+constexpr uint32_t kSplitParts = 3;
 
-// GELU(z) = max(z, 0) - t q(t) with t = |z|, q(t) = erfc(t / sqrt 2) / 2 =
-// exp(-t^2 / 2) R(t); R as a polynomial in u = 1 / (1 + 0.3 t) (Chebyshev
-// fit, 1.1e-7 relative).  Against 64 bits over |z| <= 6: 2.4e-7 at the most,
-// 5.0e-8 rms (z (1 + erff) / 2: 4.5e-7, 6.6e-8), and no cancellation for
-// negative z.
-// In four parts, so that a caller can put matrix instructions between them.
+// Two values to their three parts, pairs in a register.
+__device__ __forceinline__ void split_pair(float a0, float a1, uint32_t (&part)[kSplitParts])
+{
+    f32x2_t r = {a0, a1};
+#pragma unroll
+    for (uint32_t i = 0; i < kSplitParts; ++i) {
+        part[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2_t));
+        r[0] -= __uint_as_float(part[i] << 16);  // exact
+        r[1] -= __uint_as_float(part[i] & 0xffff0000u);
+    }
+}
+
+// GELU(z), in four parts so that a caller can put matrix instructions between
+// them.  |z| < 1: z / 2 + z^2 P(z^2), P = (Phi(z) - 1/2) / z.  From 1 on:
+// max(z, 0) - t q(t) with t = |z|, q(t) = erfc(t / sqrt 2) / 2 =
+// exp(-t^2 / 2) R(t), R a polynomial in u = 1 / (1 + 0.3 t); no cancellation
+// for negative z.  Minimax fits, P to 2.6e-10, t q to 4.4e-9 of its size.
+// Rounded to FP32 the error against 64 bits is below that of z (1 + erff) / 2
+// over every range of z (0.5 <= z < 1: 1.8e-8 rms against 2.3e-8, 1 to 2:
+// 3.4e-8 against 4.8e-8, 3 to 6: 1.1e-7 against 1.4e-7).
 struct Gelu {
-    float z, u, e, r;
+    float z, h, u, e, r, p;
     __device__ __forceinline__ void begin(float x)
     {
         z = x;
+        h = z * z;
         u = __builtin_amdgcn_rcpf(fmaf(fabsf(z), 0.3f, 1.f));
-        e = __builtin_amdgcn_exp2f(z * z * -0.72134752044448170f);
+        e = __builtin_amdgcn_exp2f(h * -0.72134752044448170f);
     }
     __device__ __forceinline__ void first()
     {
-        r = fmaf(0x1.35f336p-5f, u, -0x1.55841ep-3f);
-        r = fmaf(r, u, 0x1.cb1a38p-3f);
-        r = fmaf(r, u, -0x1.26b58cp-4f);
-        r = fmaf(r, u, 0x1.1e4c54p-3f);
+        r = fmaf(-0x1.757d7ep-4f, u, 0x1.0b8df4p-2f);
+        r = fmaf(r, u, -0x1.31abb8p-4f);
+        r = fmaf(r, u, 0x1.735f5cp-3f);
+        r = fmaf(r, u, 0x1.9dfa2p-4f);
+        r = fmaf(r, u, 0x1.f4b1c4p-4f);
     }
     __device__ __forceinline__ void second()
     {
-        r = fmaf(r, u, 0x1.87e77ap-4f);
-        r = fmaf(r, u, 0x1.f283fcp-4f);
-        r = fmaf(r, u, 0x1.e98550p-4f);
-        r = fmaf(r, u, 0x1.957c6ep-18f);
+        r = fmaf(r, u, -0x1.2f7cfp-13f);
+        p = fmaf(-0x1.012f18p-17f, h, 0x1.dc1b46p-14f);
+        p = fmaf(p, h, -0x1.36fecep-10f);
+        p = fmaf(p, h, 0x1.46ce5ep-7f);
+        p = fmaf(p, h, -0x1.105832p-4f);
+        p = fmaf(p, h, 0x1.988454p-2f);
     }
     __device__ __forceinline__ float end() const
     {
-        return fmaf(-fabsf(z), e * r, __builtin_elementwise_maximum(z, 0.f));  // fmaxf would drop a NaN
+        const float tail = fmaf(-fabsf(z), e * r, __builtin_elementwise_maximum(z, 0.f));  // fmaxf would drop a NaN
+        return fabsf(z) < 1.f ? fmaf(h, p, 0.5f * z) : tail;
     }
 };
 
-// Largest power of two s = 2^k with s * bound < 2^15 (halves reach 2^16), k
-// limited so that s and 1 / s are normal floats.
-__device__ __forceinline__ float half_scale(float bound)
-{
-    const int e = (int)(__float_as_uint(fminf(bound, 3.4e38f)) >> 23) - 127;  // bound < 2^(e + 1)
-    const int k = min(max(14 - e, -110), 110);
-    return __uint_as_float((uint32_t)(127 + k) << 23);
-}
-
-// A member's table: per layer l < hidden four rows of Hq, bias, 1 / weight
-// scale, weight of the output layer (zero except in the last hidden layer),
-// and per 16 features the largest |bias| (from 0) and sum of |W| (from 16);
-// then the first layer's weights [Hq][wpad] and the output layer's bias.
-constexpr uint32_t kInfoRows = 4;
+// A member's table, rows of Hq: the biases of each layer l < hidden, the
+// output layer's weights, the first layer's weights [Hq][wpad]; then the
+// output layer's bias.
 __host__ __device__ constexpr uint32_t split_table(uint32_t hidden, uint32_t Hq, uint32_t wpad)
 {
-    return (hidden * kInfoRows + wpad) * Hq + 4;
+    return (hidden + 1 + wpad) * Hq + 4;
 }
 
 struct SplitArgs {
     InferArgs in;
     uint32_t Hq;      // H rounded up to 128 or 256
     uint32_t hidden;
-    _Float16* packed; // [members][hidden - 1][Hq / 32 chunks][32 features]...
+    __bf16* packed;   // [members][hidden - 1][Hq / 16 features][Hq / 32 k][3 parts][64 lanes][8]
     uint32_t wpad;    // inputs the kernel is built for, 5 or 8
     float* info;      // [members][split_table]
     uint64_t first;   // of the launch's queries
     float* raw;       // null, or [members][n - first] outputs where a workgroup takes one member (blockIdx.y)
 };
 
-// One workgroup per 16 features of a layer (z = member * hidden + layer): row
-// scales and sums, then (l >= 1) the rows as hi and lo halves in the operand
-// layout: per 32 k two runs of 1 KB (hi, lo), lane i + 16 g holding feature i,
-// k = 32 kb + 16 (s / 4) + 4 g + s % 4 for its halves s = 0 .. 7.
+// One workgroup per 16 features of a layer (z = member * hidden + layer): the
+// table's entries, then (l >= 1) the rows' parts in the operand layout: per
+// 32 k three runs of 1 KB, lane i + 16 g holding feature i,
+// k = 32 kb + 16 (s / 4) + 4 g + s % 4 for its s = 0 .. 7.
 __global__ __launch_bounds__(256) void mlp_split_pack_kernel(SplitArgs A)
 {
-    __shared__ float scale[16], largest[2][16];
     const uint32_t mem = blockIdx.y / A.hidden, l = blockIdx.y % A.hidden, ob = blockIdx.x;
     const uint32_t H = A.in.H, K = l ? H : A.in.w0;
     const float* prm = A.in.params + mem * A.in.P;
     const float* W = prm + A.in.w_off[l];
     float* table = A.info + (uint64_t)mem * split_table(A.hidden, A.Hq, A.wpad);
-    float* rows = table + l * kInfoRows * A.Hq;
-    {   // 16 lanes a feature
-        const uint32_t i = threadIdx.x >> 4, o = ob * 16 + i;
-        float mx = 0.f, sum = 0.f;
-        if (o < H)
-            for (uint32_t k = threadIdx.x & 15u; k < K; k += 16) {
-                const float w = fabsf(W[(uint64_t)o * K + k]);
-                mx = fmaxf(mx, w);
-                sum += w;
-            }
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) {
-            mx = fmaxf(mx, __shfl_xor(mx, off, 16));
-            sum += __shfl_xor(sum, off, 16);
-        }
-        if ((threadIdx.x & 15u) == 0) {
-            const float s = mx > 0.f ? half_scale(mx) : 1.f;
-            scale[i] = s;
-            const float bias = o < H ? prm[A.in.b_off[l] + o] : 0.f;
-            rows[o] = bias;
-            rows[A.Hq + o] = 1.f / s;
-            rows[2 * A.Hq + o] = o < H && l + 1 == A.hidden ? prm[A.in.w_off[A.hidden] + o] : 0.f;
-            largest[0][i] = fabsf(bias);
-            largest[1][i] = sum * 1.0001f;  // its own roundings
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        float m = 0.f;
-        for (int i = 0; i < 16; ++i) m = fmaxf(m, largest[threadIdx.x][i]);
-        rows[3 * A.Hq + 16 * threadIdx.x + ob] = m;
+    if (threadIdx.x < 16) {
+        const uint32_t o = ob * 16 + threadIdx.x;
+        table[l * A.Hq + o] = o < H ? prm[A.in.b_off[l] + o] : 0.f;
+        if (l == 0) table[A.hidden * A.Hq + o] = o < H ? prm[A.in.w_off[A.hidden] + o] : 0.f;
     }
     if (l == 0) {
-        float* w_in = table + A.hidden * kInfoRows * A.Hq;
+        float* w_in = table + (A.hidden + 1) * A.Hq;
         for (uint32_t e = threadIdx.x; e < 16 * A.wpad; e += 256) {
             const uint32_t o = ob * 16 + e / A.wpad, j = e % A.wpad;
             w_in[ob * 16 * A.wpad + e] = o < H && j < K ? W[(uint64_t)o * K + j] : 0.f;
@@ -1008,19 +991,22 @@ __global__ __launch_bounds__(256) void mlp_split_pack_kernel(SplitArgs A)
         return;
     }
     const uint32_t KB = A.Hq / 32;
-    _Float16* out = A.packed + ((uint64_t)(mem * (A.hidden - 1) + l - 1) * (A.Hq / 16) + ob) * KB * 1024;
+    u32x4_t* out = reinterpret_cast<u32x4_t*>(A.packed) +
+                   ((uint64_t)(mem * (A.hidden - 1) + l - 1) * (A.Hq / 16) + ob) * KB * kSplitParts * 64;
     for (uint32_t e = threadIdx.x; e < KB * 64; e += 256) {
-        const uint32_t kb = e >> 6, lane = e & 63u, i = lane & 15u, g = lane >> 4, o = ob * 16 + i;
-        half8 hi, lo;
+        const uint32_t kb = e >> 6, lane = e & 63u, g = lane >> 4, o = ob * 16 + (lane & 15u);
+        u32x4_t x[kSplitParts];
 #pragma unroll
-        for (int sl = 0; sl < 8; ++sl) {
+        for (int sl = 0; sl < 8; sl += 2) {
             const uint32_t k = kb * 32 + 16 * (sl >> 2) + 4 * g + (sl & 3);
-            const float x = o < H && k < H ? W[(uint64_t)o * H + k] * scale[i] : 0.f;
-            hi[sl] = (_Float16)x;
-            lo[sl] = (_Float16)(x - (float)hi[sl]);
+            uint32_t part[kSplitParts];
+            split_pair(o < H && k < H ? W[(uint64_t)o * H + k] : 0.f, o < H && k + 1 < H ? W[(uint64_t)o * H + k + 1] : 0.f,
+                       part);
+#pragma unroll
+            for (uint32_t i = 0; i < kSplitParts; ++i) x[i][sl >> 1] = part[i];
         }
-        reinterpret_cast<half8*>(out)[(2 * kb) * 64 + lane] = hi;
-        reinterpret_cast<half8*>(out)[(2 * kb + 1) * 64 + lane] = lo;
+#pragma unroll
+        for (uint32_t i = 0; i < kSplitParts; ++i) out[(kb * kSplitParts + i) * 64 + lane] = x[i];
     }
 }
 
@@ -1028,44 +1014,39 @@ template <int KB, int W0>
 __global__ __launch_bounds__(kSplitThreads) void mlp_split_infer_kernel(SplitArgs S)
 {
     constexpr uint32_t HQ = 32 * KB;
-    constexpr uint32_t kChunk = 2 * KB * 2 * 64;        // half8 per chunk of 32 features
-    constexpr uint32_t kPer = kChunk / kSplitThreads;             // of them per thread
-    __shared__ half8 ring[2][kChunk];
+    constexpr uint32_t kChunk = 2 * KB * kSplitParts * 64;  // 16-byte operands per chunk of 32 features
+    constexpr uint32_t kPer = kChunk / kSplitThreads;       // of them per thread
+    // two arrays, so that the reads of one do not wait for the loads into the other
+    __shared__ u32x4_t ring0[kChunk], ring1[kChunk];
     __shared__ float outs[8][kSplitWaves * kSplitQueries];        // the members' outputs
     extern __shared__ __attribute__((aligned(16))) float info[];  // the member's table
     const InferArgs& A = S.in;
-    const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63u, g = lane >> 4;
+    const uint32_t tid = threadIdx.x, wave = uniform_u32(tid >> 6), lane = tid & 63u, g = lane >> 4;
     const uint32_t hidden = S.hidden;
     const uint64_t query = S.first + ((uint64_t)blockIdx.x * kSplitWaves + wave) * kSplitQueries + (lane & 15u);
-    float x[W0], xmax = 0.f;
-    {
+    float x[W0];
 #pragma unroll
-        for (int j = 0; j < W0; ++j) {
-            const bool ok = query < A.n && (uint32_t)j < A.w0;
-            x[j] = ok ? (A.X[query * A.w0 + j] - A.sc.in_center[j]) / A.sc.in_scale[j] : 0.f;
-            xmax = fmaxf(xmax, fabsf(x[j]));
-        }
+    for (int j = 0; j < W0; ++j) {
+        const bool ok = query < A.n && (uint32_t)j < A.w0;
+        x[j] = ok ? (A.X[query * A.w0 + j] - A.sc.in_center[j]) / A.sc.in_scale[j] : 0.f;
     }
     const uint32_t mem0 = S.raw ? blockIdx.y : 0, mem1 = S.raw ? mem0 + 1 : A.members;
     // the chunk stream: every layer of every member in turn
-    const half8* src = reinterpret_cast<const half8*>(S.packed) + (uint64_t)mem0 * (hidden - 1) * KB * kChunk + tid;
-    const half8* last = src + ((uint64_t)(mem1 - mem0) * (hidden - 1) * KB - 1) * kChunk;
-    half8 next[kPer];
-    auto fetch = [&]() {
+    const u32x4_t* src = reinterpret_cast<const u32x4_t*>(S.packed) + (uint64_t)mem0 * (hidden - 1) * KB * kChunk;
+    const u32x4_t* last = src + ((uint64_t)(mem1 - mem0) * (hidden - 1) * KB - 1) * kChunk;
+    auto fetch = [&](u32x4_t* ring) {  // the next chunk, past the end the last one again
 #pragma unroll
-        for (uint32_t i = 0; i < kPer; ++i) next[i] = src[i * kSplitThreads];
+        for (uint32_t i = 0; i < kPer; ++i)
+            __builtin_amdgcn_global_load_lds(static_cast<const void*>(src + i * kSplitThreads + tid),
+                                             (void __attribute__((address_space(3)))*)(ring + i * kSplitThreads + wave * 64),
+                                             16, 0, 0);
         src = src < last ? src + kChunk : last;
     };
-    auto put = [&](uint32_t buf) {
-#pragma unroll
-        for (uint32_t i = 0; i < kPer; ++i) ring[buf][i * kSplitThreads + tid] = next[i];
-    };
     const uint32_t table = split_table(hidden, HQ, W0);
-    const float* w_in = info + hidden * kInfoRows * HQ;
+    const float* w_out = info + hidden * HQ;
+    const float* w_in = w_out + HQ;
     constexpr uint32_t kCopies = (split_table(kMaxLayers - 1, HQ, W0) / 4 + kSplitThreads - 1) / kSplitThreads;
-    fetch();
-    put(0);
-    fetch();
+    fetch(ring0);
     for (uint32_t mem = mem0; mem < mem1; ++mem) {
         {   // sent for at once, and past the table's end its last entry again
             const f32x4_t* from = reinterpret_cast<const f32x4_t*>(S.info + (uint64_t)mem * table);
@@ -1077,150 +1058,124 @@ __global__ __launch_bounds__(kSplitThreads) void mlp_split_infer_kernel(SplitArg
             for (uint32_t i = 0; i < kCopies; ++i)
                 if (i * kSplitThreads + tid < table / 4) reinterpret_cast<f32x4_t*>(info)[i * kSplitThreads + tid] = t[i];
         }
+        __builtin_amdgcn_s_waitcnt(0);  // the first chunk has landed
         __syncthreads();
-        // the layer's largest |bias| and row sum
-        auto layer_max = [&](uint32_t l, float& bmax, float& wmax) {
-            const f32x4_t* p = reinterpret_cast<const f32x4_t*>(info + (l * kInfoRows + 3) * HQ);
-            bmax = 0.f;
-            wmax = 0.f;
+        float c[2 * KB][4];             // activations: features 16 s + 4 g + q of the query
 #pragma unroll
-            for (uint32_t i = 0; i < HQ / 64; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    bmax = fmaxf(bmax, p[i][j]);
-                    wmax = fmaxf(wmax, p[4 + i][j]);
-                }
-        };
-        u32x4_t bh[KB], bl[KB], ch[KB], cl[KB];  // halves in pairs
-        float top = 0.f, scale, y = 0.f;
-        {
-            float bmax, wmax;
-            layer_max(0, bmax, wmax);
-            scale = half_scale(fmaf(wmax, xmax, bmax) * 1.001f);
-        }
-        // activations 2 i and 2 i + 1 of the four of 16 features s
-        auto keep = [&](int s, int i, float a0, float a1, const f32x4_t& wo) {
-            half2_t hi, lo;
-            top = fmaxf(fmaxf(top, fabsf(a0)), fabsf(a1));
-            y = fmaf(a0, wo[2 * i], y);
-            y = fmaf(a1, wo[2 * i + 1], y);
-            hi[0] = (_Float16)(a0 * scale);
-            hi[1] = (_Float16)(a1 * scale);
-            lo[0] = (_Float16)fmaf(a0, scale, -(float)hi[0]);
-            lo[1] = (_Float16)fmaf(a1, scale, -(float)hi[1]);
-            ch[s >> 1][2 * (s & 1) + i] = __builtin_bit_cast(uint32_t, hi);
-            cl[s >> 1][2 * (s & 1) + i] = __builtin_bit_cast(uint32_t, lo);
-            // operands in four neighbouring registers, here and now: the
-            // compiler would carry every half in a register of its own
-            if ((s & 1) && i) asm("" : "+v"(ch[s >> 1]), "+v"(cl[s >> 1]));
-        };
-        auto operand = [](const u32x4_t& x) { return __builtin_bit_cast(half8, x); };
-#pragma unroll
-        for (int o = 0; o < 2 * KB; ++o) {
-            const uint32_t f0 = o * 16 + 4 * g;
+        for (int s = 0; s < 2 * KB; ++s) {
+            const uint32_t f0 = s * 16 + 4 * g;
             const f32x4_t bias = *reinterpret_cast<const f32x4_t*>(info + f0);
-            const f32x4_t wo = *reinterpret_cast<const f32x4_t*>(info + 2 * HQ + f0);
-            Gelu a[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float z = bias[q];
 #pragma unroll
                 for (int j = 0; j < W0; ++j) z = fmaf(w_in[(f0 + q) * W0 + j], x[j], z);
-                a[q].begin(z);
-                a[q].first();
-                a[q].second();
+                Gelu a;
+                a.begin(z);
+                a.first();
+                a.second();
+                c[s][q] = a.end();
             }
-            keep(o, 0, a[0].end(), a[1].end(), wo);
-            keep(o, 1, a[2].end(), a[3].end(), wo);
             // without these the compiler sends for several blocks' operands at
             // once and spills the activations
             __builtin_amdgcn_sched_barrier(0);
         }
         for (uint32_t l = 1; l < hidden; ++l) {
-            const float* inl = info + l * kInfoRows * HQ;
-            float bmax, wmax;
-            layer_max(l, bmax, wmax);
-            float m = fmaxf(top, __shfl_xor(top, 16, 64));
-            m = fmaxf(m, __shfl_xor(m, 32, 64));
-            const float inv = __uint_as_float(0x7f000000u - __float_as_uint(scale));  // 1 / scale, a power of two
-            scale = half_scale(fmaf(wmax, m, bmax) * 1.001f);
-            top = 0.f;
+            const float* bias_l = info + l * HQ;
+            u32x4_t b[KB][kSplitParts];  // the activations' parts, in pairs
+            auto split = [&](int k) {
 #pragma unroll
-            for (int k = 0; k < KB; ++k) {
-                bh[k] = ch[k];
-                bl[k] = cl[k];
-            }
-            // 16 features a step, 32 k a block of 3 products; between the
-            // products of a step, a part at a time, the vector unit makes
-            // operands of the results of the step before
-            f32x4_t prev[2], bias, unw, wo;
-            Gelu z[2];
-            auto tables = [&](int s) {
-                const uint32_t f0 = s * 16 + 4 * g;
-                bias = *reinterpret_cast<const f32x4_t*>(inl + f0);
-                unw = *reinterpret_cast<const f32x4_t*>(inl + HQ + f0);
-                wo = *reinterpret_cast<const f32x4_t*>(inl + 2 * HQ + f0);
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t part[kSplitParts];
+                    split_pair(c[2 * k + (i >> 1)][2 * (i & 1)], c[2 * k + (i >> 1)][2 * (i & 1) + 1], part);
+#pragma unroll
+                    for (uint32_t j = 0; j < kSplitParts; ++j) b[k][j][i] = part[j];
+                }
+                // operands in four neighbouring registers, here and now
+                asm("" : "+v"(b[k][0]), "+v"(b[k][1]), "+v"(b[k][2]));
             };
+            auto operand = [](const u32x4_t& v) { return __builtin_bit_cast(bf16x8_t, v); };
+            // 16 features a step, 32 k a block of 6 products; between the
+            // products of a step, a part at a time, the vector unit makes
+            // activations of the results of the step before, or in the first
+            // step splits the next block's operands
+            f32x4_t prev[2], bias;
+            Gelu z[2];
+            auto tables = [&](int s) { bias = *reinterpret_cast<const f32x4_t*>(bias_l + s * 16 + 4 * g); };
             auto part = [&](int s, int n) {  // of eight
                 const int i = n >> 2;        // which two of the four values
-                if ((n & 3) == 0)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        z[j].begin(fmaf((prev[0][2 * i + j] + prev[1][2 * i + j]) * inv, unw[2 * i + j], bias[2 * i + j]));
-                else if ((n & 3) == 1)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) z[j].first();
-                else if ((n & 3) == 2)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) z[j].second();
-                else
-                    keep(s, i, z[0].end(), z[1].end(), wo);
-            };
-#pragma unroll
-            for (int p = 0; p < KB; ++p) {
-                const half8* w = ring[p & 1] + lane;
-                half8 hi[2], lo[2];  // the next two blocks of weights
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    hi[j] = w[2 * j * 64];
-                    lo[j] = w[(2 * j + 1) * 64];
+                    const int q = 2 * i + j;
+                    if ((n & 3) == 0)
+                        z[j].begin(prev[0][q] + prev[1][q] + bias[q]);
+                    else if ((n & 3) == 1)
+                        z[j].first();
+                    else if ((n & 3) == 2)
+                        z[j].second();
+                    else
+                        c[s][q] = z[j].end();
                 }
-                f32x4_t acc[2];
+            };
+            split(0);
 #pragma unroll
-                for (int b = 0; b < 2 * KB; ++b) {
-                    const int k = b % KB, s = 2 * p + b / KB;
+            for (int p = 0; p < KB; ++p) {
+                fetch(p & 1 ? ring0 : ring1);  // at a member's end the next member's first
+                const u32x4_t* w = (p & 1 ? ring1 : ring0) + lane;
+                u32x4_t a[2][kSplitParts];     // the next two blocks of weights
+                auto weights = [&](int blk) {
+#pragma unroll
+                    for (uint32_t i = 0; i < kSplitParts; ++i) a[blk & 1][i] = w[(blk * kSplitParts + i) * 64];
+                };
+                weights(0);
+                weights(1);
+                f32x4_t acc[2];  // of the largest products, and of the others
+#pragma unroll
+                for (int blk = 0; blk < 2 * KB; ++blk) {
+                    const int k = blk % KB, s = 2 * p + blk / KB;
                     if (k == 0) {
                         acc[0] = acc[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
                         if (s > 0) tables(s - 1);
                     }
-                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[b & 1], operand(bl[k]), acc[1], 0, 0, 0);
-                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[b & 1], operand(bh[k]), acc[0], 0, 0, 0);
-                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo[b & 1], operand(bh[k]), acc[1], 0, 0, 0);
-                    if (b + 2 < 2 * KB) {
-                        hi[b & 1] = w[2 * (b + 2) * 64];
-                        lo[b & 1] = w[(2 * (b + 2) + 1) * 64];
-                    }
-                    if (s > 0)
+                    auto product = [&](int to, int i, int j) {
+                        acc[to] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(operand(a[blk & 1][i]), operand(b[k][j]), acc[to],
+                                                                          0, 0, 0);
+                    };
+                    product(1, 1, 1);
+                    product(0, 0, 0);
+                    product(1, 2, 0);
+                    product(1, 0, 2);
+                    product(1, 1, 0);
+                    product(1, 0, 1);
+                    if (blk + 2 < 2 * KB) weights(blk + 2);
+                    if (s > 0) {
 #pragma unroll
                         for (int n = 0; n < 8 / KB; ++n) part(s - 1, k * (8 / KB) + n);
+                    } else if (k + 1 < KB)
+                        split(k + 1);
                     __builtin_amdgcn_sched_barrier(0);
                     if (k == KB - 1) {
                         prev[0] = acc[0];
                         prev[1] = acc[1];
                     }
                 }
-                // the next chunk, at a member's end the next member's first
-                put((p & 1) ^ 1);
-                fetch();
+                __builtin_amdgcn_s_waitcnt(0);  // the next chunk has landed
                 __syncthreads();
             }
             tables(2 * KB - 1);
 #pragma unroll
             for (int n = 0; n < 8; ++n) part(2 * KB - 1, n);
         }
-        float v = y + __shfl_xor(y, 16, 64);
-        v += __shfl_xor(v, 32, 64);
-        if (g == 0) outs[mem][wave * kSplitQueries + lane] = v + info[table - 4];
+        float y = 0.f;
+#pragma unroll
+        for (int s = 0; s < 2 * KB; ++s) {
+            const f32x4_t wo = *reinterpret_cast<const f32x4_t*>(w_out + s * 16 + 4 * g);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y = fmaf(c[s][q], wo[q], y);
+        }
+        y += __shfl_xor(y, 16, 64);
+        y += __shfl_xor(y, 32, 64);
+        if (g == 0) outs[mem][wave * kSplitQueries + lane] = y + info[table - 4];
     }
     if (g || query >= A.n) return;
     if (S.raw)
@@ -1682,9 +1637,9 @@ static int raw_end(sde_surrogate* s, hipStream_t st)
 }
 
 // Widths past 64 with products between hidden layers.  Below the line the
-// operands would be padded to 128 columns: 200000 queries at H = 64 412 us on
-// the FP32 products, 433 us padded; at H = 100 (two hidden layers) 274 against
-// 1060 us.
+// operands would be padded to 128 columns: 200000 queries of five networks with
+// three hidden layers take 420 us at H = 64 on the FP32 products, 483 at H = 65
+// here; at H = 100 (two hidden layers) 310 us here, 1060 there.
 static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
 {
     sde_ctx* ctx = s->ctx;
@@ -1693,18 +1648,18 @@ static int predict_split(sde_surrogate* s, const InferArgs& a, hipStream_t st)
     S.hidden = a.n_layers - 1;
     S.Hq = a.H <= 128 ? 128 : 256;
     S.wpad = a.w0 <= 5 ? 5 : 8;
-    const size_t halves = (size_t)a.members * (S.hidden - 1) * S.Hq * S.Hq * 2;
+    const size_t parts = (size_t)a.members * (S.hidden - 1) * S.Hq * S.Hq * kSplitParts;
     const uint32_t table = split_table(S.hidden, S.Hq, S.wpad);
     // Workgroups past the last full round over the CUs: a workgroup per member
-    // where that takes at most half a round's time (a call of one query 176
-    // -> 47 us, of 200000, 6.1 rounds, 1191 -> 1059).
+    // where that takes at most half a round's time (a call of one query 204
+    // -> 53 us, of 200000, 6.1 rounds, 1565 -> 1422).
     const uint32_t per = kSplitQueries * kSplitWaves;
     const uint64_t blocks = (a.n + per - 1) / per, n_cu = (uint64_t)ctx->n_cu, tail = blocks % n_cu;
     const bool by_member = tail && 2 * ((tail * a.members + n_cu - 1) / n_cu) <= a.members && members_apart(st);
     const size_t floats = (size_t)a.members * table, raw = (size_t)a.members * n_cu * per;
-    if (const int e = ensure_packed(s, halves * sizeof(_Float16) + (floats + raw) * sizeof(float))) return e;
-    S.packed = reinterpret_cast<_Float16*>(s->packed);
-    S.info = reinterpret_cast<float*>(S.packed + halves);
+    if (const int e = ensure_packed(s, parts * sizeof(__bf16) + (floats + raw) * sizeof(float))) return e;
+    S.packed = reinterpret_cast<__bf16*>(s->packed);
+    S.info = reinterpret_cast<float*>(S.packed + parts);
     hipLaunchKernelGGL(mlp_split_pack_kernel, dim3(S.Hq / 16, a.members * S.hidden), dim3(256), 0, st, S);
     SDE_HIP(ctx, hipGetLastError());
     void (*kern)(SplitArgs) = S.Hq == 128 ? (S.wpad == 5 ? mlp_split_infer_kernel<4, 5> : mlp_split_infer_kernel<4, 8>)
