@@ -409,6 +409,7 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, c
     const uint64_t n_end = A.step0 + P.n_steps;
     uint64_t n = A.step0;
     uint32_t kk = (uint32_t)(n % P.S);               // drive phase index of step n
+    const uint32_t kk4 = P.S < 4 ? 4 % P.S : 4u;     // what a block moves it by
     // steps until the next multiple of M, kept from the window's start on (no
     // sum is open before it, so folds there would add nothing)
     uint32_t to_fold = 0;
@@ -420,7 +421,8 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, c
     };
     // recording: rc = n mod rec_every; row r holds the state after the
     // (r + 1)-th multiple of rec_every past step0
-    uint32_t rc = A.rec ? (uint32_t)(n % A.rec_every) : 0u;
+    const bool recording = sizeof(R) == 4 && A.rec;  // FP32 only
+    uint32_t rc = recording ? (uint32_t)(n % A.rec_every) : 0u;
     uint64_t row = 0;
 
     auto fold = [&]() {
@@ -448,14 +450,19 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, c
             if (live[k]) out[pid[k]] = wd[k];
         ++row;
     };
-    // `count` whole 4-step blocks with nothing but steps in them, U at a time
-    auto run_some = [&](auto in_window, auto unroll, uint32_t iterations, uint32_t blk) {
+    // `count` whole 4-step blocks, U at a time, outside the window, in it, or
+    // (kTick) in it with folds wherever they fall.  A tick has no branch; it is
+    // for the launch whose step chain has the SIMD to itself (in the other one
+    // it would pay by the instruction).
+    enum { kPlain, kWindow, kTick };
+    auto run_some = [&](auto mode, auto unroll, uint32_t iterations, uint32_t blk) {
+        constexpr int kMode = decltype(mode)::value;
         constexpr uint32_t U = decltype(unroll)::value;
         for (uint32_t i = 0; i < iterations; ++i, blk += U) {
             R g[U][PPT][4], e[U][5];
             src.take(blk, kk, g, e);
             if constexpr (Noise::kUnroll == 1) {
-                kk += 4;
+                kk += kk4;
                 kk -= kk >= P.S ? P.S : 0u;
             }
 #pragma unroll
@@ -465,71 +472,89 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, c
                     R ns[PPT];
 #pragma unroll
                     for (int k = 0; k < PPT; ++k) ns[k] = g[u][k][j];
-                    jj_step<R, PPT, SCHEME, INERTIAL, COSF, decltype(in_window)::value>(
-                        P, T, e[u][j], e[u][j + 1], ns, th, vv, af);
+                    jj_step<R, PPT, SCHEME, INERTIAL, COSF, kMode != kPlain>(P, T, e[u][j], e[u][j + 1], ns, th, vv, af);
+                    if constexpr (kMode == kTick) {
+                        const bool due = --to_fold == 0;
+                        to_fold = due ? A.M : to_fold;
+#pragma unroll
+                        for (int k = 0; k < PPT; ++k) {
+                            ad[k] += (double)(due ? af[k] : R(0));
+                            af[k] = due ? R(0) : af[k];
+                        }
+                    }
                 }
                 wrap();
             }
         }
     };
-    auto run_blocks = [&](auto in_window, uint32_t count) {
+    auto run_blocks = [&](auto mode, uint32_t count, uint32_t blk) {
         constexpr uint32_t U = Noise::kUnroll;
-        const uint32_t blk = (uint32_t)(n >> 2);
-        run_some(in_window, std::integral_constant<uint32_t, U>{}, count / U, blk);
-        if constexpr (U > 1) {
-            run_some(in_window, std::integral_constant<uint32_t, 1>{}, count % U, blk + count / U * U);
-            kk += 4 * count;  // the source holds the drive: the phase only matters afterwards
-            kk -= kk >= P.S ? P.S : 0u;
-            if (kk >= P.S) kk %= P.S;
-        }
+        run_some(mode, std::integral_constant<uint32_t, U>{}, count / U, blk);
+        if constexpr (U > 1) run_some(mode, std::integral_constant<uint32_t, 1>{}, count % U, blk + count / U * U);
     };
 
     while (n < n_end) {
         const uint32_t j0 = (uint32_t)n & 3u;
         const uint64_t left = n_end - n;
-        src.ensure();
-        if (j0 == 0 && left >= 4 && P.S >= 4) {
+        if (j0 == 0 && left >= 4) {
             // The whole blocks up to the next event: the end of the call, the
             // start of the window, the block that a fold falls into (or ends
-            // at), a record.  Their loop is one basic block: the compiler
-            // overlaps the noise, the four steps and the drive's loads, which
+            // at).  Their loop is one basic block: the compiler overlaps the noise, the four steps and the drive's loads, which
             // branches for the window and the fold between the steps had kept
             // apart (one point of 4096 paths, one wave per SIMD: 1335 -> 885 us
             // for 10^4 steps; 4096 x 1024 paths x 5000 steps, ALU-bound:
             // 18.4 -> 17.7 ms; a ragged batch 4.41 -> 3.72 ms).
+            constexpr bool kTicks = Noise::kUnroll > 1;
             const bool window = n >= P.n_transient;
             uint64_t blocks = left >> 2;
+            bool tick = false;
             if (window) {
                 open_window();
-                blocks = min(blocks, (uint64_t)(to_fold >> 2));
+                // folds in every other block or more are no events: a loop of
+                // one or two blocks costs more than the ticks (1000 paths, 2000
+                // steps, sample_every 1: 409 us with events, 120 so)
+                tick = kTicks && (A.M < 8 || to_fold < 4);
+                if (!kTicks || A.M >= 8) blocks = min(blocks, (uint64_t)max(to_fold >> 2, tick ? 1u : 0u));
             } else
                 blocks = min(blocks, (P.n_transient - n) >> 2);
-            if (A.rec) blocks = min(blocks, (uint64_t)((A.rec_every - rc) >> 2));
-            const uint32_t count = (uint32_t)min(blocks, (uint64_t)src.avail());
+            const uint32_t count = (uint32_t)min(blocks, (uint64_t)1 << 28);
             if (count) {
-                if (window) {
-                    run_blocks(std::true_type{}, count);
+                // as the noise and the records come
+                uint32_t todo = count, blk = (uint32_t)(n >> 2);
+                do {
+                    src.ensure();
+                    uint32_t some = min(todo, src.avail());
+                    if (recording) some = min(some, (A.rec_every - rc) >> 2);
+                    if (kTicks && tick)
+                        run_blocks(std::integral_constant<int, kTicks ? kTick : kPlain>{}, some, blk);
+                    else if (window)
+                        run_blocks(std::integral_constant<int, kWindow>{}, some, blk);
+                    else
+                        run_blocks(std::integral_constant<int, kPlain>{}, some, blk);
+                    blk += some;
+                    if (recording) {
+                        rc += 4 * some;
+                        if (rc == A.rec_every) record();
+                    }
+                    todo -= some;
+                } while ((kTicks || sizeof(R) == 4) && todo);  // FP64 drawing its own: at once
+                n += 4 * (uint64_t)count;
+                if (kTicks) {  // the ring holds the drive: its phase only matters to steps taken one by one
+                    kk += 4 * count;
+                    if (kk >= P.S) kk %= P.S;
+                }
+                if (window && !tick) {
                     to_fold -= 4 * count;
                     if (to_fold == 0) fold();
-                } else {
-                    run_blocks(std::false_type{}, count);
-                }
-                n += 4 * (uint64_t)count;
-                if (A.rec) {
-                    rc += 4 * count;
-                    if (rc == A.rec_every) record();
                 }
                 continue;
             }
         }
-        // one block step by step: a first or last partial one, one the window
-        // begins in, or one with a fold between its steps
+        src.ensure();
         const uint32_t jn = left >= (uint64_t)(4u - j0) ? 4u : j0 + (uint32_t)left;
-        R g[1][PPT][4], unused[1][5];  // the drive terms are taken step by step
-        src.take((uint32_t)(n >> 2), 0u, g, unused);
-        auto step = [&](const R (&ns)[PPT]) {
-            const R ea = fm(P.a_im, load_uniform(lut + kk), P.f_im);
-            const R eb = fm(P.a_im, load_uniform(lut + kk + 1), P.f_im);
+        R g[1][PPT][4], e[1][5];
+        src.take((uint32_t)(n >> 2), kk, g, e);
+        auto step = [&](R ea, R eb, const R (&ns)[PPT]) {
             if (n >= P.n_transient) {
                 open_window();
                 jj_step<R, PPT, SCHEME, INERTIAL, COSF, true>(P, T, ea, eb, ns, th, vv, af);
@@ -538,28 +563,32 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, c
                 jj_step<R, PPT, SCHEME, INERTIAL, COSF, false>(P, T, ea, eb, ns, th, vv, af);
             }
             ++n;
-            kk = (kk + 1 == P.S) ? 0u : kk + 1;
         };
         if (j0 == 0 && jn == 4) {
+            // a whole block that the window begins in, or with a fold between
+            // its steps; its drive terms come with the noise
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 R ns[PPT];
 #pragma unroll
                 for (int k = 0; k < PPT; ++k) ns[k] = g[0][k][j];
-                step(ns);
+                step(e[0][j], e[0][j + 1], ns);
             }
-        } else {
+            kk += kk4;
+            kk -= kk >= P.S ? P.S : 0u;
+        } else {  // a first or last partial block of the call
             for (uint32_t j = j0; j < jn; ++j) {
                 R ns[PPT];
 #pragma unroll
                 for (int k = 0; k < PPT; ++k)
                     ns[k] = j == 0 ? g[0][k][0] : j == 1 ? g[0][k][1] : j == 2 ? g[0][k][2] : g[0][k][3];
-                step(ns);
+                step(fm(P.a_im, load_uniform(lut + kk), P.f_im), fm(P.a_im, load_uniform(lut + kk + 1), P.f_im), ns);
+                kk = (kk + 1 == P.S) ? 0u : kk + 1;
             }
         }
         wrap();
         // a block never crosses a multiple of 4, hence of rec_every
-        if (A.rec) {
+        if (recording) {
             rc += jn - j0;
             if (rc == A.rec_every) record();
         }
