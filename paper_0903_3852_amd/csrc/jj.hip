@@ -187,10 +187,13 @@ template <bool COSF>
 __device__ __forceinline__ double jj_shape(double theta, const JJTables<double>& T)
 {
 #pragma clang fp contract(off)
-    // n = 256 theta to the nearest integer, in the low bits of t (|theta| < 2^42)
+    // whole revolutions out (exactly, whatever their number: a predictor of a
+    // path that diverges may be anywhere), then 256 of the rest to the nearest
+    // integer, in the low bits of t
     constexpr double kMagic = 0x1.8p52;
-    const double t = fma(256.0, theta, kMagic);
-    const double r = fma(-0x1p-8, t - kMagic, theta);
+    const double f = theta - __builtin_rint(theta);
+    const double t = fma(256.0, f, kMagic);
+    const double r = fma(-0x1p-8, t - kMagic, f);
     double sn, cs;
     rotate_entry<!COSF, COSF>(T, (uint32_t)__double_as_longlong(t) & 255u, r, sn, cs);
     return COSF ? cs : sn;
