@@ -1072,6 +1072,13 @@ struct JJSetup {
     uint32_t M = 100, max_period = 0;
 };
 
+// Whether every point's drive terms fit the persistent kernel's LDS table.
+template <typename R>
+static bool drive_fits(const JJSetup<R>& S)
+{
+    return S.max_period <= kDriveTable - 8;
+}
+
 // Validates a call's arguments (nothing is launched on an error) and builds
 // its per-point constants and drive tables.
 template <typename R>
@@ -1176,7 +1183,7 @@ static void jj_fill_args(sde_ctx* ctx, const sde_run* run, const JJSetup<R>& S, 
                          double* acc, double* point_sums, JJLaunch& L)
 {
     L.scheme = run->scheme;
-    L.tab = S.max_period <= kDriveTable - 8;
+    L.tab = drive_fits(S);
     L.point_sums = point_sums;
     L.A.flag = ctx->flag;
     L.A.theta = theta;
@@ -1201,15 +1208,29 @@ static int default_choice(const sde_ctx* ctx, const JJSetup<R>& S)
     return split_fits(ctx, S.P) ? kSplitChoice : 2;
 }
 
-// Tune-cache key of a call's shape class (paths per lane).
+// Tune-cache key of a call's shape class (paths per lane).  Calls that have
+// other candidates or kernels are classes of their own: those small enough for
+// the split kernel (the limit lies inside a power of two of paths), and FP32
+// periods past the drive table.
 template <typename R>
 static std::string jj_tune_key(sde_ctx* ctx, const sde_run* run, const JJSetup<R>& S)
 {
-    char key[160];
-    snprintf(key, sizeof key, "jj|%s|%s|scheme%d|kinds%x|paths2^%d|steps2^%d", ctx->arch.c_str(),
+    char key[192];
+    snprintf(key, sizeof key, "jj|%s|%s|scheme%d|kinds%x|paths2^%d|steps2^%d%s%s", ctx->arch.c_str(),
              sizeof(R) == 4 ? "f32" : "f64", run->scheme, S.kinds_present, ilog2u64(S.path_first),
-             ilog2u64(std::max<uint64_t>(S.max_steps, 1)));
+             ilog2u64(std::max<uint64_t>(S.max_steps, 1)), split_fits(ctx, S.P) ? "|few" : "",
+             sizeof(R) == 4 && !drive_fits(S) ? "|long-drive" : "");
     return key;
+}
+
+// The choice cached for a call's class, if it can run it.
+template <typename R>
+static bool cached_choice(sde_ctx* ctx, const sde_run* run, const JJSetup<R>& S, int* choice)
+{
+    int c;
+    if (!tune_lookup(ctx, jj_tune_key<R>(ctx, run, S), &c) || (c == kSplitChoice && !split_fits(ctx, S.P))) return false;
+    *choice = c;
+    return true;
 }
 
 template <typename R>
@@ -1249,20 +1270,17 @@ static int jj_integrate_t(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_pts,
     int choice = ctx->jj_ppt;
     if (sizeof(R) == 8 && choice == 4) choice = 2;
     if (!choice) {
-        const std::string key = jj_tune_key<R>(ctx, run, S);
-        if (!tune_lookup(ctx, key, &choice)) {
+        if (!cached_choice(ctx, run, S, &choice)) {
             choice = default_choice(ctx, S);
             if (ctx->autotune) {
                 const auto t0 = std::chrono::steady_clock::now();
                 if ((st = jj_tune<R>(ctx, S.P, S.kinds, L, stream, &choice))) return st;
                 ctx->last.tuned = 1;
                 ctx->last.tune_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-                tune_store(ctx, key, choice);
+                tune_store(ctx, jj_tune_key<R>(ctx, run, S), choice);
             }
         }
     }
-    // a choice cached for a smaller call of the class
-    if (choice == kSplitChoice && !split_fits(ctx, S.P)) choice = 1;
     set_choice(L, choice);
     JJPlan<R> plan;
     plan_items(S.P, S.kinds, L.ppt, plan);
@@ -1349,8 +1367,7 @@ int jj_integrate_noalloc_impl(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_
     // paths per lane: forced, else a choice the tuner cached, else the
     // default; never tuned here (tuning allocates)
     int choice = ctx->jj_ppt;
-    if (!choice && !tune_lookup(ctx, jj_tune_key<float>(ctx, run, S), &choice)) choice = default_choice(ctx, S);
-    if (choice == kSplitChoice && !split_fits(ctx, S.P)) choice = 1;
+    if (!choice && !cached_choice(ctx, run, S, &choice)) choice = default_choice(ctx, S);
 
     // layout of the scratch; the tables [o_pts, o_part) are one host image
     JJLaunch L;

@@ -1,0 +1,49 @@
+"""Which launch the path integrator's calls take: shape classes of the tuner on
+either side of the limit of the launch for small calls (6 workgroups of 64
+paths per CU, FP64 3), which lies inside a power of two of paths.
+"""
+import pytest
+import torch
+
+import sde_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _limit(dev, f64):
+    return (3 if f64 else 6) * 64 * torch.cuda.get_device_properties(dev).multi_processor_count
+
+
+def _integrate(sde, ctx, dev, n_paths, f64, steps=16, period=400):
+    pts = [sde_inputs.jj_point(n_paths=n_paths, n_steps=steps, steps_per_period=period, omega=4.9 * 400 / period)]
+    ps = torch.zeros((1, 2), dtype=torch.float64, device=dev)
+    call = sde.sde_jj_integrate_f64 if f64 else sde.sde_jj_integrate
+    call(ctx, pts, sde.make_run(3, sync=1), None, None, None, None, ps)
+    return sde.sde_get_stats(ctx)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("first", ["below", "above"])
+def test_classes_end_at_the_limit(gpu, f64, first):
+    """A call past the limit is tuned for itself, whichever came first."""
+    sde, _, dev = gpu
+    limit = _limit(dev, f64)
+    sizes = [limit, limit + 1] if first == "below" else [limit + 1, limit]
+    assert limit.bit_length() == (limit + 1).bit_length()
+    ctx = sde.sde_create(0)
+    try:
+        for n in sizes:
+            assert _integrate(sde, ctx, dev, n, f64)["tuned"] == 1
+        for n in sizes:
+            assert _integrate(sde, ctx, dev, n, f64)["tuned"] == 0
+    finally:
+        sde.sde_destroy(ctx)
+
+
+def test_periods_past_the_drive_table_are_a_class(gpu):
+    sde, _, dev = gpu
+    ctx = sde.sde_create(0)
+    try:
+        assert [_integrate(sde, ctx, dev, 5000, False, period=p)["tuned"] for p in (1016, 1017, 400, 2000)] == [1, 1, 0, 0]
+    finally:
+        sde.sde_destroy(ctx)
