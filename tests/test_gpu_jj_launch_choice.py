@@ -47,3 +47,39 @@ def test_periods_past_the_drive_table_are_a_class(gpu):
         assert [_integrate(sde, ctx, dev, 5000, False, period=p)["tuned"] for p in (1016, 1017, 400, 2000)] == [1, 1, 0, 0]
     finally:
         sde.sde_destroy(ctx)
+
+
+def _kernels(sde, ctx, dev, n_paths, f64, call=None):
+    """Names of the integration kernels that a call launches, as traced."""
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as p:
+        if call:
+            call()
+        else:
+            _integrate(sde, ctx, dev, n_paths, f64)
+        torch.cuda.synchronize()
+    return {k for e in p.key_averages() for k in ("jj_split_kernel", "jj_persistent_kernel") if k in e.key}
+
+
+@pytest.mark.parametrize("f64", [False, True])
+def test_kernel_of_small_and_large_calls(gpu, f64):
+    """Untuned calls up to the limit run the split kernel, larger ones and
+    forced paths per lane the persistent one: comparisons of the two kernels
+    elsewhere rely on it."""
+    sde, _, dev = gpu
+    limit = _limit(dev, f64)
+    ctx = sde.sde_create(0)
+    try:
+        sde.sde_set_option(ctx, sde.SDE_OPT_AUTOTUNE, 0)
+        sde.sde_set_option(ctx, sde.SDE_OPT_GRAPHS, 0)
+        assert _kernels(sde, ctx, dev, 1, f64) == {"jj_split_kernel"}
+        assert _kernels(sde, ctx, dev, limit, f64) == {"jj_split_kernel"}
+        assert _kernels(sde, ctx, dev, limit + 1, f64) == {"jj_persistent_kernel"}
+        if not f64:
+            pts = [sde_inputs.jj_point(n_paths=194, n_steps=16)]
+            assert _kernels(sde, ctx, dev, 0, f64, lambda: sde.sde_jj_integrate_noalloc(
+                ctx, pts, sde.make_run(3, sync=1))) == {"jj_split_kernel"}
+        for ppt in (1, 2, 4):
+            sde.sde_set_option(ctx, sde.SDE_OPT_JJ_PPT, ppt)
+            assert _kernels(sde, ctx, dev, 1000, f64) == {"jj_persistent_kernel"}
+    finally:
+        sde.sde_destroy(ctx)
