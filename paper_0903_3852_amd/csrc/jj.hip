@@ -1383,8 +1383,8 @@ int jj_integrate_noalloc_impl(sde_ctx* ctx, const sde_jj_point* pts, uint32_t n_
         o_lut = align256(o_items + items_bytes);
         o_part = align256(o_lut + lut_bytes);
         need = o_part + (size_t)std::max(plan.n_chunks, 1u) * 2 * sizeof(double);
-        if (need <= kNoAllocScratchBytes || ctx->jj_ppt || choice == 2) break;
-        choice = 2;  // not forced: half the chunks may fit
+        if (need <= kNoAllocScratchBytes || ctx->jj_ppt || L.ppt != 1) break;
+        choice = 2;  // one path per lane, not forced: half the chunks may fit
     }
     if (need > kNoAllocScratchBytes)
         return fail(ctx, SDE_ERR_INVALID,

@@ -83,3 +83,23 @@ def test_kernel_of_small_and_large_calls(gpu, f64):
             assert _kernels(sde, ctx, dev, 1000, f64) == {"jj_persistent_kernel"}
     finally:
         sde.sde_destroy(ctx)
+
+
+@pytest.mark.parametrize("cached", [1, 2, 4])
+def test_no_allocation_keeps_a_cached_choice_of_fewer_chunks(gpu, tmp_path, cached):
+    """A call too large for the scratch is refused with the chunks of the
+    choice it would run: 4 paths per lane stay (2 would need twice the
+    scratch), 1 falls back to 2, which needs half."""
+    sde, _, dev = gpu
+    n = 200_000_000
+    arch = torch.cuda.get_device_properties(dev).gcnArchName
+    key = f"jj|{arch}|f32|scheme0|kinds1|paths2^{n.bit_length() - 1}|steps2^4"
+    (tmp_path / "tune.json").write_text('{"%s": %d}' % (key, cached))
+    ctx = sde.sde_create(0)
+    try:
+        sde.sde_set_tune_cache(ctx, str(tmp_path / "tune.json"))
+        with pytest.raises(sde.SDEError, match=f"in {-(-n // (64 * max(cached, 2)))} path chunks") as e:
+            sde.sde_jj_integrate_noalloc(ctx, [sde_inputs.jj_point(n_paths=n, n_steps=16)], sde.make_run(3, sync=1))
+        assert e.value.status == sde.SDE_ERR_INVALID
+    finally:
+        sde.sde_destroy(ctx)
