@@ -172,12 +172,20 @@ __global__ __launch_bounds__(kObsThreads) void obs_combine_kernel(ObsArgs A, int
 //
 // What bounds it: an ensemble sits in a few bins, and atomics of one wave on
 // one LDS word are taken one after the other.  So every bin has up to 32
-// copies side by side (lane l adds to copy l mod 32, another bank), as many
-// as 64 KB hold; values come 16 bytes a lane, two loads in flight.  200 rows
-// of 2^19 windings: 227 us (1.85 TB/s) with one copy and 4-byte loads, 75-79
-// us (5.3-5.6 TB/s) with these.
-constexpr int kHistThreads = 512;
+// copies side by side (lane l adds to copy l mod 32, another bank); values
+// come 16 bytes a lane, two loads in flight.  200 rows of 2^19 windings: 227 us
+// (1.85 TB/s) with one copy and 4-byte loads, 75-79 us (5.3-5.6 TB/s) with
+// these.  Of short rows the clearing and adding up of the bins is the work, so
+// the copies stay within a sixteenth of the values that a workgroup counts
+// (20000 rows of 1000 values, 500 bins: 32 us with one copy, 165 with 32; 2000
+// rows of 20000, 10 bins: 33 with one, 27 with 8), and a workgroup has as many
+// waves as it has work for (20000 rows of 100, 100 bins: 16 us with one wave,
+// 39 with eight; 20000 of 1000, 8000 bins: 500 with one, 278 with eight).
+constexpr uint32_t kHistThreads = 512;
 constexpr uint32_t kHistWords = 16384;  // LDS words for bins and their copies
+// Values far fewer than bins are counted in memory at once (rows of 10 values,
+// 2000 bins: 299 us against 387 by way of LDS, 500 bins: 107 against 106).
+constexpr uint64_t kHistSparse = 64;
 // A share of at least this many values, so that few workgroups add to the
 // same totals (one row of 2^19 phases: 24 us with 1024 of them, 6 with 64).
 constexpr uint64_t kHistShare = 8192;
@@ -195,6 +203,7 @@ struct HistArgs {
     uint32_t nb;       // bins asked for
     uint32_t total;    // bins counted: with those for values outside
     int32_t log_copies;
+    int32_t store;     // a row has one workgroup: its counts are stored, not added
     uint64_t* counts;  // [rows][total]
 };
 
@@ -250,8 +259,9 @@ __global__ __launch_bounds__(kHistThreads) void hist_kernel(HistArgs A)
     const int lc = A.log_copies;
     const bool lds = lc >= 0;
     const uint32_t copy = lds ? threadIdx.x & ((1u << lc) - 1u) : 0u;
+    const uint32_t threads = blockDim.x;
     if (lds)
-        for (uint32_t i = threadIdx.x; i < A.total << lc; i += kHistThreads) h[i] = 0u;
+        for (uint32_t i = threadIdx.x; i < A.total << lc; i += threads) h[i] = 0u;
     for (uint64_t r = blockIdx.y; r < A.rows; r += gridDim.y) {
         const T* row = static_cast<const T*>(A.data) + r * A.pitch;
         uint64_t* cr = A.counts + r * (uint64_t)A.total;
@@ -271,8 +281,8 @@ __global__ __launch_bounds__(kHistThreads) void hist_kernel(HistArgs A)
             if (threadIdx.x < head) count(row[threadIdx.x]);
             if (tail + threadIdx.x < A.n) count(row[tail + threadIdx.x]);
         }
-        const uint64_t stride = (uint64_t)gridDim.x * kHistThreads;
-        uint64_t i = (uint64_t)blockIdx.x * kHistThreads + threadIdx.x;
+        const uint64_t stride = (uint64_t)gridDim.x * threads;
+        uint64_t i = (uint64_t)blockIdx.x * threads + threadIdx.x;
         for (; i + stride < n4; i += 2 * stride) {
             const V4 a = body[i], b = body[i + stride];
 #pragma unroll
@@ -287,14 +297,18 @@ __global__ __launch_bounds__(kHistThreads) void hist_kernel(HistArgs A)
         }
         __syncthreads();
         if (lds)
-            for (uint32_t b = threadIdx.x; b < A.total; b += kHistThreads) {
+            for (uint32_t b = threadIdx.x; b < A.total; b += threads) {
                 uint64_t sum = 0;  // and the bin is cleared for the next row
+                const uint32_t turn = b >> (5 - lc);  // of 32 neighbouring bins no two on a bank
                 for (uint32_t c = 0; c < 1u << lc; ++c) {
-                    uint32_t* q = &h[(b << lc) + ((c + b) & ((1u << lc) - 1u))];  // rotated: no two lanes on a bank
+                    uint32_t* q = &h[(b << lc) + ((c + turn) & ((1u << lc) - 1u))];
                     sum += *q;
                     *q = 0u;
                 }
-                if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(cr + b), (unsigned long long)sum);
+                if (A.store)
+                    cr[b] = sum;
+                else if (sum)
+                    atomicAdd(reinterpret_cast<unsigned long long*>(cr + b), (unsigned long long)sum);
             }
     }
 }
@@ -304,19 +318,33 @@ static int launch_hist(sde_ctx* ctx, HistArgs A, void (*kern)(HistArgs), hipStre
     const uint64_t nc = (uint64_t)A.total * A.rows;
     const uint64_t zb = (nc + 255) / 256;
     if (zb > 0x7fffffffull) return fail(ctx, SDE_ERR_INVALID, "too many counts");
-    hipLaunchKernelGGL(hist_zero_kernel, dim3((uint32_t)zb), dim3(256), 0, stream, A.counts, nc);
-    SDE_HIP(ctx, hipGetLastError());
-    if (A.n == 0) return SDE_OK;
-    A.log_copies = -1;
-    while (A.log_copies < 5 && ((uint64_t)A.total << (A.log_copies + 1)) <= kHistWords) ++A.log_copies;
-    const size_t lds = A.log_copies < 0 ? 0 : ((size_t)A.total << A.log_copies) * sizeof(uint32_t);
     // about 4 workgroups per CU in all, at least one per row (up to 65535
     // rows in flight), shares of kHistShare to 2^31 values
     const uint64_t gy = std::min<uint64_t>(A.rows, 65535);
     uint64_t gx = std::max<uint64_t>(1, (uint64_t)ctx->n_cu * 4 / gy);
     gx = std::min<uint64_t>(gx, (A.n + kHistShare - 1) / kHistShare);
     gx = std::max<uint64_t>(gx, (A.n >> 31) + 1);
-    hipLaunchKernelGGL(kern, dim3((uint32_t)gx, (uint32_t)gy), dim3(kHistThreads), lds, stream, A);
+    const uint64_t share = (A.n + gx - 1) / gx;
+    A.log_copies = -1;
+    if (A.total <= kHistWords && A.total <= kHistSparse * share) {
+        const uint64_t words = std::min<uint64_t>(kHistWords, share / 16);
+        A.log_copies = 0;
+        while (A.log_copies < 5 && ((uint64_t)A.total << (A.log_copies + 1)) <= words) ++A.log_copies;
+    }
+    const size_t lds = A.log_copies < 0 ? 0 : ((size_t)A.total << A.log_copies) * sizeof(uint32_t);
+    // a row of one workgroup needs no totals to add to (20000 rows of 1000
+    // phases, 2000 bins: 358 us with them, 75 without)
+    A.store = gx == 1 && A.log_copies >= 0;
+    if (!A.store || A.n == 0) {
+        hipLaunchKernelGGL(hist_zero_kernel, dim3((uint32_t)zb), dim3(256), 0, stream, A.counts, nc);
+        SDE_HIP(ctx, hipGetLastError());
+        if (A.n == 0) return SDE_OK;
+    }
+    // a wave for less than 2048 values and bins to clear and add up, two, four
+    // or eight for more
+    const uint64_t work = share + (A.log_copies < 0 ? 0u : 2u * A.total);
+    const uint32_t threads = work < 2048 ? 64 : work < 4096 ? 128 : work < 16384 ? 256 : kHistThreads;
+    hipLaunchKernelGGL(kern, dim3((uint32_t)gx, (uint32_t)gy), dim3(threads), lds, stream, A);
     SDE_HIP(ctx, hipGetLastError());
     return SDE_OK;
 }
@@ -329,7 +357,7 @@ int histogram_impl(sde_ctx* ctx, const int32_t* winding, uint64_t n, uint64_t pi
     if (n_rows == 0 || n_rows > (1ull << 32)) return fail(ctx, SDE_ERR_INVALID, "n_rows must be in [1, 2^32]");
     if (n_rows > 1 && pitch < n) return fail(ctx, SDE_ERR_INVALID, "row pitch below the row length");
     if (!aligned(winding, 4) || !aligned(counts, 8)) return fail(ctx, SDE_ERR_INVALID, "misaligned pointer");
-    const HistArgs A{winding, n, n_rows > 1 ? pitch : n, n_rows, x0, n_bins, n_bins + 2, 0, counts};
+    const HistArgs A{winding, n, n_rows > 1 ? pitch : n, n_rows, x0, n_bins, n_bins + 2, 0, 0, counts};
     return launch_hist(ctx, A, x0 == (int32_t)x0 ? hist_kernel<PositionBin> : hist_kernel<WidePositionBin>, stream);
 }
 
@@ -341,7 +369,7 @@ int phase_histogram_impl(sde_ctx* ctx, const float* theta, uint64_t n, uint64_t 
     if (n_rows == 0 || n_rows > (1ull << 32)) return fail(ctx, SDE_ERR_INVALID, "n_rows must be in [1, 2^32]");
     if (n_rows > 1 && pitch < n) return fail(ctx, SDE_ERR_INVALID, "row pitch below the row length");
     if (!aligned(theta, 4) || !aligned(counts, 8)) return fail(ctx, SDE_ERR_INVALID, "misaligned pointer");
-    const HistArgs A{theta, n, n_rows > 1 ? pitch : n, n_rows, 0, n_bins, n_bins + 1, 0, counts};
+    const HistArgs A{theta, n, n_rows > 1 ? pitch : n, n_rows, 0, n_bins, n_bins + 1, 0, 0, counts};
     return launch_hist(ctx, A, hist_kernel<PhaseBin>, stream);
 }
 
