@@ -9,7 +9,8 @@
 // sum).  A second kernel combines a group's slices in a fixed order: the
 // mean from the sums, and about it
 //   sum (x - mean)^2 = sum_s [ M2_s + n_s (mean_s - mean)^2 ].
-// Groups that fit one slice are finished by the first kernel.  All sums run
+// Where no group needs more than one slice, or there are groups enough to fill
+// the chip, a workgroup takes a whole group instead.  All sums run
 // in a fixed order (elements by thread, wavefront butterfly, waves, slices),
 // so results are bitwise reproducible.
 #include <hip/hip_runtime.h>
@@ -25,15 +26,17 @@ namespace sde {
 
 constexpr int kObsThreads = 256;
 
+template <int THREADS>
 __device__ double block_sum(double x, double* lds)
 {
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     x = wave_sum(x);
+    if constexpr (THREADS == kWave) return x;
     if (lane == 0) lds[wid] = x;
     __syncthreads();
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < kObsThreads / kWave; ++w) t += lds[w];
+    for (int w = 0; w < THREADS / kWave; ++w) t += lds[w];
     __syncthreads();
     return t;
 }
@@ -42,7 +45,15 @@ __device__ double block_sum(double x, double* lds)
 // it (the earlier kernel) read a single group of 2^19 values with one CU:
 // 580-930 us; in slices of 1024-4096 the same call takes 24 us, its launches
 // and the final synchronization.
-constexpr int kObsItems = 16;
+constexpr uint32_t kObsItems = 16;
+// The most that a workgroup with a group of its own holds.
+constexpr uint32_t kObsGroupItems = 32;
+// Workgroups in a grid's x; past them y counts on (their threads would not fit
+// 32 bits).
+constexpr uint32_t kObsGrid = 1u << 20;
+
+static dim3 obs_grid(uint32_t n) { return dim3(std::min(n, kObsGrid), (n + kObsGrid - 1) / kObsGrid); }
+__device__ __forceinline__ uint32_t obs_block() { return blockIdx.y * kObsGrid + blockIdx.x; }
 
 struct ObsArgs {
     const void* in;
@@ -50,65 +61,91 @@ struct ObsArgs {
     const uint32_t* counts;        // [n_groups]
     const uint32_t* slice_begin;   // [n_groups + 1] slices before the group
     double* part;                  // [slices][2]: (sum, M2 about the slice's mean), or (sum cos, sum sin)
-    double* out;                   // [n_groups][2], pinned host memory
-    uint32_t n_groups, slice;      // slice: elements per slice, at most kObsThreads * kObsItems
+    double* out;                   // [n_groups][2]
+    uint32_t n_groups, n_slices;
+    uint32_t slice;                // elements per slice, at most kObsThreads * kObsItems
 };
 
-// A slice's two sums (every thread has them): (sum, M2 about its mean) or,
-// for the order parameter, (sum cos, sum sin) in FP64.
-template <int KIND, int ITEMS>
+// The two sums (every thread has them) of n <= ITEMS * THREADS elements:
+// (sum, M2 about its mean); of any number of them for the order parameter:
+// (sum cos, sum sin) in FP64.
+template <int KIND, int ITEMS, int THREADS = kObsThreads>
 __device__ __forceinline__ void obs_slice(const void* in, uint64_t base, uint32_t n, double* lds, double& a, double& b)
 {
     using T = typename std::conditional<KIND == SDE_OBS_MEAN_F64, double, float>::type;
     const T* p = static_cast<const T*>(in) + base;
-    T raw[ITEMS];
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-        const uint32_t i = k * kObsThreads + threadIdx.x;
-        raw[k] = i < n ? p[i] : T(0);
-    }
     a = 0.0;
     b = 0.0;
     if constexpr (KIND == SDE_OBS_ORDER) {
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            if ((uint32_t)(k * kObsThreads) + threadIdx.x >= n) break;
+        auto add = [&](T x) {
             double sn, cs;
-            sincospi(2.0 * (double)raw[k], &sn, &cs);
+            sincospi(2.0 * (double)x, &sn, &cs);
             a += cs;
             b += sn;
+        };
+        // a thread's elements in order, four loads in flight
+        uint64_t i = threadIdx.x;
+        for (; i + 3 * THREADS < n; i += 4 * THREADS) {
+            T raw[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) raw[k] = p[i + k * THREADS];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) add(raw[k]);
         }
-        a = block_sum(a, lds);
-        b = block_sum(b, lds);
+        for (; i < n; i += THREADS) add(p[i]);
+        a = block_sum<THREADS>(a, lds);
+        b = block_sum<THREADS>(b, lds);
     } else {
+        if (n == 0) return;
+        // no condition on the loads, so that all of them are in flight (past the
+        // end the last element again)
+        T raw[ITEMS];
+#pragma unroll
+        for (int k = 0; k < ITEMS; ++k) raw[k] = p[min((uint32_t)(k * THREADS) + threadIdx.x, n - 1)];
         double x[ITEMS];
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            x[k] = (double)raw[k];
+            x[k] = (uint32_t)(k * THREADS) + threadIdx.x < n ? (double)raw[k] : 0.0;
             if (KIND == SDE_OBS_MEANSQ_F32) x[k] *= x[k];
             a += x[k];  // lanes past the end hold zero
         }
-        a = block_sum(a, lds);
+        a = block_sum<THREADS>(a, lds);
         const double mean = a / (double)n;
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            const double d = (uint32_t)(k * kObsThreads) + threadIdx.x < n ? x[k] - mean : 0.0;
+            const double d = (uint32_t)(k * THREADS) + threadIdx.x < n ? x[k] - mean : 0.0;
             b += d * d;
         }
-        b = block_sum(b, lds);
+        b = block_sum<THREADS>(b, lds);
     }
 }
 
 __device__ __forceinline__ void obs_finish(int kind, uint32_t n, double a, double b, double* out)
 {
+    double2 r;
     if (kind == SDE_OBS_ORDER) {
         const double inv = n ? 1.0 / (double)n : 0.0;
-        out[0] = std::sqrt(a * a + b * b) * inv;
-        out[1] = n ? atan2(b, a) / (2.0 * M_PI) : 0.0;
+        r.x = std::sqrt(a * a + b * b) * inv;
+        r.y = n ? atan2(b, a) / (2.0 * M_PI) : 0.0;
     } else {
-        out[0] = n ? a / (double)n : 0.0;
-        out[1] = n > 1 ? std::sqrt(b / (double)(n - 1) / (double)n) : 0.0;
+        r.x = n ? a / (double)n : 0.0;
+        r.y = n > 1 ? std::sqrt(b / (double)(n - 1) / (double)n) : 0.0;
     }
+    *reinterpret_cast<double2*>(out) = r;  // one store over the bus
+}
+
+// One workgroup per group, of one wave for groups of up to 256 elements (16384
+// groups of 100: 64 us with four, 50 so).
+template <int KIND, int ITEMS, int THREADS>
+__global__ __launch_bounds__(THREADS) void obs_group_kernel(ObsArgs A)
+{
+    __shared__ double lds[THREADS / kWave];
+    const uint32_t g = obs_block();
+    if (g >= A.n_groups) return;
+    const uint32_t n = A.counts[g];
+    double a, b;
+    obs_slice<KIND, ITEMS, THREADS>(A.in, A.first[g], n, lds, a, b);
+    if (threadIdx.x == 0) obs_finish(KIND, n, a, b, A.out + 2 * (uint64_t)g);
 }
 
 // One workgroup per slice; a group of one slice (or none) is finished here.
@@ -116,16 +153,18 @@ template <int KIND, int ITEMS>
 __global__ __launch_bounds__(kObsThreads) void obs_slice_kernel(ObsArgs A)
 {
     __shared__ double lds[kObsThreads / kWave];
+    const uint32_t s = obs_block();
+    if (s >= A.n_slices) return;
     // the group of this slice: the last one whose slices begin at or before it
     uint32_t lo = 0, hi = A.n_groups;
     while (hi - lo > 1) {
         const uint32_t mid = lo + (hi - lo) / 2;
-        if (A.slice_begin[mid] <= blockIdx.x)
+        if (A.slice_begin[mid] <= s)
             lo = mid;
         else
             hi = mid;
     }
-    const uint32_t sl = blockIdx.x - A.slice_begin[lo], n = A.counts[lo];
+    const uint32_t sl = s - A.slice_begin[lo], n = A.counts[lo];
     const uint64_t off = (uint64_t)sl * A.slice;
     const uint32_t cnt = (uint32_t)min((uint64_t)A.slice, (uint64_t)n - off);
     double a, b;
@@ -134,8 +173,8 @@ __global__ __launch_bounds__(kObsThreads) void obs_slice_kernel(ObsArgs A)
     if (n <= A.slice)
         obs_finish(KIND, n, a, b, A.out + 2 * (uint64_t)lo);
     else {
-        A.part[2 * (uint64_t)blockIdx.x] = a;
-        A.part[2 * (uint64_t)blockIdx.x + 1] = b;
+        A.part[2 * (uint64_t)s] = a;
+        A.part[2 * (uint64_t)s + 1] = b;
     }
 }
 
@@ -143,13 +182,15 @@ __global__ __launch_bounds__(kObsThreads) void obs_slice_kernel(ObsArgs A)
 __global__ __launch_bounds__(kObsThreads) void obs_combine_kernel(ObsArgs A, int kind)
 {
     __shared__ double lds[kObsThreads / kWave];
-    const uint32_t g = blockIdx.x, n = A.counts[g];
+    const uint32_t g = obs_block();
+    if (g >= A.n_groups) return;
+    const uint32_t n = A.counts[g];
     if (n <= A.slice) return;
     const uint32_t s0 = A.slice_begin[g], ns = A.slice_begin[g + 1] - s0;
     const double* p = A.part + 2 * (uint64_t)s0;
     double a = 0.0, b = 0.0;
     for (uint32_t i = threadIdx.x; i < ns; i += kObsThreads) a += p[2 * (uint64_t)i];
-    a = block_sum(a, lds);
+    a = block_sum<kObsThreads>(a, lds);
     const double mean = a / (double)n;
     for (uint32_t i = threadIdx.x; i < ns; i += kObsThreads) {
         b += p[2 * (uint64_t)i + 1];
@@ -160,7 +201,7 @@ __global__ __launch_bounds__(kObsThreads) void obs_combine_kernel(ObsArgs A, int
             b += cnt * (d * d);
         }
     }
-    b = block_sum(b, lds);
+    b = block_sum<kObsThreads>(b, lds);
     if (threadIdx.x == 0) obs_finish(kind, n, a, b, A.out + 2 * (uint64_t)g);
 }
 
@@ -373,17 +414,31 @@ int phase_histogram_impl(sde_ctx* ctx, const float* theta, uint64_t n, uint64_t 
     return launch_hist(ctx, A, hist_kernel<PhaseBin>, stream);
 }
 
-template <int ITEMS>
-static void launch_obs(int kind, const ObsArgs& A, uint32_t slices, hipStream_t stream)
+template <int KIND>
+static void launch_obs_kind(uint32_t items, bool split, const ObsArgs& A, hipStream_t stream)
 {
-    const dim3 grid(slices), block(kObsThreads);
+    void (*kern)(ObsArgs);
+    uint32_t threads = kObsThreads;
+    if (split) {
+        kern = items <= 4 ? obs_slice_kernel<KIND, 4> : items <= 8 ? obs_slice_kernel<KIND, 8> : obs_slice_kernel<KIND, 16>;
+    } else if (items <= 1) {
+        kern = obs_group_kernel<KIND, kObsThreads / kWave, kWave>;
+        threads = kWave;
+    } else {
+        kern = items <= 4    ? obs_group_kernel<KIND, 4, kObsThreads>
+               : items <= 16 ? obs_group_kernel<KIND, 16, kObsThreads>
+                             : obs_group_kernel<KIND, kObsGroupItems, kObsThreads>;
+    }
+    hipLaunchKernelGGL(kern, obs_grid(split ? A.n_slices : A.n_groups), dim3(threads), 0, stream, A);
+}
+
+static void launch_obs(int kind, uint32_t items, bool split, const ObsArgs& A, hipStream_t stream)
+{
     switch (kind) {
-    case SDE_OBS_MEAN_F32: hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_MEAN_F32, ITEMS>), grid, block, 0, stream, A); break;
-    case SDE_OBS_MEAN_F64: hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_MEAN_F64, ITEMS>), grid, block, 0, stream, A); break;
-    case SDE_OBS_MEANSQ_F32:
-        hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_MEANSQ_F32, ITEMS>), grid, block, 0, stream, A);
-        break;
-    default: hipLaunchKernelGGL((obs_slice_kernel<SDE_OBS_ORDER, ITEMS>), grid, block, 0, stream, A); break;
+    case SDE_OBS_MEAN_F32: return launch_obs_kind<SDE_OBS_MEAN_F32>(items, split, A, stream);
+    case SDE_OBS_MEAN_F64: return launch_obs_kind<SDE_OBS_MEAN_F64>(items, split, A, stream);
+    case SDE_OBS_MEANSQ_F32: return launch_obs_kind<SDE_OBS_MEANSQ_F32>(items, split, A, stream);
+    default: return launch_obs_kind<SDE_OBS_ORDER>(items, split, A, stream);
     }
 }
 
@@ -394,34 +449,54 @@ int observables_impl(sde_ctx* ctx, int kind, const void* in, const uint32_t* cou
     if (!in || !counts || !host_out || n_groups == 0) return fail(ctx, SDE_ERR_INVALID, "null argument or no groups");
     if (!aligned(in, kind == SDE_OBS_MEAN_F64 ? 8 : 4)) return fail(ctx, SDE_ERR_INVALID, "misaligned input");
     uint64_t total = 0;
-    for (uint32_t g = 0; g < n_groups; ++g) total += counts[g];
+    uint32_t most = 0;
+    for (uint32_t g = 0; g < n_groups; ++g) {
+        total += counts[g];
+        most = counts[g] > most ? counts[g] : most;
+    }
     // Slices of 4 elements per lane until there are 4 workgroups per CU, then
     // of up to 16 (fewer partials for the same bandwidth).
-    int items = 4;
-    while (items < kObsItems && total / ((uint64_t)items * kObsThreads) >= 4ull * ctx->n_cu) items *= 2;
+    const uint64_t enough = 4ull * ctx->n_cu;
+    uint32_t items = 4;
+    while (items < kObsItems && total / ((uint64_t)items * kObsThreads) >= enough) items *= 2;
     ObsArgs A;
-    A.slice = (uint32_t)items * kObsThreads;
-    // layout of the workspace: first[n_groups] (u64) | counts[n_groups] (u32) | slice_begin[n_groups + 1] (u32)
-    std::vector<unsigned char> meta((size_t)n_groups * 16 + 4);
+    A.slice = items * kObsThreads;
+    // No group is split where one slice holds the longest, or where there are 4
+    // groups per CU and a workgroup's registers hold the longest, or, for the
+    // order parameter (a single pass), it is no longer than the mean of as many
+    // (4000 groups of 4097 floats: their means 50 us in two slices each and a
+    // launch to add them, 33 so).
+    const bool split = most > A.slice && !(n_groups >= enough && most <= kObsGroupItems * kObsThreads) &&
+                       !(kind == SDE_OBS_ORDER && most <= total / enough);
+    if (!split) items = (uint32_t)(((uint64_t)most + kObsThreads - 1) / kObsThreads);
+    // layout of the workspace: first[n_groups] (u64) | counts[n_groups] (u32) |
+    // where groups are split slice_begin[n_groups + 1] (u32)
+    const size_t meta_bytes = (size_t)n_groups * 12 + (split ? 4 * ((size_t)n_groups + 1) : 0);
+    std::vector<uint64_t> meta((meta_bytes + 7) / 8);
     uint64_t off = 0, slices = 0;
-    bool split = false;
     for (uint32_t g = 0; g < n_groups; ++g) {
-        const uint32_t s32 = (uint32_t)slices;
-        std::memcpy(meta.data() + 8 * (size_t)g, &off, 8);
-        std::memcpy(meta.data() + 12 * (size_t)n_groups + 4 * (size_t)g, &s32, 4);
+        meta[g] = off;
         off += counts[g];
-        slices += counts[g] ? ((uint64_t)counts[g] + A.slice - 1) / A.slice : 1;  // an empty group still has a result
-        split |= counts[g] > A.slice;
-        if (slices > 0x7fffffffull) return fail(ctx, SDE_ERR_INVALID, "observables: too many elements in one call");
     }
-    const uint32_t all = (uint32_t)slices;
-    std::memcpy(meta.data() + 16 * (size_t)n_groups, &all, 4);
-    std::memcpy(meta.data() + 8 * (size_t)n_groups, counts, 4 * (size_t)n_groups);
-    int st = upload(ctx, kSlotMisc, 3, meta.data(), meta.size(), stream);
+    unsigned char* words = reinterpret_cast<unsigned char*>(meta.data() + n_groups);
+    std::memcpy(words, counts, 4 * (size_t)n_groups);
+    if (split) {
+        words += 4 * (size_t)n_groups;
+        for (uint32_t g = 0; g < n_groups; ++g) {
+            const uint32_t s32 = (uint32_t)slices;
+            std::memcpy(words + 4 * (size_t)g, &s32, 4);
+            slices += counts[g] ? ((uint64_t)counts[g] + A.slice - 1) / A.slice : 1;  // an empty group still has a result
+            if (slices > 0x7fffffffull) return fail(ctx, SDE_ERR_INVALID, "observables: too many elements in one call");
+        }
+        const uint32_t all = (uint32_t)slices;
+        std::memcpy(words + 4 * (size_t)n_groups, &all, 4);
+    }
+    int st = upload(ctx, kSlotMisc, 3, meta.data(), meta_bytes, stream);
     if (st) return st;
     // The results (16 B a group) go straight to pinned host memory, which the
     // final synchronization makes visible: no copy after the kernels (a call
-    // on one group of 2^19 values 33 -> 24 us).
+    // on one group of 2^19 values 33 -> 24 us; of any number of groups it is
+    // no slower: 2000 groups of 100 values 29 -> 20, 262144 of 10 831 -> 775).
     const size_t out_bytes = (size_t)n_groups * 2 * sizeof(double);
     DevBuf& host = ctx->obs_host;
     if (host.bytes < out_bytes) {
@@ -443,17 +518,14 @@ int observables_impl(sde_ctx* ctx, int kind, const void* in, const uint32_t* cou
     A.first = reinterpret_cast<const uint64_t*>(dmeta);
     A.counts = reinterpret_cast<const uint32_t*>(dmeta + 8 * (size_t)n_groups);
     A.slice_begin = A.counts + n_groups;
-    A.out = static_cast<double*>(host.ptr);
     A.part = static_cast<double*>(part);
+    A.out = static_cast<double*>(host.ptr);
     A.n_groups = n_groups;
-    switch (items) {
-    case 4: launch_obs<4>(kind, A, all, stream); break;
-    case 8: launch_obs<8>(kind, A, all, stream); break;
-    default: launch_obs<16>(kind, A, all, stream); break;
-    }
+    A.n_slices = (uint32_t)slices;
+    launch_obs(kind, items, split, A, stream);
     SDE_HIP(ctx, hipGetLastError());
     if (split) {
-        hipLaunchKernelGGL(obs_combine_kernel, dim3(n_groups), dim3(kObsThreads), 0, stream, A, kind);
+        hipLaunchKernelGGL(obs_combine_kernel, obs_grid(n_groups), dim3(kObsThreads), 0, stream, A, kind);
         SDE_HIP(ctx, hipGetLastError());
     }
     SDE_HIP(ctx, hipStreamSynchronize(stream));
