@@ -969,6 +969,7 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
     extern __shared__ float held[];  // [lds_theta + lds_carry rows][kMFSThreads]
     if (threadIdx.x == 0) lds_ok = 1;  // made visible by the exchange's first barrier
     const uint32_t r = blockIdx.x / A.G, w = blockIdx.x % A.G, tid = threadIdx.x;
+    const uint32_t wave0 = uniform_u32(tid & ~(uint32_t)(kWave - 1));  // the wave's first column
     const uint64_t N = A.N;
     const uint64_t i0 = std::min<uint64_t>(N, (uint64_t)w * A.chunk), i1 = std::min<uint64_t>(N, i0 + A.chunk);
     float* th = A.theta + (uint64_t)r * N + i0;
@@ -1041,7 +1042,7 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
             const uint64_t at = (uint64_t)row * kMFSThreads + tid;
 #pragma unroll
             for (int k = 0; k < kMFSBatch; ++k) {
-                if ((uint32_t)(k * kMFSThreads) >= n_left) break;  // a row past the slice
+                if (k * kMFSThreads + wave0 >= n_left) break;  // this wave's part of the row is past the slice
                 const bool in = k * kMFSThreads + tid < n_left;
                 const uint64_t e = at + k * kMFSThreads;
                 const float F1 = fmaf(A.kn, fmaf(cos_rev(t0[k]), Sf, -sin_rev(t0[k]) * Cf), om[k]);
@@ -1087,7 +1088,7 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
             const uint64_t at = (uint64_t)row * kMFSThreads + tid;
 #pragma unroll
             for (int k = 0; k < kMFSBatch; ++k) {
-                if ((uint32_t)(k * kMFSThreads) >= n_left) break;  // a row past the slice
+                if (k * kMFSThreads + wave0 >= n_left) break;  // this wave's part of the row is past the slice
                 const bool in = k * kMFSThreads + tid < n_left;
                 const float t = fmaf(A.hdt2pi, A.kn * fmaf(cos_rev(tt[k]), Sf, -sin_rev(tt[k]) * Cf), cv[k]);
                 const float u = t - floorf(t);
@@ -1123,12 +1124,21 @@ __global__ __launch_bounds__(kMFSThreads, 1) void kuramoto_mfs_kernel(MFSArgs A)
         ++local;
     }
     bool bad = false;
-    for (uint32_t row = 0; row < rows; ++row) {
+    // the rows in LDS go to memory; the others are only looked at (loops of
+    // their own: a store between the loads would keep them apart)
+#pragma unroll 4
+    for (uint32_t row = 0; row < rows_theta; ++row) {
         const uint64_t e = (uint64_t)row * kMFSThreads + tid;
         if (e >= i1 - i0) break;
-        const float t = row < rows_theta ? held[row * kMFSThreads + tid] : th[e];
-        if (row < rows_theta) th[e] = t;
+        const float t = held[row * kMFSThreads + tid];
+        th[e] = t;
         bad |= !isfinite(t);
+    }
+    for (uint32_t row = rows_theta; row < rows; row += kMFSBatch) {
+        float t[kMFSBatch];
+        load(th, row, t);
+#pragma unroll
+        for (int k = 0; k < kMFSBatch; ++k) bad |= !isfinite(t[k]);  // past the end the last one again
     }
     if (__ballot(bad) != 0 && (tid & (kWave - 1)) == 0) atomicOr(A.flag, 1);
 }
