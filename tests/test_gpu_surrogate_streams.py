@@ -72,3 +72,23 @@ def test_replays_beside_calls(surrogate):
         torch.cuda.synchronize()
         assert torch.equal(out, ref[0])
         assert all(torch.equal(b, ref[1]) for b in beside)
+
+
+def test_null_stream_and_another(surrogate):
+    """The null stream orders its own calls without an event: each way from it
+    to another stream and back, several calls at a time."""
+    sde, s, dev = surrogate
+    n = 300
+    X = [_query(n, seed, dev) for seed in range(2)]
+    ref = [_outputs(n, dev) for _ in X]
+    for x, r in zip(X, ref):
+        sde.sde_surrogate_predict(s, x, r[0], r[1])
+        torch.cuda.synchronize()
+    other = torch.cuda.Stream(dev)
+    turns = [0, 0, 1, 0, 1, 1, 0, 0, 0, 1, 0, 1] * 3
+    out = [_outputs(n, dev) for _ in turns]
+    torch.cuda.synchronize()
+    for k, o in zip(turns, out):
+        sde.sde_surrogate_predict(s, X[k], o[0], o[1], stream=other if k else torch.cuda.default_stream(dev))
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, ref[k]) for k, o in zip(turns, out))
