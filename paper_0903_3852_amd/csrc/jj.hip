@@ -342,12 +342,16 @@ struct JJRing {
     R e[2 * kBlocks][8];  // the drive terms, the same for every lane
 };
 
-template <typename R>
+template <typename R, bool INERTIAL>
 struct RingNoise {
     // Blocks taken per loop iteration: a wave alone on its SIMD issues an
     // instruction every ~6 cycles whatever it is, so the loop's scalar work
-    // and register copies count like the steps.
-    static constexpr uint32_t kUnroll = 4;
+    // and register copies count like the steps.  Two in FP64 with inertia: the
+    // values of four leave no registers to start a force before the one ahead
+    // of it is done (1000 paths x 3000 steps, Heun 497 -> 389 us, Euler-Maruyama
+    // 275 -> 223).  Without inertia a force waits for the one ahead of it anyway
+    // (446 : 451 and 259 : 262 with four : two).
+    static constexpr uint32_t kUnroll = sizeof(R) == 8 && INERTIAL ? 2 : 4;
     static constexpr uint32_t kBlocks = JJRing<R>::kBlocks;
     const JJRing<R>& ring;
     uint32_t left = 0, at = 0;  // blocks left in the current buffer; its next slot
@@ -623,8 +627,19 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, c
     if (__ballot(bad) != 0 && lane == 0) atomicOr(A.flag, 1);
 }
 
+// Most waves per SIMD that the compiler is to leave registers for.  FP64 steps
+// are chains of table lookups; two or three waves whose lookups are ahead of
+// their use do better than five that wait for each one, which is what the
+// compiler makes by itself or not, as the code around the loop happens to
+// be.  2^18 paths x 400 steps at 2 paths per lane, as it came out : 2 waves : 3,
+// us: Heun 313 : 309 : 344, overdamped 340 : 301 : 301, Euler-Maruyama 260 :
+// 236 : 235; at 1 path per lane 341 : 314 : 320, 331 : 367 : 315, 261 : 287 : 250.
+template <typename R, int PPT>
+constexpr int kMostWaves = sizeof(R) == 4 ? 8 : PPT == 2 ? 2 : 3;
+
 template <typename R, int PPT, int SCHEME, bool INERTIAL, bool COSF, bool TAB>
-__global__ __launch_bounds__(256) void jj_persistent_kernel(JJArgs A)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, kMostWaves<R, PPT>))) void
+jj_persistent_kernel(JJArgs A)
 {
     __shared__ __attribute__((aligned(16))) R drive[4][TAB ? kDriveTable : 1];
     R* mine = drive[threadIdx.x / kWave];  // this wave's own: no barrier
@@ -678,7 +693,7 @@ __global__ __launch_bounds__(kSplitThreads) void jj_split_kernel(JJArgs A)
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = uniform_u32(threadIdx.x / kWave);
     const uint32_t pid[1] = {it.chunk * kWave + lane};
     if (wave == 0) {
-        RingNoise<R> src{ring};
+        RingNoise<R, INERTIAL> src{ring};
         jj_item<R, 1, SCHEME, INERTIAL, COSF>(A, P, T, it.point, it.chunk, pid, src);
         return;
     }
@@ -861,9 +876,11 @@ constexpr int kSplitChoice = 17;
 // Most items (of 64 paths) per CU the split kernel is tried for, FP32 and
 // FP64.  With more, every SIMD has waves enough to switch between, and the
 // waves that draw ahead only take issue slots.  One point, best persistent
-// against split, us: 10^4 FP32 steps of 4096 paths 831 : 486, 32768 (2 per
-// CU) 852 : 620, 98304 (6) 1327 : 1248, 131072 (8) 1329 : 1566; 2000 FP64
-// steps of 4096 paths 598 : 360, 49152 (3) 637 : 490, 65536 (4) 643 : 755.
+// against split, us: 10^4 FP32 steps of 4096 paths 802 : 439, 32768 (2 per
+// CU) 808 : 569, 65536 (4) 823 : 824, 98304 (6) 1336 : 1143; 2000 FP64 steps of
+// 4096 paths 445 : 269, 32768 (2) 451 : 320, 49152 (3) 455 : 370.  Past the
+// lines, of earlier versions of both: 131072 FP32 paths (8) 1329 : 1566, 65536
+// FP64 paths (4) 643 : 755.
 constexpr uint32_t kSplitItemsPerCU32 = 6, kSplitItemsPerCU64 = 3;
 
 struct JJLaunch {
