@@ -123,7 +123,7 @@ PEAK_HBM = 8.0e12
 # Measured HBM bytes per oscillator-step of the streamed mean field (Fig. 4),
 # from profiles/kuramoto_fig4_hbm_counters.md; valid for that kernel source.
 FIG4_TRAFFIC_PER_OSC_STEP = 19.05
-FIG4_TRAFFIC_SOURCE_SHA1 = "9814ff20b268c564384db2e7e7be9354b653f763"
+FIG4_TRAFFIC_SOURCE_SHA1 = "1d8a4012d731ecfc1da282fea38990822e371999"
 
 
 def _source_sha1(*files):
@@ -138,10 +138,10 @@ def _source_sha1(*files):
 # (FETCH_SIZE x 2.00 + WRITE_SIZE x 1.00, copy-calibrated), and its VALU
 # counters per path-step, from profiles/jj_scan_valu_counters.md.  Only valid
 # for the kernel source they were measured on.
-JJ_TRAFFIC_BYTES = (2 * 3840.4 + 6591.3) * 1024
-JJ_TRAFFIC_SOURCE_SHA1 = "387ce42d9fc2404733e6858d53a96eb143023c4f"
-JJ_VALU_COUNTERS = {"valu_instructions_per_path_step": 30.75, "transcendental_per_path_step": 4.00,
-                    "salu_instructions_per_path_step": 2.39, "valu_instructions_per_simd_cycle": 0.245,
+JJ_TRAFFIC_BYTES = (2 * 5271.1 + 12887.7) * 1024
+JJ_TRAFFIC_SOURCE_SHA1 = "01f324dd5f389a5f35e8381e02384e568dcdb4e7"
+JJ_VALU_COUNTERS = {"valu_instructions_per_path_step": 30.91, "transcendental_per_path_step": 4.00,
+                    "salu_instructions_per_path_step": 4.30, "valu_instructions_per_simd_cycle": 0.258,
                     "source": "profiles/jj_scan_valu_counters.md"}
 
 

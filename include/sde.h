@@ -274,7 +274,7 @@ enum {
 /*
  * Reduces consecutive groups of a device array: group g covers counts[g]
  * elements following those of groups < g.  Sums are taken in FP64 with a
- * fixed order (wavefront shuffles, then LDS, then a second pass), so the
+ * fixed order (wavefront shuffles, LDS, the slices of a long group), so the
  * result is bitwise reproducible.  Writes host_out[g][0..1].  Synchronizes
  * `hip_stream`.  The standard error uses the n-1 sample variance (0 when
  * counts[g] < 2).  Example: <v> +- SE of each point from the per-path
@@ -344,6 +344,7 @@ int sde_phase_histograms(sde_ctx* ctx, const float* theta /* [device] */, uint64
  * Raw input features of a point are (a, omega, f, log10 D, gamma); they are
  * normalized with the scaling below before entering the network.
  * Calls on a surrogate are ordered on its context (one host thread).
+ * Predictions enqueued on different streams may overlap.
  */
 typedef struct sde_surrogate sde_surrogate;
 typedef struct {

@@ -307,7 +307,8 @@ __device__ __forceinline__ void jj_step(const JJPointT<R>& P, const JJTables<R>&
 // without scalar loads to wait for and without the 5 multiply-adds and 5
 // moves that wave-uniform FP32 arithmetic takes on the vector unit (1500
 // points x 1000 paths x 2000 steps at 1, 2, 4 paths per lane: 3402, 3143,
-// 2928 -> 3148, 2949, 2846 us; FP64: no change, so its kernels go without).
+// 2928 -> 3148, 2949, 2846 us, and 2829, 2716, 2728 with the present block
+// loop; FP64: no change, so its kernels go without).
 constexpr uint32_t kDriveTable = 1024;  // entries per wave: periods of up to kDriveTable - 8 steps
 
 template <typename R, int PPT, bool TAB>
@@ -506,11 +507,12 @@ __device__ __forceinline__ void jj_item(const JJArgs& A, const JJPointT<R>& P, c
         if (j0 == 0 && left >= 4) {
             // The whole blocks up to the next event: the end of the call, the
             // start of the window, the block that a fold falls into (or ends
-            // at).  Their loop is one basic block: the compiler overlaps the noise, the four steps and the drive's loads, which
-            // branches for the window and the fold between the steps had kept
-            // apart (one point of 4096 paths, one wave per SIMD: 1335 -> 885 us
-            // for 10^4 steps; 4096 x 1024 paths x 5000 steps, ALU-bound:
-            // 18.4 -> 17.7 ms; a ragged batch 4.41 -> 3.72 ms).
+            // at).  Their loop is one basic block: the compiler overlaps the
+            // noise, the four steps and the drive's loads, which branches for
+            // the window and the fold between the steps had kept apart (one
+            // point of 4096 paths, one wave per SIMD: 1335 -> 885 us for 10^4
+            // steps; 4096 x 1024 paths x 5000 steps, ALU-bound: 18.4 -> 17.7 ms;
+            // a ragged batch 4.41 -> 3.72 ms).
             constexpr bool kTicks = Noise::kUnroll > 1;
             const bool window = n >= P.n_transient;
             uint64_t blocks = left >> 2;

@@ -930,7 +930,7 @@ __global__ __launch_bounds__(kMFPThreads, 1) void kuramoto_mfp_kernel(MFArgs A)
 // between the passes tt in its place, for the first 36 rows of 1024
 // oscillators of a workgroup's slice, and with what is left their carry: 16
 // and 8 bytes less per oscillator-step (2^24 oscillators, 64 rows: 19 bytes;
-// 2^21: 4).  A step of 2^24 on one device 91 -> 70 us, of 2^22 28 -> 22 us;
+// 2^21: 4).  A step of 2^24 on one device 91 -> 67-70 us, of 2^22 27 -> 22 us;
 // bound by the vector unit, mostly Philox and Box-Muller (about 58 us), with
 // the traffic (62 us) beside it.  The noise is component
 // n & 3 of the Gaussians of Philox block n >> 2, regenerated every step: the
